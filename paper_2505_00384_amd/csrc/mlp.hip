@@ -5,9 +5,10 @@
 // n_out = N^3.  Parameters flat [W1, b1, W2, b2, W3, b3], W row-major
 // [out][in]; FP32 master weights and Adam moments, BF16 working copies.
 // Every product runs on the gfx950 matrix cores (v_mfma_f32_16x16x32_bf16
-// for the K-contiguous forward products, v_mfma_f32_16x16x16_bf16 for the
-// strided ones of the backward pass; FP32 accumulation); activations entering a product are BF16 (round to
-// nearest even), biases, losses and gradients of the biases are FP32.
+// for the forward products and the weight gradients,
+// v_mfma_f32_16x16x16_bf16 for the back-propagated signals; FP32
+// accumulation); activations entering a product are BF16 (round to nearest
+// even), biases, losses and gradients of the biases are FP32.
 //
 // Features of cell K (divided by s = RMS(r_K), zero when s = 0): r_K in local
 // order, then for each face -x,+x,-y,+y,-z,+z the neighbour's residual on its
@@ -44,80 +45,9 @@ __device__ __forceinline__ uint16_t f2bf(float f)
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
 // ---------------------------------------------------------------------------
-// C(m, n) = sum_k A(m, k) B(n, k) (+ bias[n]) (ReLU), A(m,k) = A[m*sam + k*sak],
-// B(n,k) = B[n*sbn + k*sbk], BF16 operands, FP32 accumulation on MFMA.
-// 64 x 64 output tile per workgroup of 4 waves, 32 x 32 per wave.
-// ---------------------------------------------------------------------------
-constexpr int TM = 64, TN = 64, TK = 32;
-
-__global__ void __launch_bounds__(256)
-k_gemm(int M, int N, int K, const uint16_t *__restrict__ A, int64_t sam, int64_t sak,
-       const uint16_t *__restrict__ B, int64_t sbn, int64_t sbk, const float *__restrict__ bias,
-       int relu, float *C32, int64_t ldc32, uint16_t *C16, int64_t ldc16)
-{
-    __shared__ uint16_t sA[TM][TK + 4];
-    __shared__ uint16_t sB[TN][TK + 4];
-    const int m0 = blockIdx.x * TM, n0 = blockIdx.y * TN;
-    const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
-    const int wm = (wave & 1) * 32, wn = (wave >> 1) * 32;
-    f32x4 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < K; k0 += TK) {
-        // stage the tiles (zero outside the matrices)
-        for (int e = t; e < TM * TK; e += 256) {
-            const int r = e / TK, kk = e % TK;
-            const int m = m0 + r, k = k0 + kk;
-            sA[r][kk] = (m < M && k < K) ? A[(int64_t)m * sam + (int64_t)k * sak] : (uint16_t)0;
-            const int n = n0 + r;
-            sB[r][kk] = (n < N && k < K) ? B[(int64_t)n * sbn + (int64_t)k * sbk] : (uint16_t)0;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int ks = 0; ks < TK; ks += 16) {
-            // operand layout of the 16x16x16 MFMA: lane l holds
-            //   A[row = l % 16][k = 4 (l / 16) .. +3],  B[k = 4 (l / 16) .. +3][col = l % 16]
-            const int rr = lane & 15, kq = (lane >> 4) * 4;
-            bf16x4 fa[2], fb[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    fa[i][q] = (short)sA[wm + 16 * i + rr][ks + kq + q];
-                    fb[i][q] = (short)sB[wn + 16 * i + rr][ks + kq + q];
-                }
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(fa[i], fb[j], acc[i][j], 0, 0, 0);
-        }
-        __syncthreads();
-    }
-    // result layout: lane l holds C[row = 4 (l / 16) + q][col = l % 16], q = 0..3
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int m = m0 + wm + 16 * i + 4 * (lane >> 4) + q;
-                const int n = n0 + wn + 16 * j + (lane & 15);
-                if (m < M && n < N) {
-                    float v = acc[i][j][q] + (bias ? bias[n] : 0.f);
-                    if (relu) v = v > 0.f ? v : 0.f;
-                    if (C32) C32[(int64_t)m * ldc32 + n] = v;
-                    if (C16) C16[(int64_t)m * ldc16 + n] = f2bf(v);
-                }
-            }
-}
-
-// ---------------------------------------------------------------------------
-// The same product when both operands are K-contiguous (A [M][K], B [N][K],
-// K a multiple of 32, rows 16-byte aligned) -- every forward product of the
-// network.  128 x 128 output tile per workgroup of 4 waves (64 x 64 each, a
+// C(m, n) = sum_k A(m, k) B(n, k) (+ bias[n]) (ReLU) with K-contiguous BF16
+// operands (A [M][K], B [N][K], K a multiple of 32, rows 16-byte aligned) --
+// the products of the batched forward pass.  128 x 128 output tile per workgroup of 4 waves (64 x 64 each, a
 // 4 x 4 grid of 16 x 16 accumulators), 16-byte tile loads into padded LDS
 // rows, v_mfma_f32_16x16x32_bf16 (gfx950): lane l supplies A[row l % 16] and
 // B[col l % 16] at the same 8 consecutive k, 8 (l / 16) .. + 7, so the
@@ -188,54 +118,22 @@ k_gemm_nt(int M, int N, int K, const uint16_t *__restrict__ A, int64_t lda,
         }
 }
 
-hipError_t gemm(hipStream_t st, int M, int N, int K, const uint16_t *A, int64_t sam, int64_t sak,
-                const uint16_t *B, int64_t sbn, int64_t sbk, const float *bias, int relu, float *C32,
+hipError_t gemm(hipStream_t st, int M, int N, int K, const uint16_t *A, int64_t lda,
+                const uint16_t *B, int64_t ldb, const float *bias, int relu, float *C32,
                 int64_t ldc32, uint16_t *C16, int64_t ldc16)
 {
     if (M <= 0 || N <= 0) return hipSuccess;
-    if (sak == 1 && sbk == 1 && K % NK == 0 && sam % 8 == 0 && sbn % 8 == 0 &&
-        ((uintptr_t)A & 15) == 0 && ((uintptr_t)B & 15) == 0) {
-        dim3 grid((M + NM - 1) / NM, (N + NN - 1) / NN);
-        hipLaunchKernelGGL(k_gemm_nt, grid, dim3(256), 0, st, M, N, K, A, sam, B, sbn, bias, relu,
-                           C32, ldc32, C16, ldc16);
-        return hipGetLastError();
-    }
-    dim3 grid((M + TM - 1) / TM, (N + TN - 1) / TN);
-    hipLaunchKernelGGL(k_gemm, grid, dim3(256), 0, st, M, N, K, A, sam, sak, B, sbn, sbk, bias, relu,
-                       C32, ldc32, C16, ldc16);
+    if (K % NK || lda % 8 || ldb % 8 || ((uintptr_t)A & 15) || ((uintptr_t)B & 15))
+        return hipErrorInvalidValue;
+    dim3 grid((M + NM - 1) / NM, (N + NN - 1) / NN);
+    hipLaunchKernelGGL(k_gemm_nt, grid, dim3(256), 0, st, M, N, K, A, lda, B, ldb, bias, relu, C32,
+                       ldc32, C16, ldc16);
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
 // elementwise / reduction kernels
 // ---------------------------------------------------------------------------
-__global__ void k_weights_to_bf16(int64_t n, const float *__restrict__ w, int rows, int cols,
-                                  int ld, uint16_t *out)
-{
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= (int64_t)rows * ld) return;
-    const int r = (int)(i / ld), c = (int)(i % ld);
-    out[i] = c < cols ? f2bf(w[(int64_t)r * cols + c]) : (uint16_t)0;
-    (void)n;
-}
-
-// fp32 [rows][cols] -> bf16 in the fused kernel's fragment order: for
-// column tile ct (16 output columns), k-step s (32 inputs) and lane l the
-// 8 values W[16 ct + l % 16][32 s + 8 (l / 16) .. + 7] sit at
-// ((ct ks + s) 64 + l) 8, so that one wave's fragment load is 1 KB in a
-// row and its whole slice of a layer is contiguous; rows past rows and
-// inputs past cols are zero
-__global__ void k_weights_frag(const float *__restrict__ w, int rows, int cols, int ks, uint16_t *out)
-{
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= (int64_t)((rows + 15) / 16) * ks * 512) return;
-    const int e = (int)(i & 7), lane = (int)((i >> 3) & 63);
-    const int64_t blk = i >> 9;
-    const int s = (int)(blk % ks), ct = (int)(blk / ks);
-    const int r = ct * 16 + (lane & 15), k = s * 32 + (lane >> 4) * 8 + e;
-    out[i] = (r < rows && k < cols) ? f2bf(w[(int64_t)r * cols + k]) : (uint16_t)0;
-}
-
 // fp32 [B][n_in] -> bf16 [B][ld]
 __global__ void k_pack(int64_t Bn, int n_in, int ld, const float *__restrict__ x, uint16_t *out)
 {
@@ -299,29 +197,6 @@ k_features(int n, int64_t n_cells, const double *__restrict__ r, const int32_t *
     if (threadIdx.x == 0) scale[c] = (float)sK;
 }
 
-// d_o = 2 (o - t) / (B n_out) (fp32 and bf16); partial sums of (o - t)^2
-__global__ void __launch_bounds__(256)
-k_loss_grad(int64_t total, float inv_count, const float *__restrict__ o, const float *__restrict__ tg,
-            float *d, uint16_t *db, double *part)
-{
-    __shared__ double sh[256];
-    double s = 0.0;
-    for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-        const float e = o[i] - tg[i];
-        s += (double)e * e;
-        const float g = 2.f * e * inv_count;
-        d[i] = g;
-        db[i] = f2bf(g);
-    }
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int k = 128; k > 0; k >>= 1) {
-        if ((int)threadIdx.x < k) sh[threadIdx.x] += sh[threadIdx.x + k];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
-}
-
 __global__ void __launch_bounds__(256) k_sum_parts(int nb, const double *part, double scale, float *out)
 {
     __shared__ double sh[256];
@@ -334,45 +209,6 @@ __global__ void __launch_bounds__(256) k_sum_parts(int nb, const double *part, d
         __syncthreads();
     }
     if (threadIdx.x == 0) out[0] = (float)(sh[0] * scale);
-}
-
-// d[b][j] *= (h[b][j] > 0) in place (fp32), bf16 copy
-__global__ void k_relu_back(int64_t total, const float *__restrict__ h, float *d, uint16_t *db)
-{
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    const float g = h[i] > 0.f ? d[i] : 0.f;
-    d[i] = g;
-    db[i] = f2bf(g);
-}
-
-// column sums out[j] = sum_b d[b][j] (fixed order), block per column
-__global__ void __launch_bounds__(256) k_colsum(int64_t Bn, int ncol, const float *__restrict__ d, float *out)
-{
-    __shared__ double sh[256];
-    const int j = blockIdx.x;
-    double s = 0.0;
-    for (int64_t b = threadIdx.x; b < Bn; b += 256) s += d[b * ncol + j];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int k = 128; k > 0; k >>= 1) {
-        if ((int)threadIdx.x < k) sh[threadIdx.x] += sh[threadIdx.x + k];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[j] = (float)sh[0];
-}
-
-__global__ void k_adam(int64_t n, float *w, const float *__restrict__ g, float *m, float *v, float lr,
-                       float b1, float b2, float eps, float c1, float c2)
-{
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.f - b1) * gi;
-    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    w[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
 // per cell w_K = RMS(z_K) of the block-Jacobi output; z_K += w_K * o_K
@@ -733,6 +569,422 @@ k_mlp_fused(int64_t n_cells, const double *__restrict__ w, double *__restrict__ 
     }
 }
 
+// ---------------------------------------------------------------------------
+// One training step in three launches: k_train_fb (forward, loss gradient and
+// the back-propagated signals of 16 rows per workgroup), k_train_wgrad (weight
+// and bias gradients, the batch split into chunks) and k_params (sum of the
+// chunks, Adam, BF16 copies).  All three are latency bound at the trainer's
+// batch: at 2,048 rows (degree 4) the arithmetic takes 1.5 us at the matrix
+// rate of a large product, and every launch of the former chain of 23 (8
+// products, the strided ones 160 us each on 8 to 20 workgroups) waited for
+// the one before.  Measured there: see k_train_wgrad.
+//
+// The activations and signals that the weight gradients contract over the
+// batch are kept as BF16 in fragment order: for 32 batch rows s, column tile
+// ct (16 columns) and lane l the 8 values [32 s + 8 (l / 16) .. + 7][16 ct +
+// l % 16] are contiguous, at ((s CT + ct) 64 + l) 8, so k_train_wgrad loads
+// both operands of v_mfma_f32_16x16x32_bf16 straight into registers.  Rows
+// past the batch are zero.
+// ---------------------------------------------------------------------------
+struct TrainBuf {
+    float *h1, *h2, *o, *d_o, *dh2, *dh1;             // [B][width]
+    uint16_t *xf, *h1f, *h2f, *dof, *dh2f, *dh1f;     // fragment order
+};
+
+// the workgroup's 16 rows (half hb of a 32-row step) of a BF16 tile in LDS to
+// fragment order
+template <int LD>
+__device__ __forceinline__ void tile_to_frags(const uint16_t (*sT)[LD], int CT, int64_t step, int hb,
+                                              uint16_t *__restrict__ out)
+{
+    for (int i = threadIdx.x; i < CT * 32; i += 64 * FW) {
+        const int ct = i >> 5, g = (i >> 4) & 1, c = i & 15;
+        union { uint16_t h[8]; uint4 v; } u;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) u.h[e] = sT[8 * g + e][16 * ct + c];
+        *(uint4 *)(out + (((step * CT + ct) * 64) + (2 * hb + g) * 16 + c) * 8) = u.v;
+    }
+}
+
+// acc = (16 rows of sA) x (column tile of the transposed weights in fb) by
+// v_mfma_f32_16x16x16_bf16: a lane's 8 weights are the two 16-deep halves of
+// a 32-deep step, inputs 4 (l / 16) .. + 3 of each
+template <int K, int LDA>
+__device__ __forceinline__ f32x4 back_mfma(const uint16_t (*sA)[LDA], const uint4 (&fb)[K / 32][1], int lane)
+{
+    const int rr = lane & 15, kq = (lane >> 4) * 4;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < K / 32; ++s)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const bf16x4 fa = __builtin_bit_cast(bf16x4, *(const uint2 *)&sA[rr][s * 32 + 16 * h + kq]);
+            const uint2 w2 = h ? uint2{fb[s][0].z, fb[s][0].w} : uint2{fb[s][0].x, fb[s][0].y};
+            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(fa, __builtin_bit_cast(bf16x4, w2), acc, 0, 0, 0);
+        }
+    return acc;
+}
+
+// Forward and backward signals of 16 batch rows, one column tile of every
+// 256-wide layer per wave, so that the lane that made an activation also
+// masks its signal and keeps the value in a register.  The bound is each
+// workgroup's chain of five layers (weights from L2, products, barrier), so a
+// layer's weights are requested before the previous layer's products, at
+// degrees up to 4 (above, their registers would spill).
+template <int N>
+__global__ void __launch_bounds__(64 * FW)
+k_train_fb(int64_t B, const float *__restrict__ feats, const float *__restrict__ targets,
+           const uint16_t *__restrict__ wfr, const uint16_t *__restrict__ wbk,
+           const float *__restrict__ b1, const float *__restrict__ b2, const float *__restrict__ b3,
+           float inv_count, TrainBuf t, double *__restrict__ part)
+{
+    constexpr int NF = N * N, ND = NF * N, NIN = ND + 6 * NF + 1, LDX = ((NIN + 31) / 32) * 32;
+    constexpr int NT3 = (ND + 15) / 16, PER3 = (NT3 + FW - 1) / FW, NDK = ((ND + 31) / 32) * 32;
+    constexpr int KS1 = LDX / 32, KS2 = HID / 32, KSD = NDK / 32, CTO = (ND + 15) / 16;
+    constexpr bool AHEAD = N <= 5;
+    static_assert(HID == 16 * FW && NDK <= LDX, "one column tile of a hidden layer per wave");
+    __shared__ __align__(16) uint16_t sX[16][LDX + 8];     // inputs, then d loss / d output
+    __shared__ __align__(16) uint16_t sA[16][HID + 8];     // hidden 1, then its signal
+    __shared__ __align__(16) uint16_t sB[16][HID + 8];     // hidden 2
+    __shared__ __align__(16) uint16_t sC[16][HID + 8];     // signal of hidden 2
+    __shared__ double sl[FW];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t r0 = (int64_t)blockIdx.x * 16, step = blockIdx.x >> 1;
+    const int hb = blockIdx.x & 1;
+    const int ccol = lane & 15, crow = 4 * (lane >> 4);
+    const uint16_t *__restrict__ w2f = wfr + (int64_t)FW * KS1 * 512;
+    const uint16_t *__restrict__ w3f = w2f + (int64_t)FW * KS2 * 512;
+    const uint16_t *__restrict__ w3t = wbk;
+    const uint16_t *__restrict__ w2t = wbk + (int64_t)FW * KSD * 512;
+    uint4 f1[KS1][1], f2[KS2][1], f3[KS2][PER3];
+    constexpr int XPT = (16 * LDX + 64 * FW - 1) / (64 * FW);
+    float xv[XPT];
+#pragma unroll
+    for (int u = 0; u < XPT; ++u) {
+        const int idx = tid + u * 64 * FW, r = idx / LDX, e = idx % LDX;
+        const bool ok = idx < 16 * LDX && r0 + r < B && e < NIN;
+        xv[u] = feats[ok ? (r0 + r) * NIN + e : 0];
+        if (!ok) xv[u] = 0.f;
+    }
+    layer_weights<KS1, 1>(wfr, FW, wave, lane, f1);
+    const int n = 16 * wave + ccol;      // this lane's column of the hidden layers
+    const float bv1 = b1[n], bv2 = b2[n];
+#pragma unroll
+    for (int u = 0; u < XPT; ++u) {
+        const int idx = tid + u * 64 * FW;
+        if (idx < 16 * LDX) sX[idx / LDX][idx % LDX] = f2bf(xv[u]);
+    }
+    if constexpr (AHEAD) layer_weights<KS2, 1>(w2f, FW, wave, lane, f2);
+    __syncthreads();
+    float h1v[4], h2v[4];
+    auto hidden = [&](const f32x4 &acc, float bias, float (&hv)[4], uint16_t (*sT)[HID + 8], float *out) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const bool ok = r0 + crow + q < B;
+            hv[q] = ok ? fmaxf(acc[q] + bias, 0.f) : 0.f;
+            sT[crow + q][n] = f2bf(hv[q]);
+            if (ok) out[(r0 + crow + q) * HID + n] = hv[q];
+        }
+    };
+    {
+        f32x4 acc[1];
+        layer_mfma<LDX, 1, LDX + 8>(sX, f1, lane, acc);
+        hidden(acc[0], bv1, h1v, sA, t.h1);
+        tile_to_frags<LDX + 8>(sX, LDX / 16, step, hb, t.xf);
+    }
+    if constexpr (AHEAD) layer_weights<KS2, PER3>(w3f, NT3, PER3 * wave, lane, f3);
+    else layer_weights<KS2, 1>(w2f, FW, wave, lane, f2);
+    float bv3[PER3], tv[PER3][4];
+#pragma unroll
+    for (int j = 0; j < PER3; ++j) {
+        const int o = 16 * (PER3 * wave + j) + ccol;
+        bv3[j] = b3[o < ND ? o : 0];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const bool ok = o < ND && r0 + crow + q < B;
+            tv[j][q] = targets[ok ? (r0 + crow + q) * ND + o : 0];
+        }
+    }
+    __syncthreads();
+    {
+        f32x4 acc[1];
+        layer_mfma<HID, 1, HID + 8>(sA, f2, lane, acc);
+        hidden(acc[0], bv2, h2v, sB, t.h2);
+        tile_to_frags<HID + 8>(sA, HID / 16, step, hb, t.h1f);
+    }
+    uint4 f3t[KSD][1], f2t[KS2][1];
+    if constexpr (AHEAD) layer_weights<KSD, 1>(w3t, FW, wave, lane, f3t);
+    else layer_weights<KS2, PER3>(w3f, NT3, PER3 * wave, lane, f3);
+    __syncthreads();
+    // output layer, loss and its gradient 2 (o - t) / count (into sX, whose
+    // inputs are no longer needed; columns up to NDK are zero)
+    double ls = 0.0;
+    {
+        f32x4 acc[PER3];
+        layer_mfma<HID, PER3, HID + 8>(sB, f3, lane, acc);
+#pragma unroll
+        for (int j = 0; j < PER3; ++j) {
+            const int o = 16 * (PER3 * wave + j) + ccol;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const bool ok = o < ND && r0 + crow + q < B;
+                float g = 0.f;
+                if (ok) {
+                    const int64_t i = (r0 + crow + q) * ND + o;
+                    const float v = acc[j][q] + bv3[j], e = v - tv[j][q];
+                    ls += (double)e * e;
+                    g = 2.f * e * inv_count;
+                    t.o[i] = v;
+                    t.d_o[i] = g;
+                }
+                if (o < NDK) sX[crow + q][o] = f2bf(g);
+            }
+        }
+        // columns no output tile covers
+        for (int i = tid; i < 16 * (NDK - 16 * NT3); i += 64 * FW)
+            sX[i & 15][16 * NT3 + (i >> 4)] = 0;
+        tile_to_frags<HID + 8>(sB, HID / 16, step, hb, t.h2f);
+    }
+    if constexpr (AHEAD) layer_weights<KS2, 1>(w2t, FW, wave, lane, f2t);
+    else layer_weights<KSD, 1>(w3t, FW, wave, lane, f3t);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) ls += __shfl_xor(ls, o, 64);
+    if (lane == 0) sl[wave] = ls;
+    __syncthreads();
+    if (tid == 0) {
+        double s = 0.0;
+        for (int i = 0; i < FW; ++i) s += sl[i];
+        part[blockIdx.x] = s;
+    }
+    auto signal = [&](const f32x4 &acc, const float (&hv)[4], uint16_t (*sT)[HID + 8], float *out) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float g = hv[q] > 0.f ? acc[q] : 0.f;
+            sT[crow + q][n] = f2bf(g);
+            if (r0 + crow + q < B) out[(r0 + crow + q) * HID + n] = g;
+        }
+    };
+    signal(back_mfma<NDK, LDX + 8>(sX, f3t, lane), h2v, sC, t.dh2);
+    tile_to_frags<LDX + 8>(sX, CTO, step, hb, t.dof);
+    if constexpr (!AHEAD) layer_weights<KS2, 1>(w2t, FW, wave, lane, f2t);
+    __syncthreads();
+    signal(back_mfma<HID, HID + 8>(sC, f2t, lane), h1v, sA, t.dh1);
+    tile_to_frags<HID + 8>(sC, HID / 16, step, hb, t.dh2f);
+    __syncthreads();
+    tile_to_frags<HID + 8>(sA, HID / 16, step, hb, t.dh1f);
+}
+
+// Weight gradients dW = D^T X over one chunk of the batch, FP32 partial sums
+// part[chunk][P] in the parameters' own order; bias gradients as FP64 column
+// sums pb[chunk][2 HID + n_out].  A workgroup of 4 waves makes a 64 x 64 tile
+// of one of the three matrices (32 x 32 per wave, fragments straight from
+// memory), or 64 columns of the bias sums.  The chunks exist because the
+// output tiles alone are too few: at degree 4 and 2,048 rows 44 tiles times 8
+// chunks of 8 steps fill the 256 compute units, where one pass over the whole
+// batch left 212 of them idle behind a chain of 64 dependent steps.
+// Measured (degree 4, 2,048 rows, the whole step): 729 us before, 26 us now.
+// chunks of the batch in k_train_wgrad, each of at least CHUNK_STEPS 32-row
+// steps: 8 steps are what one wave keeps in flight (128 registers of
+// fragments), and 16 chunks already fill the chip at every degree, so a
+// larger batch gets longer chunks instead of more partial sums
+constexpr int MAX_CHUNKS = 16, CHUNK_STEPS = 8;
+
+struct WGrad {
+    int n_in, n_out, ldx;
+    int64_t off_w1, off_w2, off_w3, P;
+    int tiles3, tiles2, tiles1, tilesb;   // workgroups per matrix and for the biases
+};
+
+__global__ void __launch_bounds__(256)
+k_train_wgrad(int64_t B, int ksteps, int per, WGrad g, TrainBuf t, float *__restrict__ part,
+              double *__restrict__ pb)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int chunk = blockIdx.y;
+    const int k0 = chunk * per, k1 = min(ksteps, k0 + per);
+    int tile = blockIdx.x;
+    if (tile >= g.tiles3 + g.tiles2 + g.tiles1) {
+        // bias columns: [hidden 1, hidden 2, output]
+        __shared__ double sb[4][64];
+        const int col = (tile - g.tiles3 - g.tiles2 - g.tiles1) * 64 + lane, nb = 2 * HID + g.n_out;
+        const float *src = col < HID ? t.dh1 : col < 2 * HID ? t.dh2 : t.d_o;
+        const int ld = col < 2 * HID ? HID : g.n_out;
+        const int c = col < HID ? col : col < 2 * HID ? col - HID : col - 2 * HID;
+        const int64_t rb = (int64_t)k0 * 32, re = min(B, (int64_t)k1 * 32);
+        double s = 0.0;
+        if (col < nb)
+#pragma unroll 8
+            for (int64_t r = rb + wave; r < re; r += 4) s += src[r * ld + c];
+        sb[wave][lane] = s;
+        __syncthreads();
+        if (wave == 0 && col < nb)
+            pb[(int64_t)chunk * nb + col] = (sb[0][lane] + sb[1][lane]) + (sb[2][lane] + sb[3][lane]);
+        return;
+    }
+    // matrix: rows (D) x columns (X), its fragments and their column tiles
+    const uint16_t *__restrict__ D, *__restrict__ X;
+    int rows, cols, ctd, ctx;
+    int64_t off;
+    if (tile < g.tiles3) {
+        D = t.dof, X = t.h2f, rows = g.n_out, cols = HID, off = g.off_w3;
+        ctd = (g.n_out + 15) / 16, ctx = HID / 16;
+    } else if ((tile -= g.tiles3) < g.tiles2) {
+        D = t.dh2f, X = t.h1f, rows = HID, cols = HID, off = g.off_w2;
+        ctd = ctx = HID / 16;
+    } else {
+        tile -= g.tiles2;
+        D = t.dh1f, X = t.xf, rows = HID, cols = g.n_in, off = g.off_w1;
+        ctd = HID / 16, ctx = g.ldx / 16;
+    }
+    const int tn = (cols + 63) / 64;
+    const int m0 = (tile / tn) * 64 + (wave & 1) * 32, n0 = (tile % tn) * 64 + (wave >> 1) * 32;
+    // (a tile past the last one reads the last one; its results are not stored)
+    int64_t da[2], xa[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        da[i] = ((int64_t)min(m0 / 16 + i, ctd - 1) * 64 + lane) * 8;
+        xa[i] = ((int64_t)min(n0 / 16 + i, ctx - 1) * 64 + lane) * 8;
+    }
+    f32x4 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    constexpr int KB = CHUNK_STEPS;   // steps in flight together
+    for (int kb = k0; kb < k1; kb += KB) {
+        uint4 fd[KB][2], fx[KB][2];
+#pragma unroll
+        for (int u = 0; u < KB; ++u) {
+            const int64_t k = min(kb + u, k1 - 1);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                fd[u][i] = *(const uint4 *)(D + k * ctd * 512 + da[i]);
+                fx[u][i] = *(const uint4 *)(X + k * ctx * 512 + xa[i]);
+            }
+        }
+        // keep the loads together: the compiler would otherwise issue each
+        // step's just before its products to save registers
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < KB; ++u) {
+            if (kb + u >= k1) break;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf16x8, fd[u][i]), __builtin_bit_cast(bf16x8, fx[u][j]),
+                        acc[i][j], 0, 0, 0);
+        }
+    }
+    float *__restrict__ out = part + (int64_t)chunk * g.P + off;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int m = m0 + 16 * i + 4 * (lane >> 4) + q, n = n0 + 16 * j + (lane & 15);
+                if (m < rows && n < cols) out[(int64_t)m * cols + n] = acc[i][j][q];
+            }
+}
+
+// Parameters, one per thread: with chunks > 0 the gradient (the chunks' sums
+// in order) to grad and grad_out, with update the Adam step; the BF16 copies
+// of the weight in each layout that a product reads: row-major for the
+// batched forward pass, and fragment order (columns of W and of W^T) for the
+// fused kernels.  The padding of the copies is zeroed once, at creation.
+//
+// Fragment order of W for v_mfma_f32_16x16x32_bf16: for column tile ct (16
+// output columns), k-step s (32 inputs) and lane l the 8 values
+// W[16 ct + l % 16][32 s + 8 (l / 16) .. + 7] sit at ((ct ks + s) 64 + l) 8, so
+// that one wave's fragment load is 1 KB in a row and its whole slice of a
+// layer is contiguous.  Of W^T for v_mfma_f32_16x16x16_bf16: the 8 values are
+// W[32 s + 16 h + 4 (l / 16) .. + 3][16 ct + l % 16], h = 0, 1.
+struct Params {
+    int n_in, n_out, ldx;
+    int64_t off_b1, off_w2, off_b2, off_w3, off_b3, P;
+    float *w, *m, *v, *grad;
+    uint16_t *w1b, *w2b, *w3b, *wfr, *wbk;
+};
+
+__global__ void __launch_bounds__(256)
+k_params(Params p, int chunks, const float *__restrict__ part, const double *__restrict__ pb,
+         float *__restrict__ grad_out, int update, float lr, float b1, float b2, float eps, float c1,
+         float c2)
+{
+    const int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x;
+    if (i >= p.P) return;
+    // layer, row and column of a weight; column of a bias among [b1, b2, b3]
+    int layer, r = 0, c = 0, bcol = -1;
+    if (i < p.off_b1) {
+        layer = 1;
+        r = (int)(i / p.n_in);
+        c = (int)(i % p.n_in);
+    } else if (i < p.off_w2) {
+        layer = 1;
+        bcol = (int)(i - p.off_b1);
+    } else if (i < p.off_w3) {
+        layer = 2;
+        const int64_t e = i - p.off_w2;
+        if (i >= p.off_b2) bcol = HID + (int)(i - p.off_b2);
+        r = (int)(e / HID);
+        c = (int)(e % HID);
+    } else {
+        layer = 3;
+        const int64_t e = i - p.off_w3;
+        if (i >= p.off_b3) bcol = 2 * HID + (int)(i - p.off_b3);
+        r = (int)(e / HID);
+        c = (int)(e % HID);
+    }
+    float w = p.w[i];
+    if (chunks > 0) {
+        float g;
+        if (bcol >= 0) {
+            double s = 0.0;
+            for (int k = 0; k < chunks; ++k) s += pb[(int64_t)k * (2 * HID + p.n_out) + bcol];
+            g = (float)s;
+        } else {
+            double s = 0.0;
+#pragma unroll 8
+            for (int k = 0; k < chunks; ++k) s += (double)part[(int64_t)k * p.P + i];
+            g = (float)s;
+        }
+        p.grad[i] = g;
+        if (grad_out) grad_out[i] = g;
+        if (!update) return;
+        const float mi = b1 * p.m[i] + (1.f - b1) * g;
+        const float vi = b2 * p.v[i] + (1.f - b2) * g * g;
+        p.m[i] = mi;
+        p.v[i] = vi;
+        w -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+        p.w[i] = w;
+    }
+    if (bcol >= 0) return;
+    const uint16_t h = f2bf(w);
+    auto frag = [](int row, int col, int ks) {
+        return (((int64_t)(row >> 4) * ks + (col >> 5)) * 64 + ((col & 31) >> 3) * 16 + (row & 15)) * 8 + (col & 7);
+    };
+    auto back = [](int row, int col, int ks) {
+        return (((int64_t)(col >> 4) * ks + (row >> 5)) * 64 + ((row & 15) >> 2) * 16 + (col & 15)) * 8 +
+               ((row >> 4) & 1) * 4 + (row & 3);
+    };
+    const int ks1 = p.ldx / 32, ks = HID / 32, ksd = (p.n_out + 31) / 32;
+    const int64_t f2 = (int64_t)512 * FW * ks1, f3 = f2 + (int64_t)512 * FW * ks;
+    if (layer == 1) {
+        p.w1b[(int64_t)r * p.ldx + c] = h;
+        p.wfr[frag(r, c, ks1)] = h;
+    } else if (layer == 2) {
+        p.w2b[(int64_t)r * HID + c] = h;
+        p.wfr[f2 + frag(r, c, ks)] = h;
+        p.wbk[(int64_t)512 * FW * ksd + back(r, c, ks)] = h;
+    } else {
+        p.w3b[(int64_t)r * HID + c] = h;
+        p.wfr[f3 + frag(r, c, ks)] = h;
+        p.wbk[back(r, c, ksd)] = h;
+    }
+}
+
 // targets[c][i] = (e[c][i] - z[c][i]) / w_c with e = xs - xj, w_c = RMS(z_c)
 // (0 when w_c = 0), limited to [-clip, clip] when clip > 0
 __global__ void __launch_bounds__(128)
@@ -772,27 +1024,39 @@ struct MlpState {
     int64_t off_w1 = 0, off_b1 = 0, off_w2 = 0, off_b2 = 0, off_w3 = 0, off_b3 = 0;
     float *w = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr;
     uint16_t *w1b = nullptr, *w2b = nullptr, *w3b = nullptr;
-    uint16_t *wfr = nullptr;   // the three layers in the fused kernel's fragment order
+    uint16_t *wfr = nullptr;   // the three layers in the fused kernels' fragment order
+    uint16_t *wbk = nullptr;   // W3^T, W2^T in the backward products' fragment order
     int64_t t = 0;
-    int64_t cap = 0;
+    int64_t cap = 0;         // rows of the forward buffers xb, h1b, h2b, o, scale
+    uint16_t *xb = nullptr, *h1b = nullptr, *h2b = nullptr;
+    float *o = nullptr, *scale = nullptr, *loss = nullptr;
+    int64_t tcap = 0;        // rows of the training buffers (a multiple of 32)
     int64_t trace_B = 0;     // batch of the last training step whose buffers are intact
-    uint16_t *xb = nullptr, *h1b = nullptr, *h2b = nullptr, *dob = nullptr, *dh1b = nullptr,
-             *dh2b = nullptr;
-    float *h1 = nullptr, *h2 = nullptr, *o = nullptr, *d_o = nullptr, *dh1 = nullptr,
-          *dh2 = nullptr, *scale = nullptr, *loss = nullptr;
-    double *part = nullptr, *zt = nullptr;
+    TrainBuf tb{};
+    float *gpart = nullptr;  // [MAX_CHUNKS][P] weight-gradient partial sums
+    double *bpart = nullptr; // [MAX_CHUNKS][2 HID + n_out] bias-gradient partial sums
+    double *lpart = nullptr; // [tcap / 16] loss partial sums
+    double *zt = nullptr;
     float *loss_host = nullptr;
     int n_cu = 0;            // compute units of the device
 };
 
 static void free_batch(MlpState *s)
 {
-    void **b[] = {(void **)&s->xb, (void **)&s->h1b, (void **)&s->h2b, (void **)&s->dob,
-                  (void **)&s->dh1b, (void **)&s->dh2b, (void **)&s->h1, (void **)&s->h2,
-                  (void **)&s->o, (void **)&s->d_o, (void **)&s->dh1, (void **)&s->dh2,
+    void **b[] = {(void **)&s->xb, (void **)&s->h1b, (void **)&s->h2b, (void **)&s->o,
                   (void **)&s->scale};
     for (void **p : b) dfree(p);
     s->cap = 0;
+}
+
+static void free_train(MlpState *s)
+{
+    TrainBuf &t = s->tb;
+    void **b[] = {(void **)&t.h1, (void **)&t.h2, (void **)&t.o, (void **)&t.d_o, (void **)&t.dh2,
+                  (void **)&t.dh1, (void **)&t.xf, (void **)&t.h1f, (void **)&t.h2f, (void **)&t.dof,
+                  (void **)&t.dh2f, (void **)&t.dh1f, (void **)&s->lpart};
+    for (void **p : b) dfree(p);
+    s->tcap = 0;
 }
 
 static hx_status ensure_batch(hx_ctx *c, int64_t B)
@@ -807,22 +1071,47 @@ static hx_status ensure_batch(hx_ctx *c, int64_t B)
     A(s->xb, 2 * (size_t)B * s->ldx);
     A(s->h1b, 2 * (size_t)B * HID);
     A(s->h2b, 2 * (size_t)B * HID);
-    A(s->dob, 2 * (size_t)B * s->n_out);
-    A(s->dh1b, 2 * (size_t)B * HID);
-    A(s->dh2b, 2 * (size_t)B * HID);
-    A(s->h1, 4 * (size_t)B * HID);
-    A(s->h2, 4 * (size_t)B * HID);
     A(s->o, 4 * (size_t)B * s->n_out);
-    A(s->d_o, 4 * (size_t)B * s->n_out);
-    A(s->dh1, 4 * (size_t)B * HID);
-    A(s->dh2, 4 * (size_t)B * HID);
     A(s->scale, 4 * (size_t)B);
-#undef A
     if (st != HX_OK) {
         free_batch(s);
         return st;
     }
     s->cap = B;
+    return HX_OK;
+}
+
+static hx_status ensure_train(hx_ctx *c, int64_t B)
+{
+    MlpState *s = c->mlp;
+    s->trace_B = 0;
+    const int64_t R = (B + 31) / 32 * 32;
+    hx_status st = HX_OK;
+    if (!s->gpart) A(s->gpart, 4 * (size_t)MAX_CHUNKS * s->P);
+    if (!s->bpart) A(s->bpart, 8 * (size_t)MAX_CHUNKS * (2 * HID + s->n_out));
+    if (st != HX_OK) return st;
+    if (R <= s->tcap) return HX_OK;
+    free_train(s);
+    TrainBuf &t = s->tb;
+    A(t.h1, 4 * (size_t)R * HID);
+    A(t.h2, 4 * (size_t)R * HID);
+    A(t.o, 4 * (size_t)R * s->n_out);
+    A(t.d_o, 4 * (size_t)R * s->n_out);
+    A(t.dh2, 4 * (size_t)R * HID);
+    A(t.dh1, 4 * (size_t)R * HID);
+    A(t.xf, 2 * (size_t)R * s->ldx);
+    A(t.h1f, 2 * (size_t)R * HID);
+    A(t.h2f, 2 * (size_t)R * HID);
+    A(t.dof, 2 * (size_t)R * ((s->n_out + 15) / 16 * 16));
+    A(t.dh2f, 2 * (size_t)R * HID);
+    A(t.dh1f, 2 * (size_t)R * HID);
+    A(s->lpart, 8 * (size_t)(R / 16));
+#undef A
+    if (st != HX_OK) {
+        free_train(s);
+        return st;
+    }
+    s->tcap = R;
     return HX_OK;
 }
 
@@ -859,9 +1148,17 @@ hx_status mlp_create(hx_ctx *c)
     A(s->w3b, 2 * (size_t)s->n_out * HID);
     A(s->wfr, 2 * (size_t)512 * ((HID / 16) * (s->ldx / 32) + (HID / 16) * (HID / 32) +
                                  ((s->n_out + 15) / 16) * (HID / 32)));
-    A(s->part, 8 * 1024);
+    A(s->wbk, 2 * (size_t)512 * (HID / 16) * ((s->n_out + 31) / 32 + HID / 32));
     A(s->loss, 16);
 #undef A
+    // the padding of the BF16 copies stays zero: k_params writes only weights
+    const size_t padded[] = {2 * (size_t)HID * s->ldx,
+                             2 * (size_t)512 * ((HID / 16) * (s->ldx / 32) + (HID / 16) * (HID / 32) +
+                                                ((s->n_out + 15) / 16) * (HID / 32)),
+                             2 * (size_t)512 * (HID / 16) * ((s->n_out + 31) / 32 + HID / 32)};
+    uint16_t *const pad_ptr[] = {s->w1b, s->wfr, s->wbk};
+    for (int i = 0; i < 3 && st == HX_OK; ++i)
+        if (hipMemsetAsync(pad_ptr[i], 0, padded[i], c->stream) != hipSuccess) st = HX_ERR_DEVICE;
     if (st == HX_OK && hipHostMalloc((void **)&s->loss_host, 16) != hipSuccess) st = HX_ERR_DEVICE;
     if (st == HX_OK &&
         hipDeviceGetAttribute(&s->n_cu, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess)
@@ -878,32 +1175,33 @@ void mlp_destroy(hx_ctx *c)
     MlpState *s = c->mlp;
     if (!s) return;
     free_batch(s);
+    free_train(s);
     void **b[] = {(void **)&s->w, (void **)&s->m, (void **)&s->v, (void **)&s->grad,
-                  (void **)&s->w1b, (void **)&s->w2b, (void **)&s->w3b, (void **)&s->wfr, (void **)&s->part,
-                  (void **)&s->loss, (void **)&s->zt};
+                  (void **)&s->w1b, (void **)&s->w2b, (void **)&s->w3b, (void **)&s->wfr,
+                  (void **)&s->wbk, (void **)&s->gpart, (void **)&s->bpart, (void **)&s->loss,
+                  (void **)&s->zt};
     for (void **p : b) dfree(p);
     if (s->loss_host) (void)hipHostFree(s->loss_host);
     delete s;
     c->mlp = nullptr;
 }
 
-static hipError_t refresh_bf16(hx_ctx *c)
+// k_params: gradient from the chunks' partial sums (chunks > 0), Adam with
+// lr != 0, BF16 copies
+static hipError_t params_step(hx_ctx *c, int chunks, float *grad_out, float lr)
 {
     MlpState *s = c->mlp;
-    hipLaunchKernelGGL(k_weights_to_bf16, dim3(nb256((int64_t)HID * s->ldx)), dim3(256), 0, c->stream,
-                       s->P, s->w + s->off_w1, HID, s->n_in, s->ldx, s->w1b);
-    hipLaunchKernelGGL(k_weights_to_bf16, dim3(nb256((int64_t)HID * HID)), dim3(256), 0, c->stream,
-                       s->P, s->w + s->off_w2, HID, HID, HID, s->w2b);
-    hipLaunchKernelGGL(k_weights_to_bf16, dim3(nb256((int64_t)s->n_out * HID)), dim3(256), 0,
-                       c->stream, s->P, s->w + s->off_w3, s->n_out, HID, HID, s->w3b);
-    const int ks1 = s->ldx / 32, ks = HID / 32;
-    uint16_t *f2 = s->wfr + (int64_t)512 * (HID / 16) * ks1, *f3 = f2 + (int64_t)512 * (HID / 16) * ks;
-    hipLaunchKernelGGL(k_weights_frag, dim3(nb256((int64_t)512 * (HID / 16) * ks1)), dim3(256), 0,
-                       c->stream, s->w + s->off_w1, HID, s->n_in, ks1, s->wfr);
-    hipLaunchKernelGGL(k_weights_frag, dim3(nb256((int64_t)512 * (HID / 16) * ks)), dim3(256), 0,
-                       c->stream, s->w + s->off_w2, HID, HID, ks, f2);
-    hipLaunchKernelGGL(k_weights_frag, dim3(nb256((int64_t)512 * ((s->n_out + 15) / 16) * ks)),
-                       dim3(256), 0, c->stream, s->w + s->off_w3, s->n_out, HID, ks, f3);
+    const Params p{s->n_in, s->n_out, s->ldx, s->off_b1, s->off_w2, s->off_b2, s->off_w3, s->off_b3, s->P,
+                   s->w, s->m, s->v, s->grad, s->w1b, s->w2b, s->w3b, s->wfr, s->wbk};
+    const float b1 = 0.9f, b2 = 0.999f;
+    float c1 = 1.f, c2 = 1.f;
+    if (lr != 0.0f) {
+        s->t += 1;
+        c1 = 1.f - powf(b1, (float)s->t);
+        c2 = 1.f - powf(b2, (float)s->t);
+    }
+    hipLaunchKernelGGL(k_params, dim3(nb256(s->P)), dim3(256), 0, c->stream, p, chunks, s->gpart,
+                       s->bpart, grad_out, lr != 0.0f, lr, b1, b2, 1e-8f, c1, c2);
     return hipGetLastError();
 }
 
@@ -919,7 +1217,7 @@ hx_status mlp_set(hx_ctx *c, const float *w, int64_t n)
     HX_HIP(c, hipMemsetAsync(s->m, 0, 4 * (size_t)n, c->stream));
     HX_HIP(c, hipMemsetAsync(s->v, 0, 4 * (size_t)n, c->stream));
     s->t = 0;
-    HX_HIP(c, refresh_bf16(c));
+    HX_HIP(c, params_step(c, 0, nullptr, 0.0f));
     HX_HIP(c, hipStreamSynchronize(c->stream));
     return HX_OK;
 }
@@ -944,20 +1242,19 @@ hx_status mlp_features(hx_ctx *c, const double *r, float *feats, float *scale)
     return HX_OK;
 }
 
-// forward on the packed batch s->xb (B rows); h1/h2 bf16 (and fp32 for the
-// backward pass when training), o fp32
-static hipError_t forward_packed(hx_ctx *c, int64_t B, bool training)
+// forward on the packed batch s->xb (B rows); hidden layers BF16, o FP32
+static hipError_t forward_packed(hx_ctx *c, int64_t B)
 {
     MlpState *s = c->mlp;
     hipError_t e;
-    e = gemm(c->stream, (int)B, HID, s->ldx, s->xb, s->ldx, 1, s->w1b, s->ldx, 1, s->w + s->off_b1, 1,
-             training ? s->h1 : nullptr, HID, s->h1b, HID);
+    e = gemm(c->stream, (int)B, HID, s->ldx, s->xb, s->ldx, s->w1b, s->ldx, s->w + s->off_b1, 1, nullptr,
+             HID, s->h1b, HID);
     if (e != hipSuccess) return e;
-    e = gemm(c->stream, (int)B, HID, HID, s->h1b, HID, 1, s->w2b, HID, 1, s->w + s->off_b2, 1,
-             training ? s->h2 : nullptr, HID, s->h2b, HID);
+    e = gemm(c->stream, (int)B, HID, HID, s->h1b, HID, s->w2b, HID, s->w + s->off_b2, 1, nullptr, HID,
+             s->h2b, HID);
     if (e != hipSuccess) return e;
-    return gemm(c->stream, (int)B, s->n_out, HID, s->h2b, HID, 1, s->w3b, HID, 1, s->w + s->off_b3, 0,
-                s->o, s->n_out, nullptr, 0);
+    return gemm(c->stream, (int)B, s->n_out, HID, s->h2b, HID, s->w3b, HID, s->w + s->off_b3, 0, s->o,
+                s->n_out, nullptr, 0);
 }
 
 hx_status mlp_forward(hx_ctx *c, const float *feats, int64_t B, float *out)
@@ -969,7 +1266,7 @@ hx_status mlp_forward(hx_ctx *c, const float *feats, int64_t B, float *out)
     hipLaunchKernelGGL(k_pack, dim3(nb256(B * s->ldx)), dim3(256), 0, c->stream, B, s->n_in, s->ldx,
                        feats, s->xb);
     HX_HIP(c, hipGetLastError());
-    HX_HIP(c, forward_packed(c, B, false));
+    HX_HIP(c, forward_packed(c, B));
     HX_HIP(c, hipMemcpyAsync(out, s->o, 4 * (size_t)B * s->n_out, hipMemcpyDeviceToDevice, c->stream));
     return HX_OK;
 }
@@ -1035,13 +1332,24 @@ hx_status mlp_forward_noalloc(hx_ctx *c, const float *feats, int64_t B, float *o
     hipLaunchKernelGGL(k_pack, dim3(nb256(B * s->ldx)), dim3(256), 0, c->stream, B, s->n_in, s->ldx,
                        feats, xb);
     HX_HIP(c, hipGetLastError());
-    HX_HIP(c, gemm(c->stream, (int)B, HID, s->ldx, xb, s->ldx, 1, s->w1b, s->ldx, 1, s->w + s->off_b1,
-                   1, nullptr, HID, h1b, HID));
-    HX_HIP(c, gemm(c->stream, (int)B, HID, HID, h1b, HID, 1, s->w2b, HID, 1, s->w + s->off_b2, 1,
-                   nullptr, HID, h2b, HID));
-    HX_HIP(c, gemm(c->stream, (int)B, s->n_out, HID, h2b, HID, 1, s->w3b, HID, 1, s->w + s->off_b3, 0,
-                   out, s->n_out, nullptr, 0));
+    HX_HIP(c, gemm(c->stream, (int)B, HID, s->ldx, xb, s->ldx, s->w1b, s->ldx, s->w + s->off_b1, 1,
+                   nullptr, HID, h1b, HID));
+    HX_HIP(c, gemm(c->stream, (int)B, HID, HID, h1b, HID, s->w2b, HID, s->w + s->off_b2, 1, nullptr,
+                   HID, h2b, HID));
+    HX_HIP(c, gemm(c->stream, (int)B, s->n_out, HID, h2b, HID, s->w3b, HID, s->w + s->off_b3, 0, out,
+                   s->n_out, nullptr, 0));
     return HX_OK;
+}
+
+template <int N>
+static hipError_t train_fb_n(hx_ctx *c, int64_t B, const float *feats, const float *targets)
+{
+    MlpState *s = c->mlp;
+    // both halves of every 32-row step, so that all of its rows are written
+    hipLaunchKernelGGL(k_train_fb<N>, dim3((unsigned)((B + 31) / 32 * 2)), dim3(64 * FW), 0, c->stream, B,
+                       feats, targets, s->wfr, s->wbk, s->w + s->off_b1, s->w + s->off_b2,
+                       s->w + s->off_b3, 1.0f / (float)(B * s->n_out), s->tb, s->lpart);
+    return hipGetLastError();
 }
 
 hx_status mlp_train(hx_ctx *c, const float *feats, const float *targets, int64_t B, float lr,
@@ -1049,49 +1357,37 @@ hx_status mlp_train(hx_ctx *c, const float *feats, const float *targets, int64_t
 {
     if (!c->mlp) return fail(c, HX_ERR_STATE, "no network loaded");
     MlpState *s = c->mlp;
-    hx_status st = ensure_batch(c, B);
+    hx_status st = ensure_train(c, B);
     if (st != HX_OK) return st;
     const hipStream_t q = c->stream;
-    hipLaunchKernelGGL(k_pack, dim3(nb256(B * s->ldx)), dim3(256), 0, q, B, s->n_in, s->ldx, feats,
-                       s->xb);
-    HX_HIP(c, forward_packed(c, B, true));
-    const int64_t tot = B * s->n_out;
-    const int nbk = (int)std::min<int64_t>(1024, (tot + 255) / 256);
-    hipLaunchKernelGGL(k_loss_grad, dim3(nbk), dim3(256), 0, q, tot, 1.0f / (float)tot, s->o, targets,
-                       s->d_o, s->dob, s->part);
-    hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(256), 0, q, nbk, s->part, 1.0 / (double)tot, s->loss);
-    HX_HIP(c, hipGetLastError());
-    float *g = s->grad;
-    // layer 3: dW3[o][h] = sum_b dO[b][o] H2[b][h]; db3 = colsum(dO); dH2 = dO W3
-    HX_HIP(c, gemm(q, s->n_out, HID, (int)B, s->dob, 1, s->n_out, s->h2b, 1, HID, nullptr, 0,
-                   g + s->off_w3, HID, nullptr, 0));
-    hipLaunchKernelGGL(k_colsum, dim3(s->n_out), dim3(256), 0, q, B, s->n_out, s->d_o, g + s->off_b3);
-    HX_HIP(c, gemm(q, (int)B, HID, s->n_out, s->dob, s->n_out, 1, s->w3b, 1, HID, nullptr, 0, s->dh2,
-                   HID, nullptr, 0));
-    hipLaunchKernelGGL(k_relu_back, dim3(nb256(B * HID)), dim3(256), 0, q, B * HID, s->h2, s->dh2, s->dh2b);
-    // layer 2
-    HX_HIP(c, gemm(q, HID, HID, (int)B, s->dh2b, 1, HID, s->h1b, 1, HID, nullptr, 0, g + s->off_w2,
-                   HID, nullptr, 0));
-    hipLaunchKernelGGL(k_colsum, dim3(HID), dim3(256), 0, q, B, HID, s->dh2, g + s->off_b2);
-    HX_HIP(c, gemm(q, (int)B, HID, HID, s->dh2b, HID, 1, s->w2b, 1, HID, nullptr, 0, s->dh1, HID,
-                   nullptr, 0));
-    hipLaunchKernelGGL(k_relu_back, dim3(nb256(B * HID)), dim3(256), 0, q, B * HID, s->h1, s->dh1, s->dh1b);
-    // layer 1: dW1[h][i] = sum_b dH1[b][h] X[b][i] (only the n_in real columns)
-    HX_HIP(c, gemm(q, HID, s->n_in, (int)B, s->dh1b, 1, HID, s->xb, 1, s->ldx, nullptr, 0,
-                   g + s->off_w1, s->n_in, nullptr, 0));
-    hipLaunchKernelGGL(k_colsum, dim3(HID), dim3(256), 0, q, B, HID, s->dh1, g + s->off_b1);
+    hipError_t e = hipSuccess;
+    switch (c->n) {
+    case 2: e = train_fb_n<2>(c, B, feats, targets); break;
+    case 3: e = train_fb_n<3>(c, B, feats, targets); break;
+    case 4: e = train_fb_n<4>(c, B, feats, targets); break;
+    case 5: e = train_fb_n<5>(c, B, feats, targets); break;
+    case 6: e = train_fb_n<6>(c, B, feats, targets); break;
+    case 7: e = train_fb_n<7>(c, B, feats, targets); break;
+    default: e = train_fb_n<8>(c, B, feats, targets); break;
+    }
+    HX_HIP(c, e);
+    if (loss_out) {
+        hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(256), 0, q, (int)((B + 31) / 32 * 2), s->lpart,
+                           1.0 / (double)(B * s->n_out), s->loss);
+        HX_HIP(c, hipGetLastError());
+    }
+    const int ksteps = (int)((B + 31) / 32);
+    const int per = std::max(CHUNK_STEPS, (ksteps + MAX_CHUNKS - 1) / MAX_CHUNKS);
+    const int chunks = (ksteps + per - 1) / per;
+    auto t64 = [](int v) { return (v + 63) / 64; };
+    const WGrad g{s->n_in, s->n_out, s->ldx, s->off_w1, s->off_w2, s->off_w3, s->P,
+                  t64(s->n_out) * t64(HID), t64(HID) * t64(HID), t64(HID) * t64(s->n_in),
+                  t64(2 * HID + s->n_out)};
+    hipLaunchKernelGGL(k_train_wgrad, dim3(g.tiles3 + g.tiles2 + g.tiles1 + g.tilesb, chunks), dim3(256),
+                       0, q, B, ksteps, per, g, s->tb, s->gpart, s->bpart);
     HX_HIP(c, hipGetLastError());
     s->trace_B = B;
-    if (grad_out)
-        HX_HIP(c, hipMemcpyAsync(grad_out, g, 4 * (size_t)s->P, hipMemcpyDeviceToDevice, q));
-    if (lr != 0.0f) {
-        s->t += 1;
-        const float b1 = 0.9f, b2 = 0.999f;
-        const float c1 = 1.f - powf(b1, (float)s->t), c2 = 1.f - powf(b2, (float)s->t);
-        hipLaunchKernelGGL(k_adam, dim3(nb256(s->P)), dim3(256), 0, q, s->P, s->w, g, s->m, s->v, lr,
-                           b1, b2, 1e-8f, c1, c2);
-        HX_HIP(c, refresh_bf16(c));
-    }
+    HX_HIP(c, params_step(c, chunks, grad_out, lr));
     if (loss_out) {
         HX_HIP(c, hipMemcpyAsync(s->loss_host, s->loss, 4, hipMemcpyDeviceToHost, q));
         HX_HIP(c, hipStreamSynchronize(q));
@@ -1109,12 +1405,12 @@ hx_status mlp_trace(hx_ctx *c, int what, float *host_buf, int64_t count)
     int width = HID;
     switch (what) {
     case HX_TRACE_INPUT: width = s->n_in; break;
-    case HX_TRACE_H1: src = s->h1; break;
-    case HX_TRACE_H2: src = s->h2; break;
-    case HX_TRACE_OUT: src = s->o; width = s->n_out; break;
-    case HX_TRACE_DOUT: src = s->d_o; width = s->n_out; break;
-    case HX_TRACE_DH2: src = s->dh2; break;
-    case HX_TRACE_DH1: src = s->dh1; break;
+    case HX_TRACE_H1: src = s->tb.h1; break;
+    case HX_TRACE_H2: src = s->tb.h2; break;
+    case HX_TRACE_OUT: src = s->tb.o; width = s->n_out; break;
+    case HX_TRACE_DOUT: src = s->tb.d_o; width = s->n_out; break;
+    case HX_TRACE_DH2: src = s->tb.dh2; break;
+    case HX_TRACE_DH1: src = s->tb.dh1; break;
     default: return fail(c, HX_ERR_ARG, "unknown trace %d", what);
     }
     if (count != B * width)
@@ -1125,13 +1421,15 @@ hx_status mlp_trace(hx_ctx *c, int what, float *host_buf, int64_t count)
         HX_HIP(c, hipStreamSynchronize(c->stream));
         return HX_OK;
     }
-    // the packed BF16 inputs: rows of ldx, the first n_in columns widened to FP32
-    std::vector<uint16_t> tmp((size_t)B * s->ldx);
-    HX_HIP(c, hipMemcpyAsync(tmp.data(), s->xb, 2 * tmp.size(), hipMemcpyDeviceToHost, c->stream));
+    // the BF16 inputs, in fragment order (32 rows a step), widened to FP32
+    std::vector<uint16_t> tmp((size_t)((B + 31) / 32 * 32) * s->ldx);
+    HX_HIP(c, hipMemcpyAsync(tmp.data(), s->tb.xf, 2 * tmp.size(), hipMemcpyDeviceToHost, c->stream));
     HX_HIP(c, hipStreamSynchronize(c->stream));
+    const int64_t ct = s->ldx / 16;
     for (int64_t b = 0; b < B; ++b)
         for (int j = 0; j < s->n_in; ++j) {
-            const uint32_t u = (uint32_t)tmp[(size_t)b * s->ldx + j] << 16;
+            const int64_t lane = (b % 32) / 8 * 16 + j % 16;
+            const uint32_t u = (uint32_t)tmp[(size_t)(((b / 32 * ct + j / 16) * 64 + lane) * 8 + b % 8)] << 16;
             std::memcpy(&host_buf[b * s->n_in + j], &u, 4);
         }
     return HX_OK;
@@ -1236,7 +1534,7 @@ hx_status mlp_precondition_batched(hx_ctx *c, const double *r, double *z)
                        c->n_cells, r, c->nbr, c->coef_feat, (float *)nullptr, (int64_t)0, s->xb,
                        (int64_t)s->ldx, s->scale);
     HX_HIP(c, hipGetLastError());
-    HX_HIP(c, forward_packed(c, c->n_cells, false));
+    HX_HIP(c, forward_packed(c, c->n_cells));
     HX_HIP(c, launch_bj64(c, r, z));
     hipLaunchKernelGGL(k_add_correction, dim3((unsigned)c->n_cells), dim3(128), 0, c->stream, c->nd,
                        s->o, z);
