@@ -131,6 +131,16 @@ static hx_status update_visit_masks(hx_ctx *c)
     return HX_OK;
 }
 
+// the general data of affine cells and faces, if the last coefficient update
+// left them out
+static hx_status expand_general(hx_ctx *c)
+{
+    if (!c->has_coef || !c->lean) return HX_OK;
+    HX_HIP(c, launch_expand_general(c));
+    c->lean = false;
+    return HX_OK;
+}
+
 // Block-Jacobi penalty of each non-conforming cell end: the fine cell's
 // quarter penalty, or the area-weighted mean over the four quarters of a
 // coarse face (the end term of the separable block stands for the whole face).
@@ -417,6 +427,7 @@ hx_status hx_setup_mesh_hanging(hx_ctx *c, int degree, int64_t n_cells, int geo_
     HX_HIP(c, launch_bj_eigen(c));
     HX_HIP(c, launch_geofac(c));
     HX_HIP(c, launch_affine_detect(c));
+    HX_HIP(c, launch_face_const(c));
     c->ctype_h = new std::vector<uint8_t>(nc);
     HX_HIP(c, hipMemcpyAsync(c->ctype_h->data(), c->ctype, nc, hipMemcpyDeviceToHost, c->stream));
     HX_HIP(c, hipStreamSynchronize(c->stream));
@@ -442,6 +453,10 @@ hx_status hx_set_cell_compression(hx_ctx *c, int on)
 {
     if (!c) return HX_ERR_ARG;
     if (!c->has_mesh) return fail(c, HX_ERR_STATE, "set_cell_compression before setup_mesh");
+    if (!on) {
+        const hx_status s = expand_general(c);
+        if (s != HX_OK) return s;
+    }
     c->compress = on ? 1 : 0;
     return update_visit_masks(c);
 }
@@ -502,6 +517,7 @@ hx_status hx_set_coefficients(hx_ctx *c, const double *alpha, const double *beta
     if (penalty_factor != c->P) {
         c->P = penalty_factor;
         HX_HIP(c, launch_face_sigma(c));
+        HX_HIP(c, launch_face_const(c));
         hx_status sh = update_hang_sigma(c);
         if (sh != HX_OK) return sh;
         HX_HIP(c, launch_bj_eigen(c));
@@ -841,6 +857,10 @@ hx_status hx_debug_export(hx_ctx *c, int what, void *host_buf, int64_t bytes)
         !c->has_coef)
         return fail(c, HX_ERR_STATE, "no coefficients");
     if (bytes < (int64_t)need) return fail(c, HX_ERR_ARG, "buffer too small (%zu needed)", need);
+    if (what == HX_EXPORT_CELL_DATA || what == HX_EXPORT_FACE_DATA) {
+        const hx_status s = expand_general(c);
+        if (s != HX_OK) return s;
+    }
     HX_HIP(c, hipMemcpyAsync(host_buf, src, need, hipMemcpyDeviceToHost, c->stream));
     HX_HIP(c, hipStreamSynchronize(c->stream));
     return HX_OK;

@@ -84,6 +84,7 @@ struct hx_ctx {
     // reads these instead of cell64/face64 for affine cells and for faces
     // between two affine cells (bits of the traversal record's last word)
     int compress = 1;             // 1: use the compressed data where it applies
+    bool lean = false;            // the general data of affine cells and faces are not written
     int64_t n_affine = 0;         // affine cells
     int64_t n_iface = 0;          // interior faces (each once)
     int64_t n_cface = 0;          // interior faces between two affine cells
@@ -208,7 +209,10 @@ hipError_t launch_geofac(hx_ctx *c);
 // affine cells (geometry nodes an affine image of the reference nodes) and
 // their per-cell constants J^-1 J^-T, detJ
 hipError_t launch_affine_detect(hx_ctx *c);
-hipError_t launch_cell_diag(hx_ctx *c);
+// constants of the faces between two affine cells (after sigma changes)
+hipError_t launch_face_const(hx_ctx *c);
+// the general data of affine cells and faces from the compressed data
+hipError_t launch_expand_general(hx_ctx *c);
 hipError_t launch_diag64(hx_ctx *c, int which, const double *r, double *z);
 hipError_t launch_diag32(hx_ctx *c, int which, const float *r, float *z);
 // z = M^{-1} r, M the block-diagonal alpha-weighted mass matrix (fast

@@ -2,15 +2,22 @@
 // surface elements and penalties, merged per-quadrature-point operator data,
 // the separable block-Jacobi eigen-tables and dof coordinates.
 //
-// Everything here runs once per mesh (setup_mesh) or once per coefficient
-// update (set_coefficients, redone each fixed-point iteration of the paper's
-// pressure solve, section 3.1), so it favours clarity over speed.
+// The geometry kernels run once per mesh (setup_mesh) and favour clarity over
+// speed; the coefficient kernels (k_set_cell, k_set_face) run at every
+// fixed-point iteration of the paper's pressure solve (section 3.1).
 #include "common.hpp"
 
 #include <cmath>
 
 namespace hx {
 namespace {
+
+// compile-time copies of the 1-D tables (generated at build time from the
+// library's rules)
+template <int N> struct KB;
+template <int N> struct KBD;
+template <int N> struct KDL;
+#include "optables.inc"
 
 // Lagrange basis through the equispaced nodes a/g, a = 0..g (the geometry
 // nodes of the mesh format): values and derivatives at t.
@@ -403,152 +410,545 @@ __global__ void k_affine_detect(const double *__restrict__ nodes, int ng, int nd
 }
 
 // -------------------------------------------------------------------------
-// merged cell data from the coefficients (block per cell, thread per point):
+// Coefficient update, cell part: from nodal alpha, beta of a cell
 //   m = alpha_q w detJ,  G = beta_q w detJ J^-1 J^-T  (alpha_q, beta_q: the
-// nodal fields at the Gauss point), plus the cell means of the separable
-// block (volume-weighted alpha, beta) and the network's coefficient feature
+// nodal fields at the Gauss point), on affine cells alpha w detJ and beta w
+// detJ in their place, the cell means of the separable block (volume-weighted
+// alpha, beta), the network's coefficient feature, and the inverse volume
+// diagonals
+//   d_i = sum_q [ m_q phi_i(q)^2 + grad phi_i(q)^T G_q grad phi_i(q) ],
+// phi_i(q) = B(qx,a) B(qy,b) B(qz,l), reference gradient from BD: dg[0] of
+// mass plus stiffness (the paper's Helmholtz preconditioner, section 3.1),
+// dg[1] of the mass alone (its internal-energy variant).
+//
+// One wave serves CPW cells with LPC lanes each (N = 5: 2 x 32), lane (a, b)
+// owning a pencil as in the operator kernel.  alpha and beta go to the Gauss
+// points by three sweeps; the z-pencil lanes form the merged values plane by
+// plane, store them and contract them along z on the fly with the products
+// of the 1-D tables P0 = B B, P1 = B BD, P2 = BD BD (every term of the
+// diagonal is a tensor contraction of one quadrature field with such
+// products, e.g. the Gxy term is 2 sum_q Gxy P1(qx,a) P1(qy,b) P0(qz,l); terms
+// that share their remaining tables are merged); y and x follow through LDS.
+// The bound is memory: at degree 4 a general cell reads 72 and writes 108
+// bytes per dof, an affine one, whose six G components nothing reads while
+// the compressed data are in use, 24 and 60 (FULL writes them all the same).
+// The former kernels (N^6 interpolation with one point per lane, a second
+// kernel that read the merged data back for the diagonals) took 1.17 ms at
+// 64x32x32 cells, degree 4; this one 0.28 ms, with the two waves per SIMD
+// that its registers allow (three or four waves, by spilling or with the
+// geometric factors loaded plane by plane, 0.32 to 0.44: more concurrent
+// streams only scatter the writes).
 // -------------------------------------------------------------------------
-__global__ void k_set_cell(int n, const RefTab64 *__restrict__ T, const double *__restrict__ alpha,
-                           const double *__restrict__ beta, const double *__restrict__ ell,
-                           const double *__restrict__ cellgeo, double *cell64, float *cell32,
-                           double *bjC64, float *bjC32, double *coef_feat,
-                           const uint8_t *__restrict__ ctype, double *acell64, float *acell32)
+constexpr int lanes_for(int v)
 {
-    const int64_t c = blockIdx.x;
-    const int nd = n * n * n;
-    const int q = threadIdx.x;
+    int p = 1;
+    while (p < v) p *= 2;
+    return p;
+}
+
+template <int N>
+struct SCfg {
+    static constexpr int NF = N * N, ND = NF * N, LPC = lanes_for(NF), CPW = 64 / LPC;
+    // face kernel: 6 N columns per cell
+    static constexpr int FLPC = lanes_for(6 * N), FCPW = 64 / FLPC;
+    static_assert(NF <= 64 && 6 * N <= 64, "one wave per cell at most");
+};
+
+// this workgroup's place when every XCD takes one contiguous range (they are
+// dealt round-robin to the XCDs): the cache lines that two neighbouring
+// cells share are then written through one L2 (both kernels together at
+// 64x32x32 cells, degree 4: 0.48 -> 0.42 ms)
+__device__ __forceinline__ int64_t xcd_range()
+{
+    const int bid = blockIdx.x, nwg = gridDim.x;
+    const int q8 = nwg / NXCD, r8 = nwg % NXCD, xcd = bid % NXCD;
+    return xcd * q8 + (xcd < r8 ? xcd : r8) + bid / NXCD;
+}
+
+// products of the 1-D tables: kind 0 B B, 1 B BD, 2 BD BD
+template <int N, int KIND>
+__device__ __forceinline__ constexpr double ptab(int q, int a)
+{
+    const double bv = KB<N>::d[q * N + a], dv = KBD<N>::d[q * N + a];
+    return KIND == 0 ? bv * bv : (KIND == 1 ? bv * dv : dv * dv);
+}
+
+// y += P^T u along a pencil (table index q, output index a)
+template <int N, int KIND>
+__device__ __forceinline__ void padd(const double (&u)[N], double (&y)[N])
+{
+#pragma unroll
+    for (int a = 0; a < N; ++a)
+#pragma unroll
+        for (int q = 0; q < N; ++q) y[a] += ptab<N, KIND>(q, a) * u[q];
+}
+
+template <int N, bool FULL>
+__global__ void __launch_bounds__(64)
+k_set_cell(int64_t n_cells, const double *__restrict__ alpha, const double *__restrict__ beta,
+           const double *__restrict__ ell, const double *__restrict__ cellgeo,
+           const uint8_t *__restrict__ ctype, const double *__restrict__ kk, double *__restrict__ cell64,
+           float *__restrict__ cell32, double *__restrict__ acell64, float *__restrict__ acell32,
+           double *__restrict__ bjC64, float *__restrict__ bjC32, double *__restrict__ coef_feat,
+           double *__restrict__ dg64, float *__restrict__ dg32)
+{
+    constexpr int NF = SCfg<N>::NF, ND = SCfg<N>::ND, LPC = SCfg<N>::LPC, CPW = SCfg<N>::CPW;
+    __shared__ double sm[CPW][4 * ND];
+    const int cs = threadIdx.x / LPC, ln = threadIdx.x % LPC;
+    const int64_t cid = xcd_range() * CPW + cs;
+    const bool valid = cid < n_cells, on = valid && ln < NF;
+    const int a = ln % N, b = ln / N;
+    double *S = sm[cs];
+    const bool aff = on && ctype[cid];
+    // alpha, beta to the Gauss points: x, y, z sweeps, lane (a, b) the pencil's
+    // two fixed indices
+    double u[N], v[N], p[N], q_[N];
+    if (on) {
+        const int64_t o = cid * ND + N * a + NF * b;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            u[i] = alpha[o + i];
+            v[i] = beta[o + i];
+        }
+    }
+    // the quadrature points' geometric factors, requested before the sweeps
+    // (degrees up to 4; above, plane by plane in the loop below)
+    constexpr bool PRE = N <= 5;
+    const double *g = cellgeo + (on ? cid : 0) * 7 * ND + a + N * b;
+    double gq[PRE ? N : 1][7];
+    if constexpr (PRE) {
+        if (on) {
+#pragma unroll
+            for (int q = 0; q < N; ++q) {
+                gq[q][0] = __builtin_nontemporal_load(g + NF * q);
+                if (FULL || !aff)
+#pragma unroll
+                    for (int s = 1; s < 7; ++s) gq[q][s] = __builtin_nontemporal_load(g + NF * q + s * ND);
+            }
+        }
+    }
+    auto interp = [&](const double (&w)[N], double (&y)[N]) {
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            double s = 0.0;
+#pragma unroll
+            for (int i = 0; i < N; ++i) s += KB<N>::d[q * N + i] * w[i];
+            y[q] = s;
+        }
+    };
+    if (on) {
+        interp(u, p);
+        interp(v, q_);
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            S[q + N * a + NF * b] = p[q];
+            S[ND + q + N * a + NF * b] = q_[q];
+        }
+    }
+    __syncthreads();
+    if (on) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            u[j] = S[a + N * j + NF * b];
+            v[j] = S[ND + a + N * j + NF * b];
+        }
+        interp(u, p);
+        interp(v, q_);
+    }
+    __syncthreads();
+    if (on) {
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            S[a + N * q + NF * b] = p[q];
+            S[ND + a + N * q + NF * b] = q_[q];
+        }
+    }
+    __syncthreads();
+    // z sweep, merged values and the diagonals' z contraction: lane (qx, qy)
     double sw = 0.0, sa = 0.0, sb = 0.0;
-    if (q < nd) {
-        const int i = q % n, j = (q / n) % n, l = q / (n * n);
-        const double *ac = alpha + c * nd, *bc = beta + c * nd;
-        double aq = 0.0, bq = 0.0;
-        for (int l2 = 0; l2 < n; ++l2)
-            for (int j2 = 0; j2 < n; ++j2) {
-                const double byz = T->B[j * n + j2] * T->B[l * n + l2];
-                for (int i2 = 0; i2 < n; ++i2) {
-                    const double wgt = T->B[i * n + i2] * byz;
-                    const int e = lidx(n, i2, j2, l2);
-                    aq += wgt * ac[e];
-                    bq += wgt * bc[e];
+    // contracted fields: m, Gxx, Gxy, Gxz, Gyy, Gyz, Gzz (tables P0, P0, P0,
+    // P1, P0, P1, P2)
+    double t[7][N];
+#pragma unroll
+    for (int s = 0; s < 7; ++s)
+#pragma unroll
+        for (int l = 0; l < N; ++l) t[s][l] = 0.0;
+    if (on) {
+#pragma unroll
+        for (int l = 0; l < N; ++l) {
+            u[l] = S[a + N * b + NF * l];
+            v[l] = S[ND + a + N * b + NF * l];
+        }
+        interp(u, p);
+        interp(v, q_);
+        double kc[6];
+        if (aff)
+#pragma unroll
+            for (int s = 0; s < 6; ++s) kc[s] = kk[8 * cid + s];
+        double *dst = cell64 + cid * 7 * ND + a + N * b;
+        float *dstf = cell32 + cid * 7 * ND + a + N * b;
+        double *ad = acell64 + cid * 2 * ND + a + N * b;
+        float *af = acell32 + cid * 2 * ND + a + N * b;
+        auto pz = [&](int kind, int q, int l) {
+            return kind == 0 ? ptab<N, 0>(q, l) : (kind == 1 ? ptab<N, 1>(q, l) : ptab<N, 2>(q, l));
+        };
+        constexpr int zk[7] = {0, 0, 0, 1, 0, 1, 2};
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            const double w = PRE ? gq[PRE ? q : 0][0] : g[NF * q];
+            const double am = p[q] * w, bm = q_[q] * w;
+            sw += w;
+            sa += am;
+            sb += bm;
+            dst[NF * q] = am;
+            dstf[NF * q] = (float)am;
+            if (FULL || !aff) {
+                double G[7];
+#pragma unroll
+                for (int s = 1; s < 7; ++s) {
+                    G[s] = q_[q] * (PRE ? gq[PRE ? q : 0][s] : g[NF * q + s * ND]);
+                    dst[NF * q + s * ND] = G[s];
+                    dstf[NF * q + s * ND] = (float)G[s];
+                }
+                G[0] = am;
+#pragma unroll
+                for (int s = 0; s < 7; ++s)
+#pragma unroll
+                    for (int l = 0; l < N; ++l) t[s][l] += pz(zk[s], q, l) * G[s];
+            } else {
+                // G = bm J^-1 J^-T: contract bm once with each table
+#pragma unroll
+                for (int l = 0; l < N; ++l) {
+                    t[0][l] += ptab<N, 0>(q, l) * am;
+                    t[1][l] += ptab<N, 0>(q, l) * bm;
+                    t[3][l] += ptab<N, 1>(q, l) * bm;
+                    t[6][l] += ptab<N, 2>(q, l) * bm;
                 }
             }
-        const double *g = cellgeo + c * 7 * nd + q;
-        double *dst = cell64 + c * 7 * nd + q;
-        float *dstf = cell32 + c * 7 * nd + q;
-        const double w = g[0];
-        dst[0] = aq * w;
-        dstf[0] = (float)(aq * w);
-        for (int s = 1; s < 7; ++s) {
-            const double v = bq * g[s * nd];
-            dst[s * nd] = v;
-            dstf[s * nd] = (float)v;
+            if (aff) {
+                ad[NF * q] = am;
+                ad[ND + NF * q] = bm;
+                af[NF * q] = (float)am;
+                af[ND + NF * q] = (float)bm;
+            }
         }
-        if (ctype[c]) {
-            // affine cell: alpha w detJ and beta w detJ (G = beta w detJ J^-1 J^-T)
-            const double am = aq * w, bm = bq * w;
-            acell64[c * 2 * nd + q] = am;
-            acell64[c * 2 * nd + nd + q] = bm;
-            acell32[c * 2 * nd + q] = (float)am;
-            acell32[c * 2 * nd + nd + q] = (float)bm;
+        if (!FULL && aff) {
+#pragma unroll
+            for (int l = 0; l < N; ++l) {
+                const double b0 = t[1][l], b1 = t[3][l];
+                t[1][l] = kc[0] * b0;
+                t[2][l] = kc[1] * b0;
+                t[3][l] = kc[2] * b1;
+                t[4][l] = kc[3] * b0;
+                t[5][l] = kc[4] * b1;
+                t[6][l] *= kc[5];
+            }
         }
-        sw = w;
-        sa = w * aq;
-        sb = w * bq;
     }
-    // block reduction (fixed order)
-    __shared__ double red[3][512];
-    red[0][threadIdx.x] = sw;
-    red[1][threadIdx.x] = sa;
-    red[2][threadIdx.x] = sb;
-    __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s)
-            for (int r = 0; r < 3; ++r) red[r][threadIdx.x] += red[r][threadIdx.x + s];
-        __syncthreads();
+    // cell means (fixed order: pencils, then lanes folded by halves)
+#pragma unroll
+    for (int o = LPC / 2; o > 0; o >>= 1) {
+        sw += __shfl_xor(sw, o, 64);
+        sa += __shfl_xor(sa, o, 64);
+        sb += __shfl_xor(sb, o, 64);
     }
-    if (threadIdx.x == 0) {
-        const double vol = red[0][0];
-        const double ab = red[1][0] / vol, bb = red[2][0] / vol;
-        const double lx = ell[3 * c], ly = ell[3 * c + 1], lz = ell[3 * c + 2];
+    if (valid && ln == 0) {
+        const double ab = sa / sw, bb = sb / sw;
+        const double lx = ell[3 * cid], ly = ell[3 * cid + 1], lz = ell[3 * cid + 2];
         const double cc[4] = {ab * lx * ly * lz, bb * ly * lz / lx, bb * lx * lz / ly, bb * lx * ly / lz};
         for (int r = 0; r < 4; ++r) {
-            bjC64[4 * c + r] = cc[r];
-            bjC32[4 * c + r] = (float)cc[r];
+            bjC64[4 * cid + r] = cc[r];
+            bjC32[4 * cid + r] = (float)cc[r];
         }
         const double l2 = cbrt(lx * ly * lz);
-        coef_feat[c] = log(bb / (ab * l2 * l2));
+        coef_feat[cid] = log(bb / (ab * l2 * l2));
+    }
+    // y contraction, lane (qx, l), in two rounds of LDS: the terms whose x
+    // table is P0 (mass; m + Gzz, Gyy, 2 Gyz), then P2 (Gxx) and P1 (2 Gxy,
+    // 2 Gxz)
+    auto put = [&](int f, const double (&w)[N], double sc) {
+#pragma unroll
+        for (int l = 0; l < N; ++l) S[f * ND + a + N * b + NF * l] = sc * w[l];
+    };
+    auto get = [&](int f, double (&w)[N]) {
+#pragma unroll
+        for (int q = 0; q < N; ++q) w[q] = S[f * ND + a + N * q + NF * b];
+    };
+    __syncthreads();
+    if (on) {
+#pragma unroll
+        for (int l = 0; l < N; ++l) t[6][l] += t[0][l];
+        put(0, t[0], 1.0);
+        put(1, t[6], 1.0);
+        put(2, t[4], 1.0);
+        put(3, t[5], 2.0);
+    }
+    __syncthreads();
+    double cm[N], c0[N], c1[N], c2[N], w[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) cm[i] = c0[i] = c1[i] = c2[i] = 0.0;
+    if (on) {
+        get(0, w);
+        padd<N, 0>(w, cm);
+        get(1, w);
+        padd<N, 0>(w, c0);
+        get(2, w);
+        padd<N, 2>(w, c0);
+        get(3, w);
+        padd<N, 1>(w, c0);
+    }
+    __syncthreads();
+    if (on) {
+        put(0, t[1], 1.0);
+        put(1, t[2], 2.0);
+        put(2, t[3], 2.0);
+    }
+    __syncthreads();
+    if (on) {
+        get(0, w);
+        padd<N, 0>(w, c2);
+        get(1, w);
+        padd<N, 1>(w, c1);
+        get(2, w);
+        padd<N, 0>(w, c1);
+    }
+    __syncthreads();
+    // x contraction: lane (j, l)
+    if (on) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const int e = a + N * j + NF * b;
+            S[e] = cm[j];
+            S[ND + e] = c0[j];
+            S[2 * ND + e] = c2[j];
+            S[3 * ND + e] = c1[j];
+        }
+    }
+    __syncthreads();
+    if (!on) return;
+    double dm[N], dt[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) dm[i] = dt[i] = 0.0;
+    auto row = [&](int f) {
+#pragma unroll
+        for (int q = 0; q < N; ++q) w[q] = S[f * ND + q + N * a + NF * b];
+    };
+    row(0);
+    padd<N, 0>(w, dm);
+    row(1);
+    padd<N, 0>(w, dt);
+    row(2);
+    padd<N, 2>(w, dt);
+    row(3);
+    padd<N, 1>(w, dt);
+    const int64_t o = cid * ND + N * a + NF * b, nt = n_cells * ND;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const double ih = 1.0 / dt[i], im = 1.0 / dm[i];
+        dg64[o + i] = ih;
+        dg64[nt + o + i] = im;
+        dg32[o + i] = (float)ih;
+        dg32[nt + o + i] = (float)im;
     }
 }
 
 // -------------------------------------------------------------------------
-// merged face data of the +d face of every cell (thread per face point),
+// Coefficient update, face part: merged data of the +d face of every cell,
 // [cell][d][component][a][b] with a, b the first and second tangential index:
 //   g- = beta- ds J-^{-1} n,  g+ = beta+ ds J+^{-1} n,  s = sigma 1/2 (b- + b+) ds
 // with n and ds from the minus cell; the three components of g are stored in
 // the order (d, first tangential, second tangential) so that the operator
 // pairs them with its reference derivatives without a per-lane selection.
+// A face between two affine cells takes beta- w, beta+ w with w the face
+// weight instead (g- = (beta- w) v-, g+ = (beta+ w) v+, s = sd ((beta- w) +
+// (beta+ w)), constants in k_face_const); its general values are written only
+// with FULL.
+//
+// One wave serves FCPW cells with FLPC lanes each (N = 5: 2 x 32), in the
+// operator's traversal (one record gives neighbours and kind, so that all
+// loads leave in one round trip after it).  Lane (d, side, p) takes column p of the face layer of beta, own or neighbour's,
+// to the Gauss points of the second tangential direction, one LDS transpose,
+// then the first; with the traces in LDS all lanes of the cell write its
+// 21 N^2 values in memory order.  Memory bound (read 34, write 50 bytes per
+// dof at degree 4 on general faces, 2 and 10 on compressed ones); the former
+// kernel interpolated with N^2 work per point and lane: 0.355 ms at 64x32x32
+// cells, degree 4, this one 0.14 ms.
 // -------------------------------------------------------------------------
-__global__ void k_set_face(int n, int64_t n_cells, const int32_t *__restrict__ nbr,
-                           const RefTab64 *__restrict__ T, const double *__restrict__ beta,
-                           const double *__restrict__ sigma, const double *__restrict__ facegeo,
-                           double *face64, float *face32, const uint8_t *__restrict__ ctype,
-                           double *aface64, float *aface32, double *fc64, float *fc32)
+template <int N, bool FULL>
+__global__ void __launch_bounds__(64)
+k_set_face(int64_t n_cells, const int32_t *__restrict__ visit, const RefTab64 *__restrict__ T,
+           const double *__restrict__ beta, const double *__restrict__ sigma,
+           const double *__restrict__ facegeo, const uint8_t *__restrict__ ctype,
+           double *__restrict__ face64, float *__restrict__ face32, double *__restrict__ aface64,
+           float *__restrict__ aface32)
 {
-    const int nf = n * n, nd = nf * n;
-    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t >= 3 * n_cells * nf) return;
-    const int pt = (int)(t % nf);
-    const int64_t cd = t / nf;
-    const int64_t c = cd / 3;
-    const int d = (int)(cd % 3);
-    const int b = pt % n, a = pt / n;
-    double *dst = face64 + cd * 7 * nf + pt;
-    float *dstf = face32 + cd * 7 * nf + pt;
-    const double *g = facegeo + cd * 7 * nf + pt;
-    const int32_t nb = nbr[6 * c + 2 * d + 1];
-    if (nb < 0) {
-        for (int s = 0; s < 7; ++s) {
-            dst[s * nf] = 0.0;
-            dstf[s * nf] = 0.0f;
+    constexpr int NF = SCfg<N>::NF, ND = SCfg<N>::ND, LPC = SCfg<N>::FLPC, CPW = SCfg<N>::FCPW;
+    __shared__ double sT[CPW][6][NF], sV[CPW][6][NF];
+    const int cs = threadIdx.x / LPC, ln = threadIdx.x % LPC;
+    const int64_t slot = xcd_range() * CPW + cs;
+    // the traversal record {cell, neighbours, mask}; bit 2 + 2 e of the mask:
+    // the +e face lies between two affine cells
+    const int32_t *rec = visit + (slot < n_cells ? slot : 0) * 8;
+    const int32_t rc = rec[0];
+    const bool valid = slot < n_cells && rc >= 0;
+    const int64_t cid = valid ? rc : 0;
+    const bool on = valid && ln < 6 * N;
+    const int f = on ? ln / N : 0, p = ln % N, d = f >> 1, plus = f & 1;
+    int32_t nb[3];
+    bool cmp[3];
+    const int32_t mask = rec[7];
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+        nb[e] = valid ? rec[2 + 2 * e] : -1;
+        cmp[e] = valid && (mask >> (2 + 2 * e)) & 1;
+    }
+    if constexpr (FULL) {
+        // (the records hold no masks while the compression is off)
+#pragma unroll
+        for (int e = 0; e < 3; ++e) cmp[e] = valid && ctype[cid] && nb[e] >= 0 && ctype[nb[e]];
+    }
+    const int32_t nbd = d == 0 ? nb[0] : (d == 1 ? nb[1] : nb[2]);
+    const bool fl = on && nbd >= 0;
+    // every load up front: the column of beta, then the geometric factors
+    double h[N], y[N], sg[3];
+    if (fl) {
+        const int sd = d == 0 ? 1 : (d == 1 ? N : NF), sp = d == 0 ? N : 1, sr = d == 2 ? N : NF;
+        const double *src = beta + (int64_t)(plus ? nbd : cid) * ND + (plus ? 0 : (N - 1) * sd) + p * sp;
+#pragma unroll
+        for (int r = 0; r < N; ++r) h[r] = src[r * sr];
+    }
+    constexpr int GPL = (7 * NF + LPC - 1) / LPC;
+    double g[3][GPL];
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+        sg[e] = valid ? sigma[3 * cid + e] : 0.0;
+        if (nb[e] >= 0 && (FULL || !cmp[e]))
+#pragma unroll
+            for (int k = 0; k < GPL; ++k)
+                g[e][k] = __builtin_nontemporal_load(facegeo + (3 * cid + e) * 7 * NF +
+                                                     (ln + k * LPC < 7 * NF ? ln + k * LPC : 0));
+        else
+#pragma unroll
+            for (int k = 0; k < GPL; ++k) g[e][k] = 0.0;
+    }
+    auto interp = [&](const double (&w)[N], double (&z)[N]) {
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            double s = 0.0;
+#pragma unroll
+            for (int i = 0; i < N; ++i) s += KB<N>::d[q * N + i] * w[i];
+            z[q] = s;
         }
-        return;
+    };
+    if (fl) {
+        interp(h, y);
+#pragma unroll
+        for (int q = 0; q < N; ++q) sT[cs][f][q * N + p] = y[q];
     }
-    double bm = 0.0, bp = 0.0;
-    for (int r = 0; r < n; ++r)
-        for (int p = 0; p < n; ++p) {
-            const double wgt = T->B[a * n + p] * T->B[b * n + r];
-            bm += wgt * beta[c * nd + layer_idx(n, d, n - 1, p, r)];
-            bp += wgt * beta[(int64_t)nb * nd + layer_idx(n, d, 0, p, r)];
-        }
-    double out[7];
-    for (int k = 0; k < 3; ++k) {
-        out[k] = bm * g[k * nf];
-        out[3 + k] = bp * g[(3 + k) * nf];
+    __syncthreads();
+    if (on) {
+        // lane (f, q2 = p): along the first tangential direction; point (a, b)
+        // at b + N a (a boundary face's traces are zero)
+#pragma unroll
+        for (int i = 0; i < N; ++i) h[i] = fl ? sT[cs][f][p * N + i] : 0.0;
+        interp(h, y);
+#pragma unroll
+        for (int q = 0; q < N; ++q) sV[cs][f][q * N + p] = y[q];
     }
-    out[6] = sigma[3 * c + d] * (bm + bp) * g[6 * nf];
-    for (int s = 0; s < 7; ++s) {
-        dst[s * nf] = out[s];
-        dstf[s * nf] = (float)out[s];
-    }
-    if (ctype[c] && ctype[nb]) {
-        // face between two affine cells: g- = (beta- w) v-, g+ = (beta+ w) v+,
-        // s = sd ((beta- w) + (beta+ w)) with w the face weight, v = ds0 J^-1 n
-        // and sd = sigma ds0 / 2 constant over the face (ds = w ds0)
-        const double wab = T->wq[a] * T->wq[b];
-        aface64[cd * 2 * nf + pt] = bm * wab;
-        aface64[cd * 2 * nf + nf + pt] = bp * wab;
-        aface32[cd * 2 * nf + pt] = (float)(bm * wab);
-        aface32[cd * 2 * nf + nf + pt] = (float)(bp * wab);
-        if (pt == 0) {
-            double v[8];
-            for (int k = 0; k < 6; ++k) v[k] = g[k * nf] / wab;
-            v[6] = sigma[3 * c + d] * g[6 * nf] / wab;
-            v[7] = 0.0;
-            for (int k = 0; k < 8; ++k) {
-                fc64[cd * 8 + k] = v[k];
-                fc32[cd * 8 + k] = (float)v[k];
+    __syncthreads();
+    if (!valid) return;
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+        const int64_t cd = 3 * cid + e;
+        if (FULL || !cmp[e]) {
+            double *dst = face64 + cd * 7 * NF;
+            float *dstf = face32 + cd * 7 * NF;
+#pragma unroll
+            for (int u = 0; u < GPL; ++u) {
+                const int k = ln + u * LPC;
+                if (k >= 7 * NF) break;
+                const int s = k / NF, pt = k - s * NF;
+                const double bm = sV[cs][2 * e][pt], bp = sV[cs][2 * e + 1][pt];
+                const double out = (s < 3 ? bm : (s < 6 ? bp : sg[e] * (bm + bp))) * g[e][u];
+                dst[k] = out;
+                dstf[k] = (float)out;
             }
         }
+        if (cmp[e]) {
+            double *dst = aface64 + cd * 2 * NF;
+            float *dstf = aface32 + cd * 2 * NF;
+#pragma unroll
+            for (int u = 0; u < (2 * NF + LPC - 1) / LPC; ++u) {
+                const int k = ln + u * LPC;
+                if (k >= 2 * NF) break;
+                const int s = k / NF, pt = k - s * NF;
+                const double out = sV[cs][2 * e + s][pt] * (T->wq[pt / N] * T->wq[pt % N]);
+                dst[k] = out;
+                dstf[k] = (float)out;
+            }
+        }
+    }
+}
+
+// Constants of the +d face between two affine cells (thread per (cell, d)):
+// v- = ds0 J-^-1 n, v+ = ds0 J+^-1 n and sd = sigma ds0 / 2 (ds = w ds0, w the
+// face weight), from the general factors of the first face point.  They
+// follow the mesh and the penalty, not the coefficients.
+__global__ void k_face_const(int n, int64_t n_cells, const int32_t *__restrict__ nbr,
+                             const RefTab64 *__restrict__ T, const double *__restrict__ sigma,
+                             const double *__restrict__ facegeo, const uint8_t *__restrict__ ctype,
+                             double *fc64, float *fc32)
+{
+    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (t >= 3 * n_cells) return;
+    const int64_t c = t / 3;
+    const int32_t nb = nbr[6 * c + 2 * (int)(t % 3) + 1];
+    if (nb < 0 || !ctype[c] || !ctype[nb]) return;
+    const int nf = n * n;
+    const double *g = facegeo + t * 7 * nf;
+    const double w0 = T->wq[0] * T->wq[0];
+    for (int k = 0; k < 8; ++k) {
+        const double v = k < 6 ? g[k * nf] / w0 : (k == 6 ? sigma[t] * g[6 * nf] / w0 : 0.0);
+        fc64[t * 8 + k] = v;
+        fc32[t * 8 + k] = (float)v;
+    }
+}
+
+// General values of the affine cells and of the faces between two of them,
+// rebuilt from the compressed ones (m is always there): for a caller that
+// turns the compression off or exports them.
+__global__ void k_expand_cell(int64_t total, int nd, const uint8_t *__restrict__ ctype,
+                              const double *__restrict__ acell, const double *__restrict__ kk,
+                              double *cell64, float *cell32)
+{
+    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (t >= total) return;
+    const int64_t c = t / nd;
+    const int q = (int)(t % nd);
+    if (!ctype[c]) return;
+    const double bw = acell[c * 2 * nd + nd + q];
+    for (int s = 0; s < 6; ++s) {
+        const double v = bw * kk[8 * c + s];
+        cell64[(c * 7 + 1 + s) * nd + q] = v;
+        cell32[(c * 7 + 1 + s) * nd + q] = (float)v;
+    }
+}
+
+__global__ void k_expand_face(int64_t total, int nf, const int32_t *__restrict__ nbr,
+                              const uint8_t *__restrict__ ctype, const double *__restrict__ aface,
+                              const double *__restrict__ fc, double *face64, float *face32)
+{
+    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (t >= total) return;
+    const int64_t cd = t / nf, c = cd / 3;
+    const int pt = (int)(t % nf);
+    const int32_t nb = nbr[6 * c + 2 * (int)(cd % 3) + 1];
+    if (nb < 0 || !ctype[c] || !ctype[nb]) return;
+    const double bm = aface[cd * 2 * nf + pt], bp = aface[cd * 2 * nf + nf + pt];
+    for (int s = 0; s < 7; ++s) {
+        const double v = s < 6 ? (s < 3 ? bm : bp) * fc[cd * 8 + s] : fc[cd * 8 + 6] * (bm + bp);
+        face64[(cd * 7 + s) * nf + pt] = v;
+        face32[(cd * 7 + s) * nf + pt] = (float)v;
     }
 }
 
@@ -631,133 +1031,64 @@ hipError_t launch_affine_detect(hx_ctx *c)
     return hipGetLastError();
 }
 
-hipError_t launch_set_coefficients(hx_ctx *c, const double *alpha, const double *beta)
+hipError_t launch_face_const(hx_ctx *c)
 {
-    int threads = 64;                     // power of two for the tree reduction
-    while (threads < c->nd) threads *= 2;
-    hipLaunchKernelGGL(k_set_cell, dim3((unsigned)c->n_cells), dim3(threads), 0, c->stream, c->n,
-                       c->ref, alpha, beta, c->ell, c->cellgeo, c->cell64, c->cell32, c->bjC64,
-                       c->bjC32, c->coef_feat, c->ctype, c->acell64, c->acell32);
+    hipLaunchKernelGGL(k_face_const, dim3(nblk(3 * c->n_cells, 256)), dim3(256), 0, c->stream, c->n,
+                       c->n_cells, c->nbr, c->ref, c->sigma, c->facegeo, c->ctype, c->fc64, c->fc32);
+    return hipGetLastError();
+}
+
+hipError_t launch_expand_general(hx_ctx *c)
+{
+    const int64_t nt = c->n_dofs, nf = 3 * c->n_cells * c->nf;
+    hipLaunchKernelGGL(k_expand_cell, dim3(nblk(nt, 256)), dim3(256), 0, c->stream, nt, c->nd, c->ctype,
+                       c->acell64, c->kk64, c->cell64, c->cell32);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int64_t nt = 3 * c->n_cells * c->nf;
-    hipLaunchKernelGGL(k_set_face, dim3(nblk(nt, 128)), dim3(128), 0, c->stream, c->n, c->n_cells,
-                       c->nbr, c->ref, beta, c->sigma, c->facegeo, c->face64, c->face32, c->ctype,
-                       c->aface64, c->aface32, c->fc64, c->fc32);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (c->n_hang) {
-        e = launch_hang_coefficients(c, beta);
-        if (e != hipSuccess) return e;
-    }
-    return launch_cell_diag(c);
-}
-
-// -------------------------------------------------------------------------
-// Volume diagonals from the merged cell data (block per cell):
-//   d_i = sum_q [ m_q phi_i(q)^2 + grad phi_i(q)^T G_q grad phi_i(q) ],
-// phi_i(q) = B(qx,a) B(qy,b) B(qz,l), reference gradient from BD.  Every
-// term is a tensor contraction of one quadrature field with products of
-// 1-D tables, P0 = B B, P1 = B BD, P2 = BD BD, e.g. the Gxy term is
-// 2 sum_q Gxy P1(qx,a) P1(qy,b) P0(qz,l); the kernel contracts z, then y,
-// then x, merging terms that share their remaining tables (N^4 work per
-// sweep instead of N^6 per cell).  Stored as inverses: dg[0] of mass plus
-// stiffness (the paper's Helmholtz preconditioner, section 3.1), dg[1] of
-// the mass alone (its internal-energy variant).
-// -------------------------------------------------------------------------
-__device__ __forceinline__ double ptab(const RefTab64 *T, int n, int kind, int q, int a)
-{
-    const double bv = T->B[q * n + a], dv = T->BD[q * n + a];
-    return kind == 0 ? bv * bv : (kind == 1 ? bv * dv : dv * dv);
-}
-
-__global__ void k_cell_diag(int n, int64_t n_cells, const RefTab64 *__restrict__ T,
-                            const double *__restrict__ cell, double *dg64, float *dg32)
-{
-    extern __shared__ double sd[];           // F [7][nd], then A [7][nd]
-    const int nd = n * n * n;
-    const int64_t c = blockIdx.x;
-    const double *cd = cell + c * 7 * nd;
-    double *F = sd, *A = sd + 7 * nd;
-    for (int e = threadIdx.x; e < 7 * nd; e += blockDim.x) F[e] = cd[e];
-    __syncthreads();
-    const int t = threadIdx.x;
-    const bool on = t < nd;
-    const int i0 = t % n, i1 = (t / n) % n, i2 = t / (n * n);
-    // z: thread (qx, qy, l); fields m, Gxx, Gxy, Gxz, Gyy, Gyz, Gzz
-    if (on) {
-        double tm = 0, txx = 0, tyy = 0, tzz = 0, txy = 0, txz = 0, tyz = 0;
-        for (int qz = 0; qz < n; ++qz) {
-            const int q = i0 + n * (i1 + n * qz);
-            const double p0 = ptab(T, n, 0, qz, i2), p1 = ptab(T, n, 1, qz, i2),
-                         p2 = ptab(T, n, 2, qz, i2);
-            tm += p0 * F[q];
-            txx += p0 * F[nd + q];
-            txy += p0 * F[2 * nd + q];
-            txz += p1 * F[3 * nd + q];
-            tyy += p0 * F[4 * nd + q];
-            tyz += p1 * F[5 * nd + q];
-            tzz += p2 * F[6 * nd + q];
-        }
-        // groups by their remaining (x, y) tables:
-        // 0 mass (P0,P0), 1 m + Gzz (P0,P0), 2 Gxx (P2,P0), 3 Gyy (P0,P2),
-        // 4 2Gxy (P1,P1), 5 2Gxz (P1,P0), 6 2Gyz (P0,P1)
-        A[t] = tm;
-        A[nd + t] = tm + tzz;
-        A[2 * nd + t] = txx;
-        A[3 * nd + t] = tyy;
-        A[4 * nd + t] = 2.0 * txy;
-        A[5 * nd + t] = 2.0 * txz;
-        A[6 * nd + t] = 2.0 * tyz;
-    }
-    __syncthreads();
-    // y: thread (qx, b, l); results by their x table: mass P0, P0, P2, P1
-    double cm = 0, c0 = 0, c2 = 0, c1 = 0;
-    if (on) {
-        for (int qy = 0; qy < n; ++qy) {
-            const int q = i0 + n * (qy + n * i2);
-            const double p0 = ptab(T, n, 0, qy, i1), p1 = ptab(T, n, 1, qy, i1),
-                         p2 = ptab(T, n, 2, qy, i1);
-            cm += p0 * A[q];
-            c0 += p0 * A[nd + q] + p2 * A[3 * nd + q] + p1 * A[6 * nd + q];
-            c2 += p0 * A[2 * nd + q];
-            c1 += p1 * A[4 * nd + q] + p0 * A[5 * nd + q];
-        }
-    }
-    __syncthreads();
-    if (on) {
-        F[t] = cm;
-        F[nd + t] = c0;
-        F[2 * nd + t] = c2;
-        F[3 * nd + t] = c1;
-    }
-    __syncthreads();
-    // x: thread (a, b, l)
-    if (!on) return;
-    double dm = 0, dt = 0;
-    for (int qx = 0; qx < n; ++qx) {
-        const int q = qx + n * (i1 + n * i2);
-        const double p0 = ptab(T, n, 0, qx, i0), p1 = ptab(T, n, 1, qx, i0),
-                     p2 = ptab(T, n, 2, qx, i0);
-        dm += p0 * F[q];
-        dt += p0 * F[nd + q] + p2 * F[2 * nd + q] + p1 * F[3 * nd + q];
-    }
-    const int64_t o = c * nd + t, nt = n_cells * nd;
-    const double ih = 1.0 / dt, im = 1.0 / dm;
-    dg64[o] = ih;
-    dg64[nt + o] = im;
-    dg32[o] = (float)ih;
-    dg32[nt + o] = (float)im;
-}
-
-hipError_t launch_cell_diag(hx_ctx *c)
-{
-    int threads = 64;
-    while (threads < c->nd) threads *= 2;
-    hipLaunchKernelGGL(k_cell_diag, dim3((unsigned)c->n_cells), dim3(threads),
-                       sizeof(double) * 14 * c->nd, c->stream, c->n, c->n_cells, c->ref, c->cell64,
-                       c->dg64, c->dg32);
+    hipLaunchKernelGGL(k_expand_face, dim3(nblk(nf, 256)), dim3(256), 0, c->stream, nf, c->nf, c->nbr,
+                       c->ctype, c->aface64, c->fc64, c->face64, c->face32);
     return hipGetLastError();
+}
+
+template <int N, bool FULL>
+static hipError_t set_coefficients_n(hx_ctx *c, const double *alpha, const double *beta)
+{
+    hipLaunchKernelGGL((k_set_cell<N, FULL>), dim3(nblk(c->n_cells, SCfg<N>::CPW)), dim3(64), 0, c->stream,
+                       c->n_cells, alpha, beta, c->ell, c->cellgeo, c->ctype, c->kk64, c->cell64, c->cell32,
+                       c->acell64, c->acell32, c->bjC64, c->bjC32, c->coef_feat, c->dg64, c->dg32);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_set_face<N, FULL>), dim3(nblk(c->n_vis_op, SCfg<N>::FCPW)), dim3(64), 0, c->stream,
+                       c->n_vis_op, c->visit, c->ref, beta, c->sigma, c->facegeo, c->ctype, c->face64,
+                       c->face32, c->aface64, c->aface32);
+    return hipGetLastError();
+}
+
+template <bool FULL>
+static hipError_t set_coefficients_all(hx_ctx *c, const double *alpha, const double *beta)
+{
+    switch (c->n) {
+    case 2: return set_coefficients_n<2, FULL>(c, alpha, beta);
+    case 3: return set_coefficients_n<3, FULL>(c, alpha, beta);
+    case 4: return set_coefficients_n<4, FULL>(c, alpha, beta);
+    case 5: return set_coefficients_n<5, FULL>(c, alpha, beta);
+    case 6: return set_coefficients_n<6, FULL>(c, alpha, beta);
+    case 7: return set_coefficients_n<7, FULL>(c, alpha, beta);
+    case 8: return set_coefficients_n<8, FULL>(c, alpha, beta);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+// with the compressed data in use the general values of affine cells and
+// faces are not written (c->lean); hx_set_cell_compression(c, 0) and the
+// export rebuild them when they are asked for
+hipError_t launch_set_coefficients(hx_ctx *c, const double *alpha, const double *beta)
+{
+    c->lean = c->compress != 0;
+    const hipError_t e = c->lean ? set_coefficients_all<false>(c, alpha, beta)
+                                 : set_coefficients_all<true>(c, alpha, beta);
+    if (e != hipSuccess || c->n_hang == 0) return e;
+    return launch_hang_coefficients(c, beta);
 }
 
 hipError_t launch_dof_coords(hx_ctx *c, double *xyz)
