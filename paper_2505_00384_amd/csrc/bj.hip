@@ -96,24 +96,7 @@ k_bj(const T *__restrict__ rin, T *__restrict__ z, const T *__restrict__ S, cons
     const bool active = slot && cid < n_cells;
 
     double acc_rr = 0.0, acc_rz = 0.0;
-    T sfac = 1;
     const bool scaled = !FUSE && !CHEB && part != nullptr;
-    if (scaled) {
-        static_assert(Cfg<N>::NT == 256, "the scaled form sums with a 256-thread workgroup");
-        __shared__ double shs[4];
-        sfac = (T)(1.0 / sqrt(sum256(part, ld, shs)));
-    }
-    // p.q: the operator's partial sums summed here (every workgroup the same
-    // fixed order), or the value in sc[1]
-    double pq = 0.0;
-    if (FUSE) {
-        if (pqp) {
-            __shared__ double shq[4];
-            pq = sum256(pqp, npq, shq);
-        } else {
-            pq = sc[1];
-        }
-    }
     // every global load of the cell at once (one memory round trip): the
     // residual (and for the CG step x, p and q), the eigenvector matrices,
     // the eigenvalues and the constants; each thread's values lie NF apart
@@ -142,6 +125,24 @@ k_bj(const T *__restrict__ rin, T *__restrict__ z, const T *__restrict__ S, cons
     }
     // (the scheduler would otherwise wait for each load before the next)
     __builtin_amdgcn_sched_barrier(0);
+    T sfac = 1;
+    // the scale and p.q while those loads are in flight
+    if (scaled) {
+        static_assert(Cfg<N>::NT == 256, "the scaled form sums with a 256-thread workgroup");
+        __shared__ double shs[4];
+        sfac = (T)(1.0 / sqrt(sum256(part, ld, shs)));
+    }
+    // p.q: the operator's partial sums summed here (every workgroup the same
+    // fixed order), or the value in sc[1]
+    double pq = 0.0;
+    if (FUSE) {
+        if (pqp) {
+            __shared__ double shq[4];
+            pq = sum256(pqp, npq, shq);
+        } else {
+            pq = sc[1];
+        }
+    }
     if (FUSE && active) {
         const T al = (T)(pq != 0.0 ? sc[0] / pq : 0.0);
 #pragma unroll
@@ -420,16 +421,6 @@ k_massinv(const T *__restrict__ rin, T *__restrict__ z, const T *__restrict__ wg
     const T fb = t < NF ? (T)(INV ? Fm[t] : Fm[(t % N) * N + t / N]) : T(0);
     T mq[N], v[N], w[N], rp[N];
     double acc_rr = 0.0, acc_rz = 0.0;
-    double pq = 0.0;
-    if (FUSE) {
-        static_assert(!FUSE || Cfg<N>::NT == 256, "the fused step sums with a 256-thread workgroup");
-        if (pqp) {
-            __shared__ double shq[4];
-            pq = sum256(pqp, npq, shq);
-        } else {
-            pq = sc[1];
-        }
-    }
     // every global load of the cell at once: the residual (and for the CG
     // step x, p and q) and the pencil's weights
     T rv[N], xv[N], pv[N], qv[N];
@@ -448,6 +439,16 @@ k_massinv(const T *__restrict__ rin, T *__restrict__ z, const T *__restrict__ wg
         for (int m = 0; m < N; ++m) mq[m] = wgt[cid * wstride + a + N * b + NF * m];
     }
     __builtin_amdgcn_sched_barrier(0);
+    double pq = 0.0;
+    if (FUSE) {
+        static_assert(!FUSE || Cfg<N>::NT == 256, "the fused step sums with a 256-thread workgroup");
+        if (pqp) {
+            __shared__ double shq[4];
+            pq = sum256(pqp, npq, shq);
+        } else {
+            pq = sc[1];
+        }
+    }
     if (t < NF) sB[t] = fb;
     if (FUSE && active) {
         const T al = (T)(pq != 0.0 ? sc[0] / pq : 0.0);

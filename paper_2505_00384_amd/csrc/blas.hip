@@ -208,39 +208,44 @@ __global__ void __launch_bounds__(1024) k_dcgs_coef(int j, int nb, const double 
     const int m = j + 1;
     sum_rows(part, 2 * m, nb, DC_LD, sums);
     __syncthreads();
-    if (threadIdx.x != 0) return;
-    const double *ca = sums, *cb = sums + m;
-    double cc = 0.0, ch = 0.0;
-    for (int k = 0; k < j; ++k) {
-        cc += ca[k] * ca[k];
-        ch += ca[k] * cb[k];
-    }
-    const double r2 = ca[j] - cc;
+    if (threadIdx.x >= 64) return;
+    // one wave, lane k the coefficients of vector k (j < 64)
+    const int k = threadIdx.x;
+    const double ca = k <= j ? sums[k] : 0.0, cb = k <= j ? sums[m + k] : 0.0;
+    const double cc = __shfl(wave_sum(k < j ? ca * ca : 0.0), 0, 64);
+    const double ch = __shfl(wave_sum(k < j ? ca * cb : 0.0), 0, 64);
+    const double tt = sums[j], tw = sums[m + j];
+    const double r2 = tt - cc;
     double flag = 0.0, rho;
-    if (r2 > 0.0 && r2 >= 1e-12 * ca[j]) {
+    if (r2 > 0.0 && r2 >= 1e-12 * tt) {
         rho = sqrt(r2);
     } else {
         flag = 1.0;
-        rho = ca[j] > 0.0 ? sqrt(ca[j]) : 1.0;
+        rho = tt > 0.0 ? sqrt(tt) : 1.0;
     }
-    const double hj = (cb[j] - ch) / rho;
-    for (int k = 0; k <= j; ++k) {
-        sc[k] = ca[k];
-        sc[64 + k] = cb[k];
-    }
-    for (int k = 0; k < j; ++k) sc[DC_CW + k] = cb[k] - ca[k] * (hj / rho);
-    sc[DC_S + 0] = 1.0 / rho;
-    sc[DC_S + 1] = hj / rho;
-    sc[DC_S + 2] = rho;
-    sc[DC_S + 3] = hj;
-    sc[DC_S + 4] = flag;
-    if (hout) {
-        for (int k = 0; k <= j; ++k) {
-            hout[k] = ca[k];
-            hout[64 + k] = cb[k];
+    const double hj = (tw - ch) / rho;
+    if (k <= j) {
+        sc[k] = ca;
+        sc[64 + k] = cb;
+        if (hout) {
+            host_store(hout + k, ca);
+            host_store(hout + 64 + k, cb);
         }
-        for (int k = 0; k < 5; ++k) hout[DC_S + k] = sc[DC_S + k];
     }
+    if (k < j) sc[DC_CW + k] = cb - ca * (hj / rho);
+    if (k == 0) {
+        sc[DC_S + 0] = 1.0 / rho;
+        sc[DC_S + 1] = hj / rho;
+        sc[DC_S + 2] = rho;
+        sc[DC_S + 3] = hj;
+        sc[DC_S + 4] = flag;
+        if (hout) {
+            host_store(hout + DC_S + 2, rho);
+            host_store(hout + DC_S + 3, hj);
+            host_store(hout + DC_S + 4, flag);
+        }
+    }
+    if (hout) host_stores_done();
 }
 
 // k_dcgs_update: with t = V[j],
@@ -292,7 +297,10 @@ __global__ void __launch_bounds__(RT) k_dcgs_update(int64_t n, int j, const doub
     nu = block_sum(nu, sh);
     if (threadIdx.x == 0) {
         part[blockIdx.x] = nu;
-        if (hpart) hpart[blockIdx.x] = nu;
+        if (hpart) {
+            host_store(hpart + blockIdx.x, nu);
+            host_stores_done();
+        }
     }
 }
 
@@ -482,6 +490,10 @@ __global__ void __launch_bounds__(256) k_cg_pt_red(int64_t n, const T *__restric
                                                    double *sc, int cur, double *host)
 {
     __shared__ double sh[4];
+    // the vectors' loads in flight while the partial sums are added
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const T zi = i < n ? z[i] : T(0), pi = i < n ? p[i] : T(0);
+    __builtin_amdgcn_sched_barrier(0);
     const double rz = sum256(part, nb, sh);
     const double old = sc[cur];
     const T bt = (T)(old != 0.0 ? rz / old : 0.0);
@@ -490,11 +502,13 @@ __global__ void __launch_bounds__(256) k_cg_pt_red(int64_t n, const T *__restric
         if (threadIdx.x == 0) {
             sc[2 - cur] = rz;
             sc[3] = rr;
-            if (host) *host = rr;
+            if (host) {
+                host_store(host, rr);
+                host_stores_done();
+            }
         }
     }
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i < n) p[i] = z[i] + bt * p[i];
+    if (i < n) p[i] = zi + bt * pi;
 }
 
 // stage 2 of a fused CG step whose z is final: workgroup 0 sums r.z (row 0
@@ -518,7 +532,10 @@ __global__ void __launch_bounds__(RT) k_red_cg(const double *__restrict__ part, 
         sc[0] = s;
     } else {
         sc[3] = s;
-        if (host) *host = s;
+        if (host) {
+            host_store(host, s);
+            host_stores_done();
+        }
     }
 }
 

@@ -32,6 +32,16 @@ namespace {
 
 constexpr int64_t SC_OFF = 1024 * 66;   // device scalar area inside c->red
 
+// Phase times from HIP events on the stream.  An event between two kernels
+// costs 2 to 4 us of idle device, so on small systems with a cheap step only
+// every TIMED-th step is timed and the sums are scaled to all steps (a solve
+// of 103 CG steps at 512,000 dofs, five events a step: 5.55 ms with every
+// step timed, 4.05 without timing); from 2^22 dofs on, where a step takes
+// 300 us, and with costly preconditioners every step is.  7 shares no factor
+// with the usual restart lengths, so all positions of a cycle are met.
+constexpr int TIMED = 7;
+constexpr int64_t TIME_ALL = (int64_t)1 << 22;
+
 struct Timer {
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
     double op = 0, pc = 0, orth = 0;
@@ -41,7 +51,7 @@ struct Timer {
         if (!on) return;
         ok = true;
         for (auto &e : ev)
-            if (hipEventCreate(&e) != hipSuccess) ok = false;
+            if (hipEventCreateWithFlags(&e, hipEventDisableSystemFence) != hipSuccess) ok = false;
     }
     ~Timer()
     {
@@ -74,6 +84,38 @@ struct Timer {
         op += span(1, 2);
         orth += span(2, 0);
         pc += span(0, 3);
+    }
+    // add the second timer of two steps in flight, and scale the sums of the
+    // timed steps to all
+    void finish(const Timer &other, int timed, int all)
+    {
+        const double f = timed > 0 ? (double)all / timed : 0.0;
+        op = (op + other.op) * f;
+        pc = (pc + other.pc) * f;
+        orth = (orth + other.orth) * f;
+    }
+};
+
+// Events that the host waits on.  fast: for values the kernels have stored
+// with host_store (their stores have arrived when the kernel ends), so the
+// event need not write back the caches; else with the system-scope fence,
+// for values that an asynchronous copy brings.
+struct Signals {
+    hipEvent_t fast[2] = {nullptr, nullptr}, full[2] = {nullptr, nullptr};
+    bool ok = true;
+    Signals()
+    {
+        for (auto &e : fast)
+            ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming | hipEventDisableSystemFence) == hipSuccess;
+        for (auto &e : full)
+            ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+    }
+    ~Signals()
+    {
+        for (auto &e : fast)
+            if (e) (void)hipEventDestroy(e);
+        for (auto &e : full)
+            if (e) (void)hipEventDestroy(e);
     }
 };
 
@@ -297,17 +339,16 @@ hx_status solve_cg(hx_ctx *c, const hx_solve_params *prm, const double *b, doubl
         return HX_OK;
     }
     // two steps in flight: slot k % 2 of the pinned buffer, events and timers
+    Signals sig;
+    if (!sig.ok) return fail(c, HX_ERR_DEVICE, "hipEventCreate failed");
     hipEvent_t done[2] = {nullptr, nullptr};
-    for (auto &e : done)
-        if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess)
-            return fail(c, HX_ERR_DEVICE, "hipEventCreate failed");
     Timer tb(true);
     Timer *tms[2] = {&tm, &tb};
+    const bool costly = prm->pc == HX_PC_CHEBYSHEV || prm->pc == HX_PC_MULTIGRID ||
+                        prm->pc == HX_PC_MULTIGRID_MIXED;
+    const int every = (costly || prm->system != 0 || n >= TIME_ALL) ? 1 : TIMED;
+    int timed = 0;
     double *hr = c->pin_host;   // slots 0, 1 (device-mapped: the reduction may write them)
-    auto cleanup = [&]() {
-        for (auto &e : done)
-            if (e) (void)hipEventDestroy(e);
-    };
     int it = 0, checked = 0;
     bool stop = false;
     hx_status err = HX_OK;
@@ -318,7 +359,10 @@ hx_status solve_cg(hx_ctx *c, const hx_solve_params *prm, const double *b, doubl
             err = fail(c, HX_ERR_DEVICE, "CG: event wait failed");
             return true;
         }
-        tms[k % 2]->acc_cg();
+        if (k % every == 0) {
+            tms[k % 2]->acc_cg();
+            ++timed;
+        }
         const double rk = std::sqrt(hr[k % 2]) / nb;
         if (info->history && k < info->history_len) info->history[k] = rk;
         checked = k + 1;
@@ -326,16 +370,20 @@ hx_status solve_cg(hx_ctx *c, const hx_solve_params *prm, const double *b, doubl
     };
     while (it < prm->max_iter && !stop) {
         Timer &t = *tms[it % 2];
-        t.rec(1, c->stream);
+        const bool timing = it % every == 0;
+        if (timing) t.rec(1, c->stream);
         int npq = 0;
         if (hipSuccess != sys_apply_dot(c, prm, p, q, sc + 1, &npq)) { err = fail(c, HX_ERR_DEVICE, "CG: apply"); break; }
-        t.rec(2, c->stream);
-        t.rec(0, c->stream);
+        if (timing) {
+            t.rec(2, c->stream);
+            t.rec(0, c->stream);
+        }
         int fl = 0;
         if (hipSuccess != cg_step_pc64(c, prm->pc, x, r, p, q, z, sc, c->pin_dev + it % 2, &fl, npq, &lp)) { err = fail(c, HX_ERR_DEVICE, "CG: step"); break; }
-        t.rec(3, c->stream);
+        if (timing) t.rec(3, c->stream);
         if (hipSuccess != cg_step_p64(c, z, p, sc, fl, &lp)) { err = fail(c, HX_ERR_DEVICE, "CG: p update"); break; }
         // |r|^2 for the host: written by the reduction itself, else copied
+        done[it % 2] = (fl & CG_RR_ON_HOST) ? sig.fast[it % 2] : sig.full[it % 2];
         if ((!(fl & CG_RR_ON_HOST) &&
              hipSuccess != hipMemcpyAsync(hr + it % 2, sc + 3, sizeof(double), hipMemcpyDeviceToHost,
                                           c->stream)) ||
@@ -349,10 +397,7 @@ hx_status solve_cg(hx_ctx *c, const hx_solve_params *prm, const double *b, doubl
     }
     // the steps still in flight
     while (err == HX_OK && checked < it) check(checked);
-    cleanup();
-    tm.op += tb.op;
-    tm.pc += tb.pc;
-    tm.orth += tb.orth;
+    tm.finish(tb, timed, it);
     if (err != HX_OK) return err;
     info->iters = it;
     info->history_len = info->history ? (it < info->history_len ? it : info->history_len) : 0;
@@ -456,20 +501,17 @@ hx_status solve_fgmres(hx_ctx *c, const hx_solve_params *prm, const double *b, d
     const bool delayed = prm->orth == 1;
     // delayed form: two steps in flight, slot j % 2 of the pinned buffer,
     // events and timers
-    struct Ready {
-        hipEvent_t e[2] = {nullptr, nullptr};
-        ~Ready()
-        {
-            for (auto &x : e)
-                if (x) (void)hipEventDestroy(x);
-        }
-    } rd;
-    hipEvent_t *ready = rd.e;
-    for (int i = 0; i < 2; ++i)
-        if (hipEventCreateWithFlags(&ready[i], hipEventDisableTiming) != hipSuccess)
-            return fail(c, HX_ERR_DEVICE, "hipEventCreate failed");
+    Signals sig;
+    if (!sig.ok) return fail(c, HX_ERR_DEVICE, "hipEventCreate failed");
+    hipEvent_t *ready = sig.fast;
     Timer tb(tm.ok);
     Timer *tms[2] = {&tm, &tb};
+    const bool costly = prm->mixed == 1 || prm->pc == HX_PC_CHEBYSHEV || prm->pc == HX_PC_MULTIGRID ||
+                        prm->pc == HX_PC_MULTIGRID_MIXED;
+    const int every = (costly || prm->system != 0 || n >= TIME_ALL) ? 1 : TIMED;
+    int timed = 0, steps = 0;        // steps whose times were taken, and all
+    double fin_ms = 0.0;             // the cycles' extra block dots
+    Timer tfin(tm.ok);
     int nb_step[2] = {0, 0};
     double *fin_host = c->red_host;
 
@@ -504,13 +546,13 @@ hx_status solve_fgmres(hx_ctx *c, const hx_solve_params *prm, const double *b, d
     // V[0..j] and finalise column j (H(0..j, j) += nu c, H(j+1, j) = nu rho)
     double nu_prev = 0.0;
     auto finalise = [&](int j) -> hx_status {
-        tm.rec(2, c->stream);
+        tfin.rec(2, c->stream);
         HX_HIP(c, blas_mdot(c, n, j + 2, V, n, V + (size_t)(j + 1) * n, sc));
-        tm.rec(3, c->stream);
+        tfin.rec(3, c->stream);
         HX_HIP(c, hipMemcpyAsync(fin_host, sc, sizeof(double) * (j + 2), hipMemcpyDeviceToHost,
                                  c->stream));
         HX_HIP(c, hipStreamSynchronize(c->stream));
-        tm.orth += tm.span(2, 3);
+        fin_ms += tfin.span(2, 3);
         double cc = 0.0;
         for (int i = 0; i <= j; ++i) cc += fin_host[i] * fin_host[i];
         const double r2 = fin_host[j + 1] - cc;
@@ -553,6 +595,8 @@ hx_status solve_fgmres(hx_ctx *c, const hx_solve_params *prm, const double *b, d
                                          hipMemcpyDeviceToHost, c->stream));
                 HX_HIP(c, hipStreamSynchronize(c->stream));
                 tm.acc();
+                ++timed;
+                ++steps;
                 for (int i = 0; i <= j; ++i) H.h(i, j) = c->red_host[i] + c->red_host[64 + i];
                 const double hn = std::sqrt(c->red_host[128]);
                 H.h(j + 1, j) = hn;
@@ -590,7 +634,8 @@ hx_status solve_fgmres(hx_ctx *c, const hx_solve_params *prm, const double *b, d
         auto launch_step = [&](int j) -> hx_status {
             double *vj = V + (size_t)j * n, *zj = Z + (size_t)j * n;
             Timer &t = *tms[j % 2];
-            t.rec(0, c->stream);
+            const bool timing = (base + j) % every == 0;
+            if (timing) t.rec(0, c->stream);
             if (j > 0 && fuse) {
                 if (pc == HX_PC_LEARNED) {
                     hx_status st = mlp_apply_fused(c, w, c->red + RED_WPART, nb_prev, vj, zj);
@@ -602,14 +647,14 @@ hx_status solve_fgmres(hx_ctx *c, const hx_solve_params *prm, const double *b, d
                 hx_status st = precondition(c, pc, mixed, prm->inner_iters, vj, zj, w32, &info->inner_iters);
                 if (st != HX_OK) return st;
             }
-            t.rec(1, c->stream);
+            if (timing) t.rec(1, c->stream);
             HX_HIP(c, step_apply(c, prm, zj, w, w32));
-            t.rec(2, c->stream);
+            if (timing) t.rec(2, c->stream);
             const bool scale_now = !(fuse && will_launch(j + 1));
             HX_HIP(c, blas_dcgs(c, n, j, V, n, w, sc, c->pin_dev + (size_t)(j % 2) * FG_SLOT, scale_now,
                                 &nb_prev));
             nb_step[j % 2] = nb_prev;
-            t.rec(3, c->stream);
+            if (timing) t.rec(3, c->stream);
             HX_HIP(c, hipEventRecord(ready[j % 2], c->stream));
             return HX_OK;
         };
@@ -620,7 +665,11 @@ hx_status solve_fgmres(hx_ctx *c, const hx_solve_params *prm, const double *b, d
             if (ahead && (s = launch_step(j + 1)) != HX_OK) return s;
             if (hipEventSynchronize(ready[j % 2]) != hipSuccess)
                 return fail(c, HX_ERR_DEVICE, "FGMRES: event wait failed");
-            tms[j % 2]->acc();
+            ++steps;
+            if ((base + j) % every == 0) {
+                tms[j % 2]->acc();
+                ++timed;
+            }
             const double *hs = c->pin_host + (size_t)(j % 2) * FG_SLOT;
             const double rho = hs[DCGS_S + 2], hj = hs[DCGS_S + 3], flag = hs[DCGS_S + 4];
             const double nu = std::sqrt(host_sum256(hs + FG_PART, nb_step[j % 2]));
@@ -710,9 +759,8 @@ hx_status solve_fgmres(hx_ctx *c, const hx_solve_params *prm, const double *b, d
             }
         }
     }
-    tm.op += tb.op;
-    tm.pc += tb.pc;
-    tm.orth += tb.orth;
+    tm.finish(tb, timed, steps);
+    tm.orth += fin_ms;
     info->iters = it;
     info->history_len = info->history ? hist : 0;
     return HX_OK;
