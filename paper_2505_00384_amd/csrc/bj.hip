@@ -7,7 +7,8 @@
 // with S a Kronecker product of 1-D matrices), applied here to the
 // separable approximation of the Helmholtz cell block.
 //
-// Mapping: N*N threads per cell, one per pencil; 6 sweeps of N x N 1-D
+// Mapping: N*N threads per cell, one per pencil, a cell's threads in one wave
+// where enough of its lanes work (BjMap in bj_cell.hpp); 6 sweeps of N x N 1-D
 // matrices that differ per cell (kept in LDS) plus one diagonal scaling.
 // A fused form also performs the conjugate-gradient updates of x and r
 // before the solve and sums r.z and r.r per block, so one CG step touches
@@ -28,6 +29,12 @@ struct Cfg {
     static constexpr int NF = N * N, ND = N * N * N;
     static constexpr int CPB = (256 / NF) > 0 ? 256 / NF : 1;
     static constexpr int NT = ((CPB * NF + 63) / 64) * 64;
+};
+
+// block-Jacobi kernels: 256 threads
+template <int N>
+struct BCfg {
+    static constexpr int NF = N * N, ND = N * N * N, NT = 256, CPB = BjMap<N>::cells(NT);
 };
 
 // deterministic block sum of two values (result valid in thread 0)
@@ -70,14 +77,14 @@ __device__ __forceinline__ void block_sum2(double &u, double &v, double *sh)
 constexpr int CHEB_READ_D = 1, CHEB_ACCUM = 2;
 
 template <int N, typename T, bool FUSE, bool CHEB = false>
-__global__ void __launch_bounds__(Cfg<N>::NT)
+__global__ void __launch_bounds__(BCfg<N>::NT)
 k_bj(const T *__restrict__ rin, T *__restrict__ z, const T *__restrict__ S, const T *__restrict__ L,
      const T *__restrict__ C, int n_cells, int nwg, T *x, T *rw, const T *__restrict__ p,
      const T *__restrict__ q, const double *__restrict__ sc, double *part, int ld, T ca = 0,
      T cb = 0, int flags = 0, const double *__restrict__ pqp = nullptr, int npq = 0)
 {
     const T *r = FUSE ? rw : rin;
-    constexpr int NF = Cfg<N>::NF, ND = Cfg<N>::ND, CPB = Cfg<N>::CPB;
+    constexpr int NF = BCfg<N>::NF, ND = BCfg<N>::ND, CPB = BCfg<N>::CPB;
     __shared__ T sR[CPB][ND];
     __shared__ T sS[CPB][3][NF];
     __shared__ T sL[CPB][3][N];
@@ -87,10 +94,10 @@ k_bj(const T *__restrict__ rin, T *__restrict__ z, const T *__restrict__ S, cons
     const int q8 = nwg / NXCD, r8 = nwg % NXCD, xcd = bid % NXCD;
     const int wg = xcd * q8 + (xcd < r8 ? xcd : r8) + bid / NXCD;
     const int t = threadIdx.x;
-    const int lc0 = t / NF;
+    int lc0, tt;
+    BjMap<N>::place(t, BCfg<N>::NT, lc0, tt);
     const bool slot = lc0 < CPB;
     const int lc = slot ? lc0 : 0;
-    const int tt = t - lc0 * NF;
     const int a = tt % N, b = tt / N;
     const int64_t cid = (int64_t)wg * CPB + lc;
     const bool active = slot && cid < n_cells;
@@ -128,7 +135,7 @@ k_bj(const T *__restrict__ rin, T *__restrict__ z, const T *__restrict__ S, cons
     T sfac = 1;
     // the scale and p.q while those loads are in flight
     if (scaled) {
-        static_assert(Cfg<N>::NT == 256, "the scaled form sums with a 256-thread workgroup");
+        static_assert(BCfg<N>::NT == 256, "the scaled form sums with a 256-thread workgroup");
         __shared__ double shs[4];
         sfac = (T)(1.0 / sqrt(sum256(part, ld, shs)));
     }
@@ -177,8 +184,10 @@ k_bj(const T *__restrict__ rin, T *__restrict__ z, const T *__restrict__ S, cons
         }
         if (tt < 4) sC[lc][tt] = tC;
     }
-    __syncthreads();
-    bj_cell_solve<N, T>(sR[lc], sS[lc], sL[lc], sC[lc], a, b, active, acc_rz);
+    constexpr bool WAVE = BjMap<N>::WAVE;
+    if constexpr (WAVE) lds_wave_sync();
+    else __syncthreads();
+    bj_cell_solve<N, T, WAVE>(sR[lc], sS[lc], sL[lc], sC[lc], a, b, active, acc_rz);
     if (active) {
         if (CHEB) {
             T zo[N], xo[N];
@@ -203,8 +212,8 @@ k_bj(const T *__restrict__ rin, T *__restrict__ z, const T *__restrict__ S, cons
         }
     }
     if (FUSE) {
-        __shared__ double sh2[2 * (Cfg<N>::NT / 64)];
-        block_sum2<Cfg<N>::NT>(acc_rz, acc_rr, sh2);
+        __shared__ double sh2[2 * (BCfg<N>::NT / 64)];
+        block_sum2<BCfg<N>::NT>(acc_rz, acc_rr, sh2);
         if (threadIdx.x == 0) {
             part[bid] = acc_rz;
             part[ld + bid] = acc_rr;
@@ -225,13 +234,13 @@ struct CgArgs {
 template <int N, typename T>
 hipError_t bj_cheb_n(hx_ctx *c, const T *r, T *d, T *x, double ca, double cb, int flags)
 {
-    const int cpb = Cfg<N>::CPB;
+    const int cpb = BCfg<N>::CPB;
     const int nwg = (int)((c->n_cells + cpb - 1) / cpb);
     const bool dbl = std::is_same<T, double>::value;
     const T *S = dbl ? (const T *)c->bjS64 : (const T *)c->bjS32;
     const T *L = dbl ? (const T *)c->bjL64 : (const T *)c->bjL32;
     const T *C = dbl ? (const T *)c->bjC64 : (const T *)c->bjC32;
-    hipLaunchKernelGGL((k_bj<N, T, false, true>), dim3(nwg), dim3(Cfg<N>::NT), 0, c->stream, r, d,
+    hipLaunchKernelGGL((k_bj<N, T, false, true>), dim3(nwg), dim3(BCfg<N>::NT), 0, c->stream, r, d,
                        S, L, C, (int)c->n_cells, nwg, x, (T *)nullptr, (const T *)nullptr,
                        (const T *)nullptr, (const double *)nullptr, (double *)nullptr, 0, (T)ca,
                        (T)cb, flags);
@@ -258,7 +267,7 @@ hipError_t bj_cheb_dispatch(hx_ctx *c, const T *r, T *d, T *x, double ca, double
 template <int N, typename T>
 hipError_t bj_n(hx_ctx *c, const T *r, T *z, const CgArgs<T> *cg, int *nblk)
 {
-    const int cpb = Cfg<N>::CPB;
+    const int cpb = BCfg<N>::CPB;
     const int nwg = (int)((c->n_cells + cpb - 1) / cpb);
     const bool dbl = std::is_same<T, double>::value;
     const T *S = dbl ? (const T *)c->bjS64 : (const T *)c->bjS32;
@@ -266,11 +275,11 @@ hipError_t bj_n(hx_ctx *c, const T *r, T *z, const CgArgs<T> *cg, int *nblk)
     const T *C = dbl ? (const T *)c->bjC64 : (const T *)c->bjC32;
     if (nblk) *nblk = nwg;
     if (cg)
-        hipLaunchKernelGGL((k_bj<N, T, true>), dim3(nwg), dim3(Cfg<N>::NT), 0, c->stream, r, z, S,
+        hipLaunchKernelGGL((k_bj<N, T, true>), dim3(nwg), dim3(BCfg<N>::NT), 0, c->stream, r, z, S,
                            L, C, (int)c->n_cells, nwg, cg->x, cg->r, cg->p, cg->q, cg->sc,
                            c->cgpart, (int)c->n_cells + 1, (T)0, (T)0, 0, cg->pqp, cg->npq);
     else
-        hipLaunchKernelGGL((k_bj<N, T, false>), dim3(nwg), dim3(Cfg<N>::NT), 0, c->stream, r, z, S,
+        hipLaunchKernelGGL((k_bj<N, T, false>), dim3(nwg), dim3(BCfg<N>::NT), 0, c->stream, r, z, S,
                            L, C, (int)c->n_cells, nwg, (T *)nullptr, (T *)nullptr,
                            (const T *)nullptr, (const T *)nullptr, (const double *)nullptr,
                            (double *)nullptr, 0);
@@ -296,9 +305,9 @@ hipError_t bj_dispatch(hx_ctx *c, const T *r, T *z, const CgArgs<T> *cg = nullpt
 template <int N>
 hipError_t bj_scaled_n(hx_ctx *c, const double *w, const double *part, int nb, double *v, double *z)
 {
-    const int cpb = Cfg<N>::CPB;
+    const int cpb = BCfg<N>::CPB;
     const int nwg = (int)((c->n_cells + cpb - 1) / cpb);
-    hipLaunchKernelGGL((k_bj<N, double, false>), dim3(nwg), dim3(Cfg<N>::NT), 0, c->stream, w, z,
+    hipLaunchKernelGGL((k_bj<N, double, false>), dim3(nwg), dim3(BCfg<N>::NT), 0, c->stream, w, z,
                        c->bjS64, c->bjL64, c->bjC64, (int)c->n_cells, nwg, v, (double *)nullptr,
                        (const double *)nullptr, (const double *)nullptr, (const double *)nullptr,
                        const_cast<double *>(part), nb);

@@ -10,19 +10,58 @@
 
 namespace hx {
 
+// Order of LDS accesses between the lanes of one wave, whose LDS operations
+// execute in order: only the compiler has to keep them so.
+__device__ __forceinline__ void lds_wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Cells are packed into waves, 64 / N^2 each, so that a cell's threads never
+// wait for another wave, unless that leaves too many lanes empty (N = 6: 36 of
+// 64 against 252 of 256): then N^2 consecutive threads per cell and barriers.
+// At N = 5 50 of 64 lanes work instead of 250 of 256, and the sweeps of a
+// cell take its own latency, not the slowest of four waves'.
+template <int N>
+struct BjMap {
+    static constexpr int NF = N * N, CPW = 64 / NF;
+    static constexpr bool WAVE = 4 * CPW * 4 >= 3 * (256 / NF);
+    // cells of a workgroup of nt threads, and a thread's cell and index in it
+    // (a cell index at or past cells(nt): no cell)
+    static constexpr int cells(int nt) { return WAVE ? nt / 64 * CPW : nt / NF; }
+    __device__ static __forceinline__ void place(int t, int nt, int &cell, int &tt)
+    {
+        if (WAVE) {
+            const int lane = t & 63, c = lane / NF;
+            cell = c < CPW ? (t >> 6) * CPW + c : cells(nt);
+            tt = lane - c * NF;
+        } else {
+            cell = t / NF;
+            tt = t - cell * NF;
+        }
+    }
+};
+
 // One cell's solve in place in LDS.  sR: the cell's N^3 values (r on entry,
 // z on return), x fastest; sS: [3][N*N] per-direction eigenvector matrices
 // (sS[d][i*N + m] = S_d(i, m)); sL: [3][N] eigenvalues; sC: c0, cx, cy, cz.
 // Thread (a, b) of the cell (a, b < N) owns one pencil per sweep; every
 // thread of the workgroup calls this (barriers inside), with active false
-// for threads without a cell.  acc_rz accumulates r.z over the thread's
+// for threads without a cell; the caller's LDS writes are already visible to
+// the cell's threads.  WAVE: all threads of a cell are in one wave.  acc_rz accumulates r.z over the thread's
 // final pencil (positions i + N a + N^2 b).
-template <int N, typename T>
+template <int N, typename T, bool WAVE>
 __device__ __forceinline__ void bj_cell_solve(T *sR, const T (*sS)[N * N], const T (*sL)[N],
                                               const T *sC, int a, int b, bool active,
                                               double &acc_rz)
 {
     constexpr int NF = N * N;
+    auto sync = [] {
+        if constexpr (WAVE) lds_wave_sync();
+        else __syncthreads();
+    };
     T v[N], w[N], rp[N];
     // S_x^T along x: thread (j=a, l=b); rp keeps the residual pencil, whose
     // positions are those of the output pencil written at the end
@@ -37,12 +76,12 @@ __device__ __forceinline__ void bj_cell_solve(T *sR, const T (*sS)[N * N], const
             w[m] = s;
         }
     }
-    __syncthreads();
+    sync();
     if (active) {
 #pragma unroll
         for (int m = 0; m < N; ++m) sR[m + N * a + NF * b] = w[m];
     }
-    __syncthreads();
+    sync();
     // S_y^T along y: thread (mx=a, l=b)
     if (active) {
 #pragma unroll
@@ -55,12 +94,12 @@ __device__ __forceinline__ void bj_cell_solve(T *sR, const T (*sS)[N * N], const
             w[m] = s;
         }
     }
-    __syncthreads();
+    sync();
     if (active) {
 #pragma unroll
         for (int m = 0; m < N; ++m) sR[a + N * m + NF * b] = w[m];
     }
-    __syncthreads();
+    sync();
     // S_z^T along z, diagonal scaling, S_z along z: thread (mx=a, my=b)
     if (active) {
 #pragma unroll
@@ -82,12 +121,12 @@ __device__ __forceinline__ void bj_cell_solve(T *sR, const T (*sS)[N * N], const
             v[l] = s;
         }
     }
-    __syncthreads();
+    sync();
     if (active) {
 #pragma unroll
         for (int l = 0; l < N; ++l) sR[a + N * b + NF * l] = v[l];
     }
-    __syncthreads();
+    sync();
     // S_y along y: thread (mx=a, l=b)
     if (active) {
 #pragma unroll
@@ -100,12 +139,12 @@ __device__ __forceinline__ void bj_cell_solve(T *sR, const T (*sS)[N * N], const
             w[j] = s;
         }
     }
-    __syncthreads();
+    sync();
     if (active) {
 #pragma unroll
         for (int j = 0; j < N; ++j) sR[a + N * j + NF * b] = w[j];
     }
-    __syncthreads();
+    sync();
     // S_x along x: thread (j=a, l=b); the result goes back through LDS so
     // that the callers' stores are contiguous across threads
     if (active) {
@@ -120,12 +159,12 @@ __device__ __forceinline__ void bj_cell_solve(T *sR, const T (*sS)[N * N], const
             acc_rz += (double)rp[i] * (double)s;
         }
     }
-    __syncthreads();
+    sync();
     if (active) {
 #pragma unroll
         for (int i = 0; i < N; ++i) sR[i + N * a + NF * b] = w[i];
     }
-    __syncthreads();
+    sync();
 }
 
 }  // namespace hx

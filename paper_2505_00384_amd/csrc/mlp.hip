@@ -324,7 +324,7 @@ k_mlp_fused(int64_t n_cells, const double *__restrict__ w, double *__restrict__ 
     constexpr int NT3 = (ND + 15) / 16, PER3 = (NT3 + FW - 1) / FW;
     constexpr int SUB = NTH / FT;                         // threads per cell in the norms
     static_assert(PER * FW * 16 == HID && SUB >= 16 && (SUB & (SUB - 1)) == 0, "layout");
-    static_assert(FT * NF <= NTH && NTH >= 256, "block-Jacobi threads");
+    static_assert(!WBJ || (BjMap<N>::cells(NTH) >= FT && NTH >= 256), "block-Jacobi threads");
     constexpr int FB = WBJ ? FT : 1;
     __shared__ __align__(16) uint16_t sX[FT][LDX + 8];
     __shared__ __align__(16) uint16_t sH[FT][HID + 8];
@@ -461,10 +461,16 @@ k_mlp_fused(int64_t n_cells, const double *__restrict__ w, double *__restrict__ 
     }
     if constexpr (WBJ) {
         // block Jacobi in place: NF threads per cell
-        const int lc0 = tid / NF, lc = lc0 < FT ? lc0 : 0, tt = tid - lc0 * NF;
+        int lc0, tt;
+        BjMap<N>::place(tid, NTH, lc0, tt);
+        const int lc = lc0 < FT ? lc0 : 0;
         const bool active = lc0 < FT && c0 + lc0 < n_cells;
         double unused = 0.0;
-        bj_cell_solve<N, double>(sR[lc], sBS[lc], sBL[lc], sBC[lc], tt % N, tt / N, active, unused);
+        // (the features of other waves have read r before the solve writes)
+        __syncthreads();
+        bj_cell_solve<N, double, BjMap<N>::WAVE>(sR[lc], sBS[lc], sBL[lc], sBC[lc], tt % N, tt / N, active,
+                                                 unused);
+        if constexpr (BjMap<N>::WAVE) __syncthreads();
     } else {
         // BJ(r) from z (loaded above), once the features have read r
         __syncthreads();
