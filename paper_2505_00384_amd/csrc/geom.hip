@@ -1207,11 +1207,16 @@ namespace {
 // the merged cell and face data of the operator at the nq-point rule, the
 // same quantities as k_cell_geofac / k_set_cell and k_face_geofac /
 // k_set_face, with alpha and beta interpolated from the nodes to the points.
-// Cell point index qx + nq (qy + nq qz); face point a + nq b (a along t1).
+// Cell point index qx + nq (qy + nq qz); face point b + nq a (a along t1).
+// An affine cell takes alpha w detJ and beta w detJ in the first two of its
+// seven fields, and a face between two affine cells beta- w, beta+ w in its
+// first two and the constants v- (3), v+ (3), sigma ds0 / 2 (ds = w ds0, v = ds0
+// J^-1 n) at the start of the third.
 // -------------------------------------------------------------------------
 __global__ void k_q_cell(const double *__restrict__ nodes, int ng, int n, int64_t n_cells,
                          const RefTabQ *__restrict__ Q, const double *__restrict__ alpha,
-                         const double *__restrict__ beta, double *qcell)
+                         const double *__restrict__ beta, const uint8_t *__restrict__ ctype,
+                         double *qcell)
 {
     const int nq = Q->nq, nq3 = nq * nq * nq, nd = n * n * n;
     const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -1238,6 +1243,10 @@ __global__ void k_q_cell(const double *__restrict__ nodes, int ng, int n, int64_
         }
     double *dst = qcell + c * 7 * nq3 + q;
     dst[0] = aq * w;
+    if (ctype[c]) {
+        dst[nq3] = bq * w;
+        return;
+    }
     const int pa[6] = {0, 0, 0, 1, 1, 2}, pb[6] = {0, 1, 2, 1, 2, 2};
     for (int s = 0; s < 6; ++s) {
         const int A = pa[s], Bq = pb[s];
@@ -1249,7 +1258,7 @@ __global__ void k_q_cell(const double *__restrict__ nodes, int ng, int n, int64_
 __global__ void k_q_face(const double *__restrict__ nodes, int ng, int n, int64_t n_cells,
                          const int32_t *__restrict__ nbr, const RefTabQ *__restrict__ Q,
                          const double *__restrict__ beta, const double *__restrict__ sigma,
-                         double *qface)
+                         const uint8_t *__restrict__ ctype, double *qface)
 {
     const int nq = Q->nq, nq2 = nq * nq, nd = n * n * n;
     const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -1258,7 +1267,7 @@ __global__ void k_q_face(const double *__restrict__ nodes, int ng, int n, int64_
     const int64_t cd = t / nq2;
     const int64_t c = cd / 3;
     const int d = (int)(cd % 3);
-    const int a = pt % nq, b = pt / nq;
+    const int a = pt / nq, b = pt % nq;
     double *dst = qface + cd * 7 * nq2 + pt;
     const int32_t nb = nbr[6 * c + 2 * d + 1];
     if (nb < 0) {
@@ -1290,6 +1299,22 @@ __global__ void k_q_face(const double *__restrict__ nodes, int ng, int n, int64_
             bp += wgt * beta[(int64_t)nb * nd + layer_idx(n, d, 0, e1, e2)];
         }
     const int dir[3] = {d, t1, t2};
+    if (ctype[c] && ctype[nb]) {
+        const double wab = Q->wq[a] * Q->wq[b];
+        dst[0] = bm * wab;
+        dst[nq2] = bp * wab;
+        if (pt == 0) {
+            double *fc = dst + 2 * nq2;
+            const double ds0 = ds / wab;
+            for (int k = 0; k < 3; ++k) {
+                const int r = dir[k];
+                fc[k] = ds0 * (Jmi[r][0] * nv[0] + Jmi[r][1] * nv[1] + Jmi[r][2] * nv[2]);
+                fc[3 + k] = ds0 * (Jpi[r][0] * nv[0] + Jpi[r][1] * nv[1] + Jpi[r][2] * nv[2]);
+            }
+            fc[6] = sigma[3 * c + d] * 0.5 * ds0;
+        }
+        return;
+    }
     for (int k = 0; k < 3; ++k) {
         const int r = dir[k];
         dst[k * nq2] = bm * ds * (Jmi[r][0] * nv[0] + Jmi[r][1] * nv[1] + Jmi[r][2] * nv[2]);
@@ -1305,12 +1330,12 @@ hipError_t launch_q_setup(hx_ctx *c, const double *alpha, const double *beta)
     const int nq = c->nq;
     const int64_t nt = c->n_cells * nq * nq * nq;
     hipLaunchKernelGGL(k_q_cell, dim3(nblk(nt, 128)), dim3(128), 0, c->stream, c->nodes, c->g + 1, c->n,
-                       c->n_cells, c->refq, alpha, beta, c->qcell);
+                       c->n_cells, c->refq, alpha, beta, c->ctype, c->qcell);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int64_t nf = 3 * c->n_cells * nq * nq;
     hipLaunchKernelGGL(k_q_face, dim3(nblk(nf, 128)), dim3(128), 0, c->stream, c->nodes, c->g + 1, c->n,
-                       c->n_cells, c->nbr, c->refq, beta, c->sigma, c->qface);
+                       c->n_cells, c->nbr, c->refq, beta, c->sigma, c->ctype, c->qface);
     return hipGetLastError();
 }
 

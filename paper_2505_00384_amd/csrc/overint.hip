@@ -5,16 +5,28 @@
 // interpolation B (nq x n) and its derivative BD are rectangular now, so the
 // sweeps change pencil lengths (n nodes <-> nq points).
 //
-// One cell per block.  Cell part: x sweep by lanes (j, l) (n^2), y sweep by
-// lanes (qx, l) (nq n), z sweep, quadrature-point operation and transposed z
-// sweep by lanes (qx, qy) (nq^2), transposed y and x sweeps back; fields in
-// LDS between the sweeps.  Face part, face by face: lanes (e1, e2) form the
-// own and the neighbour's face layer and normal-derivative column (the
-// derivative of the GLL basis at the face end), lanes (a, b) evaluate value,
-// tangential and normal derivatives at the nq^2 face points and the flux
-// terms, lanes (e1, e2) contract them back to layer weights, and the pencil
-// owners add them (layer weights to the face layer, derivative weights
-// along the normal lines).  One thread writes each output.
+// A workgroup serves one cell: wave 0 the cell integrals, one further wave
+// (two for N > 5) the face terms, at the same time; they meet at one barrier,
+// after which wave 0 adds the faces and writes its output pencils.  Inside a
+// wave only the order of its LDS accesses matters, so there are no other
+// barriers.
+//  * cell: x sweep by lanes (j, l), y sweep by items (qx, l), z sweep,
+//    quadrature-point operation and transposed z sweep by items (qx, qy), two
+//    rounds of lanes for N = 5, then back; fields in LDS between the sweeps;
+//    the point data of the next plane always in flight.
+//  * faces: column lanes (f, p) hold a face's layer values and normal
+//    derivatives, interpolate them along the second tangential direction
+//    (step 1); row lanes (f, q2) along the first one, where they form the flux
+//    terms point by point and sweep back (steps 2, 3); the column lanes finish
+//    (step 4).  The neighbour's side goes first and leaves its flux and value
+//    in registers.
+// The 1-D tables are compile-time scalars.  What bounds it: the quadrature
+// data stream (452 bytes per dof at degree 4, 140 on affine cells, which read
+// two values per point and their constants) and the LDS traffic between the
+// sweeps.  The former form (two waves per cell in lock step, 23 barriers, face
+// contractions with both operands and the tables from LDS) was bound by LDS:
+// 0.500 ms at 64x16x32 cells, degree 4, and no faster with the compressed
+// data of the affine cells (0.508); this one 0.381 ms.
 #include "common.hpp"
 
 namespace hx {
@@ -25,133 +37,127 @@ namespace {
 template <int N> struct KBQ;
 template <int N> struct KBDQ;
 #include "optables_q.inc"
+// and the (k+1)-point tables, of which the end derivatives KDL are used
+template <int N> struct KB;
+template <int N> struct KBD;
+template <int N> struct KDL;
+#include "optables.inc"
 
 template <int N>
 __device__ __forceinline__ constexpr double tq(int q, int i) { return KBQ<N>::d[q * N + i]; }
 template <int N>
 __device__ __forceinline__ constexpr double tdq(int q, int i) { return KBDQ<N>::d[q * N + i]; }
 
-template <int N, int Q>
+template <int N>
 struct QCfg {
-    static constexpr int ND = N * N * N, NF = N * N, Q2 = Q * Q, Q3 = Q * Q * Q;
+    static constexpr int Q = 2 * N - 1, ND = N * N * N, NF = N * N, Q2 = Q * Q, Q3 = Q * Q * Q;
     static constexpr int QN = Q * N, QNN = Q * N * N, QQN = Q * Q * N;
-    static constexpr int NT = ((Q2 > QN ? Q2 : QN) + 63) / 64 * 64;
+    static constexpr int FW = 6 * Q <= 64 ? 1 : 2;   // face waves
+    static constexpr int FPW = 6 / FW;               // faces per face wave
+    static constexpr int NT = 64 * (1 + FW);
+    static_assert(NF <= 64 && FPW * Q <= 64, "one row lane per face row");
 };
 
-// threads per block for N nodes and 2N-1 points per direction
-template <int N>
-constexpr int q_nt() { return QCfg<N, 2 * N - 1>::NT; }
-
-template <int N>
-__device__ __forceinline__ int qlay(int d, int m, int e1, int e2)
+// order of LDS accesses between the lanes of one wave
+__device__ __forceinline__ void wave_sync()
 {
-    const int s1 = d == 0 ? N : 1, s2 = d == 2 ? N : N * N, sd = d == 0 ? 1 : (d == 1 ? N : N * N);
-    return m * sd + e1 * s1 + e2 * s2;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int N>
-__global__ void __launch_bounds__(q_nt<N>(), 4)
-k_apply_q(const double *__restrict__ x, double *__restrict__ y, const double *__restrict__ cell,
-          const double *__restrict__ face, const int32_t *__restrict__ nbr,
-          const RefTabQ *__restrict__ TQ, const RefTab64 *__restrict__ T, int n_cells)
+// y = B u (W = 0) or BD u (W = 1), n -> nq
+template <int N, int W>
+__device__ __forceinline__ void up(const double (&u)[N], double (&y)[2 * N - 1])
 {
-    constexpr int Q = 2 * N - 1;
-    using C = QCfg<N, Q>;
-    constexpr int ND = C::ND, NF = C::NF, Q2 = C::Q2, Q3 = C::Q3, QNN = C::QNN, QQN = C::QQN;
-    __shared__ double sB[Q * N], sD[Q * N], sDL[2][N];
-    __shared__ double sX[ND];
-    __shared__ double FA[6][2][NF];
-    // one pool for the sweep buffers of the cell part (U0, U1, V0, V1, V2)
-    // and, once those are free, the face stage: U0 keeps the output pencils
-    // and the face arrays overlay U1 .. V2
-    // the face stage handles the two faces of one direction together: per
-    // face 4 NF (layers), 6 QN (along e1), 4 Q2 (face points), 3 QN (back)
-    constexpr int FACE1 = 4 * NF + 9 * C::QN + 4 * Q2;
-    constexpr int CELLW = QNN + 3 * QQN, FACEW = 2 * FACE1;
-    __shared__ double pool[QNN + (CELLW > FACEW ? CELLW : FACEW)];
-    double *const U0 = pool, *const U1 = pool + QNN, *const V0 = U1 + QNN, *const V1 = V0 + QQN,
-                 *const V2 = V1 + QQN;
-    const int t = threadIdx.x;
-    const int64_t cid = blockIdx.x;
-    for (int e = t; e < Q * N; e += blockDim.x) {
-        sB[e] = TQ->B[e];
-        sD[e] = TQ->BD[e];
-    }
-    for (int e = t; e < 2 * N; e += blockDim.x) sDL[e / N][e % N] = T->DL[e / N][e % N];
-    for (int e = t; e < ND; e += blockDim.x) sX[e] = x[cid * ND + e];
-    __syncthreads();
-
-    // x sweep: lane (j, l): u and du/dxi at (qx, j, l), layout qx + Q (j + N l)
-    if (t < NF) {
-        const int j = t % N, l = t / N;
-        double v[N];
 #pragma unroll
-        for (int i = 0; i < N; ++i) v[i] = sX[i + N * j + NF * l];
+    for (int q = 0; q < 2 * N - 1; ++q) {
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < N; ++i) s += (W ? tdq<N>(q, i) : tq<N>(q, i)) * u[i];
+        y[q] = s;
+    }
+}
+
+// Cell integrals by one wave; U0, U1 (Q N^2 each) and V0, V1, V2 (Q^2 N each)
+// in LDS, U overlaying V0; the output pencil of lane (j, l) in Y.
+template <int N, bool AFF>
+__device__ __forceinline__ void q_cell(const double *__restrict__ x, const double *__restrict__ cell,
+                                       const double *__restrict__ kk, int64_t cid, int lane,
+                                       double *__restrict__ U, double *__restrict__ V, double (&Y)[N])
+{
+    using C = QCfg<N>;
+    constexpr int Q = C::Q, ND = C::ND, NF = C::NF, Q2 = C::Q2, Q3 = C::Q3, QN = C::QN, QNN = C::QNN,
+                  QQN = C::QQN, NC = AFF ? 2 : 7;
+    const double *cp = cell + cid * 7 * Q3;
+    double *U1 = U + QNN, *V1 = V + QQN, *V2 = V1 + QQN;
+    double kc[6];
+    if constexpr (AFF)
+#pragma unroll
+        for (int k = 0; k < 6; ++k) kc[k] = kk[8 * cid + k];
+    // the first plane's point data, in flight during the x and y sweeps
+    double nx[NC];
+#pragma unroll
+    for (int k = 0; k < NC; ++k) nx[k] = cp[(lane < Q2 ? lane : 0) + k * Q3];
+    // x sweep: lane (j, l): u and du/dxi at (qx, j, l), layout qx + Q (j + N l)
+    if (lane < NF) {
+        double v[N], s0[Q], s1[Q];
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = x[cid * ND + N * lane + i];
+        up<N, 0>(v, s0);
+        up<N, 1>(v, s1);
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
-            double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-            for (int i = 0; i < N; ++i) {
-                s0 += tq<N>(q, i) * v[i];
-                s1 += tdq<N>(q, i) * v[i];
-            }
-            U0[q + Q * (j + N * l)] = s0;
-            U1[q + Q * (j + N * l)] = s1;
+            U[q + Q * lane] = s0[q];
+            U1[q + Q * lane] = s1[q];
         }
     }
-    __syncthreads();
-    // y sweep: lane (qx, l): u, d/deta (from u) and d/dxi (from U1) at
+    wave_sync();
+    // y sweep: item (qx, l): u, d/deta (from u) and d/dxi (from U1) at
     // (qx, qy, l), layout qx + Q (qy + Q l)
-    if (t < C::QN) {
-        const int qx = t % Q, l = t / Q;
-        double v0[N], v1[N];
+    for (int it = lane; it < QN; it += 64) {
+        const int qx = it % Q, l = it / Q;
+        double v0[N], v1[N], s0[Q], s1[Q], s2[Q];
 #pragma unroll
         for (int j = 0; j < N; ++j) {
-            v0[j] = U0[qx + Q * (j + N * l)];
+            v0[j] = U[qx + Q * (j + N * l)];
             v1[j] = U1[qx + Q * (j + N * l)];
         }
+        up<N, 0>(v0, s0);
+        up<N, 1>(v0, s1);
+        up<N, 0>(v1, s2);
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
-            double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-#pragma unroll
-            for (int j = 0; j < N; ++j) {
-                s0 += tq<N>(q, j) * v0[j];
-                s1 += tdq<N>(q, j) * v0[j];
-                s2 += tq<N>(q, j) * v1[j];
-            }
-            V0[qx + Q * (q + Q * l)] = s0;
-            V1[qx + Q * (q + Q * l)] = s1;
-            V2[qx + Q * (q + Q * l)] = s2;
+            V[qx + Q * (q + Q * l)] = s0[q];
+            V1[qx + Q * (q + Q * l)] = s1[q];
+            V2[qx + Q * (q + Q * l)] = s2[q];
         }
     }
-    __syncthreads();
-    // z sweep, quadrature-point operation, transposed z sweep: lane (qx, qy)
-    double w0[N], w1[N], w2[N];
-    if (t < Q2) {
-        const int qx = t % Q, qy = t / Q;
-        double a0[N], a1[N], a2[N];
+    wave_sync();
+    // z sweep, quadrature-point operation, transposed z sweep: item (qx, qy),
+    // in place (an item reads and writes its own columns only)
+    for (int it = lane; it < Q2; it += 64) {
+        double a0[N], a1[N], a2[N], w0[N], w1[N], w2[N];
 #pragma unroll
         for (int l = 0; l < N; ++l) {
-            a0[l] = V0[qx + Q * (qy + Q * l)];
-            a1[l] = V1[qx + Q * (qy + Q * l)];
-            a2[l] = V2[qx + Q * (qy + Q * l)];
+            a0[l] = V[it + Q2 * l];
+            a1[l] = V1[it + Q2 * l];
+            a2[l] = V2[it + Q2 * l];
+            w0[l] = w1[l] = w2[l] = 0.0;
         }
-#pragma unroll
-        for (int l = 0; l < N; ++l) w0[l] = w1[l] = w2[l] = 0.0;
-        const double *cp = cell + cid * 7 * Q3 + qx + Q * qy;
-        // the point data of plane q + 1 are requested before plane q's
-        // arithmetic, so one plane's loads are always in flight
-        double nx[7];
-#pragma unroll
-        for (int k = 0; k < 7; ++k) nx[k] = cp[k * Q3];
+        // (the last plane requests the next round's first one)
+        const int nit = it + 64 < Q2 ? it + 64 : it;
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             double cd[7];
 #pragma unroll
-            for (int k = 0; k < 7; ++k) cd[k] = nx[k];
-            if (q + 1 < Q) {
+            for (int k = 0; k < NC; ++k) cd[k] = nx[k];
 #pragma unroll
-                for (int k = 0; k < 7; ++k) nx[k] = cp[Q2 * (q + 1) + k * Q3];
+            for (int k = 0; k < NC; ++k) nx[k] = cp[(q + 1 < Q ? it + Q2 * (q + 1) : nit) + k * Q3];
+            if constexpr (AFF) {
+                const double bw = cd[1];
+#pragma unroll
+                for (int k = 0; k < 6; ++k) cd[1 + k] = bw * kc[k];
             }
             double u = 0.0, dz = 0.0, dy = 0.0, dx = 0.0;
 #pragma unroll
@@ -174,27 +180,24 @@ k_apply_q(const double *__restrict__ x, double *__restrict__ y, const double *__
                 w2[l] += tq<N>(q, l) * fx;
             }
         }
-    }
-    __syncthreads();
-    if (t < Q2) {
-        const int qx = t % Q, qy = t / Q;
+#pragma unroll
         for (int l = 0; l < N; ++l) {
-            V0[qx + Q * (qy + Q * l)] = w0[l];
-            V1[qx + Q * (qy + Q * l)] = w1[l];
-            V2[qx + Q * (qy + Q * l)] = w2[l];
+            V[it + Q2 * l] = w0[l];
+            V1[it + Q2 * l] = w1[l];
+            V2[it + Q2 * l] = w2[l];
         }
     }
-    __syncthreads();
-    // transposed y sweep: lane (qx, l) -> (qx, j, l): s0 = B^T w0 + BD^T w1,
+    wave_sync();
+    // transposed y sweep: item (qx, l) -> (qx, j, l): s0 = B^T w0 + BD^T w1,
     // s1 = B^T w2
-    if (t < C::QN) {
-        const int qx = t % Q, l = t / Q;
+    for (int it = lane; it < QN; it += 64) {
+        const int qx = it % Q, l = it / Q;
         double s0[N], s1[N];
 #pragma unroll
         for (int j = 0; j < N; ++j) s0[j] = s1[j] = 0.0;
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
-            const double a0 = V0[qx + Q * (q + Q * l)], a1 = V1[qx + Q * (q + Q * l)],
+            const double a0 = V[qx + Q * (q + Q * l)], a1 = V1[qx + Q * (q + Q * l)],
                          a2 = V2[qx + Q * (q + Q * l)];
 #pragma unroll
             for (int j = 0; j < N; ++j) {
@@ -202,202 +205,311 @@ k_apply_q(const double *__restrict__ x, double *__restrict__ y, const double *__
                 s1[j] += tq<N>(q, j) * a2;
             }
         }
+#pragma unroll
         for (int j = 0; j < N; ++j) {
-            U0[qx + Q * (j + N * l)] = s0[j];
+            U[qx + Q * (j + N * l)] = s0[j];
             U1[qx + Q * (j + N * l)] = s1[j];
         }
     }
-    __syncthreads();
+    wave_sync();
     // transposed x sweep: lane (j, l) keeps its output pencil
-    double Y[N];
-    if (t < NF) {
-        const int j = t % N, l = t / N;
 #pragma unroll
-        for (int i = 0; i < N; ++i) Y[i] = 0.0;
+    for (int i = 0; i < N; ++i) Y[i] = 0.0;
+    if (lane < NF)
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
-            const double a0 = U0[q + Q * (j + N * l)], a1 = U1[q + Q * (j + N * l)];
+            const double a0 = U[q + Q * lane], a1 = U1[q + Q * lane];
 #pragma unroll
             for (int i = 0; i < N; ++i) Y[i] += tq<N>(q, i) * a0 + tdq<N>(q, i) * a1;
         }
-    }
+}
 
-    // ---------------------------------------------------------------- faces
-    // The output pencils wait in LDS (U0, free after the transposed x
-    // sweep) while the faces run, the two faces of each direction together.
-    // Per face, sum-factorised in two 1-D steps each way: items (e1, e2)
-    // form the own and the neighbour's face layer and normal-derivative
-    // column; items (a, e2) contract along e1 (value and e1-derivative of
-    // both layers, value of both derivative columns); items (a, b) contract
-    // along e2 and form the flux terms at the face points; items (e1, b) and
-    // then (e1, e2) contract back.
-    __syncthreads();
-    double *sY = U0;
-    if (t < NF) {
-        const int j = t % N, l = t / N;
+// Face terms of faces f0 .. f0 + FPW - 1 by one wave.  S: own values (N^3);
+// F: three fields of Q x N per face, [field][q2][p], layer weights and
+// normal-derivative weights in fields 0 and 1, [r][p], on return.
+template <int N>
+__device__ __forceinline__ void q_faces(const double *__restrict__ x, const double *__restrict__ face,
+                                        const int32_t *__restrict__ nbr, const uint8_t *__restrict__ ctype,
+                                        bool aff, int64_t cid, int lane, int f0, double *__restrict__ S,
+                                        double *__restrict__ F)
+{
+    using C = QCfg<N>;
+    constexpr int Q = C::Q, ND = C::ND, NF = C::NF, Q2 = C::Q2, QN = C::QN, FPW = C::FPW;
+    // column lane (f, p) and row lane (f, q2); the face data belong to the row
+    const bool cl0 = lane < FPW * N, rl0 = lane < FPW * Q;
+    const int fc = f0 + (cl0 ? lane / N : 0), p = lane % N;
+    const int fr = f0 + (rl0 ? lane / Q : 0), q2 = lane % Q;
+    const int32_t nbc = cl0 ? nbr[6 * cid + fc] : -1, nbr_ = rl0 ? nbr[6 * cid + fr] : -1;
+    const bool cl = nbc >= 0, rl = nbr_ >= 0;
+    const int dc = fc >> 1, sc = fc & 1, dr = fr >> 1, sr_ = fr & 1;
+    // strides of the normal, column and row index in a cell's numbering
+    const int sm = dc == 0 ? 1 : (dc == 1 ? N : NF), sp = dc == 0 ? N : 1, sr = dc == 2 ? N : NF;
+    double *gc = F + (cl0 ? lane / N : 0) * 3 * QN, *gr = F + (rl0 ? lane / Q : 0) * 3 * QN + q2 * N;
+    // own values to LDS, the neighbour's normal lines to registers: layer
+    // values and normal derivatives, walked from the shared face inwards (so
+    // both sides use the derivative weights of the lower end, mirrored and
+    // negated at the upper one)
+    double L[N], D[N];
+    if (cl) {
+        const int m0 = sc ? 0 : (N - 1) * sm, dm = sc ? sm : -sm;
+        const double sgn = sc ? 1.0 : -1.0;
+        const double *xn = x + (int64_t)nbc * ND + p * sp + m0;
 #pragma unroll
-        for (int i = 0; i < N; ++i) sY[i + N * j + NF * l] = Y[i];
+        for (int r = 0; r < N; ++r) {
+            double s = 0.0;
+#pragma unroll
+            for (int m = 0; m < N; ++m) s += KDL<N>::d[m] * xn[r * sr + m * dm];
+            D[r] = sgn * s;
+            L[r] = xn[r * sr];
+        }
     }
-    for (int d = 0; d < 3; ++d) {
-        const int32_t nbs[2] = {nbr[6 * cid + 2 * d], nbr[6 * cid + 2 * d + 1]};
-        // layers and normal-derivative columns of face (d, s), own and
-        // neighbour side: item (s, e1, e2)
-        for (int it = t; it < 2 * NF; it += blockDim.x) {
-            const int s = it / NF, k = it - s * NF;
-            const int32_t nb = nbs[s];
-            if (nb < 0) {
-                FA[2 * d + s][0][k] = FA[2 * d + s][1][k] = 0.0;
-                continue;
-            }
-            double *F = U1 + s * FACE1;
-            const int e1 = k % N, e2 = k / N;
-            const int mo = s ? N - 1 : 0, mn = s ? 0 : N - 1;
-            const double *xn = x + (int64_t)nb * ND;
-            double dov = 0.0, dnv = 0.0;
-            for (int m = 0; m < N; ++m) {
-                dov += sDL[s][m] * sX[qlay<N>(d, m, e1, e2)];
-                dnv += sDL[1 - s][m] * xn[qlay<N>(d, m, e1, e2)];
-            }
-            F[k] = sX[qlay<N>(d, mo, e1, e2)];
-            F[NF + k] = dov;
-            F[2 * NF + k] = xn[qlay<N>(d, mn, e1, e2)];
-            F[3 * NF + k] = dnv;
-        }
-        __syncthreads();
-        // along e1: item (s, a, e2)
-        for (int it = t; it < 2 * C::QN; it += blockDim.x) {
-            const int s = it / C::QN, k = it - s * C::QN;
-            if (nbs[s] < 0) continue;
-            const double *F = U1 + s * FACE1;
-            double *Tf = U1 + s * FACE1 + 4 * NF;
-            const int a = k % Q, e2 = k / Q;
-            double c0 = 0, c1 = 0, c2 = 0, c3 = 0, c4 = 0, c5 = 0;
 #pragma unroll
-            for (int e1 = 0; e1 < N; ++e1) {
-                const double ba = sB[a * N + e1], da = sD[a * N + e1];
-                const int kk = e1 + N * e2;
-                c0 += ba * F[kk];
-                c1 += da * F[kk];
-                c2 += ba * F[NF + kk];
-                c3 += ba * F[2 * NF + kk];
-                c4 += da * F[2 * NF + kk];
-                c5 += ba * F[3 * NF + kk];
-            }
-            Tf[0 * C::QN + k] = c0;
-            Tf[1 * C::QN + k] = c1;
-            Tf[2 * C::QN + k] = c2;
-            Tf[3 * C::QN + k] = c3;
-            Tf[4 * C::QN + k] = c4;
-            Tf[5 * C::QN + k] = c5;
-        }
-        __syncthreads();
-        // along e2 and the flux terms: item (s, a, b)
-        for (int it = t; it < 2 * Q2; it += blockDim.x) {
-            const int s = it / Q2, k = it - s * Q2;
-            const int32_t nb = nbs[s];
-            if (nb < 0) continue;
-            const double *Tf = U1 + s * FACE1 + 4 * NF;
-            double *P = U1 + s * FACE1 + 4 * NF + 6 * C::QN;
-            const int a = k % Q, b = k / Q;
-            double vo = 0, t1o = 0, t2o = 0, dno = 0, vn = 0, t1n = 0, t2n = 0, dnn = 0;
+    for (int k = 0; k < (ND + 63) / 64; ++k)
+        if (lane + 64 * k < ND) S[lane + 64 * k] = x[cid * ND + lane + 64 * k];
+    // face data of the row: g of the neighbour's side (the plus side's if the
+    // own cell is the minus cell), g of the own side, penalty factor; on a
+    // face between two affine cells beta w of both sides and constants
+    const bool cmp = aff && rl && ctype[nbr_];
+    const int64_t fid = sr_ ? cid : (int64_t)nbr_;
+    const double *fd = face + ((rl ? fid : 0) * 3 + dr) * 7 * Q2 + q2;
+    const double *kf = fd - q2 + 2 * Q2;
+    const int gn = sr_ ? 3 : 0, go = sr_ ? 0 : 3;
+    const double *fn = fd + (cmp ? (sr_ ? 1 : 0) : gn) * Q2, *fo = fd + (cmp ? (sr_ ? 0 : 1) : go) * Q2;
+    double gv[3][Q];
+    if (rl) {
 #pragma unroll
-            for (int e2 = 0; e2 < N; ++e2) {
-                const double bb = sB[b * N + e2], db = sD[b * N + e2];
-                const int kk = a + Q * e2;
-                vo += bb * Tf[0 * C::QN + kk];
-                t1o += bb * Tf[1 * C::QN + kk];
-                t2o += db * Tf[0 * C::QN + kk];
-                dno += bb * Tf[2 * C::QN + kk];
-                vn += bb * Tf[3 * C::QN + kk];
-                t1n += bb * Tf[4 * C::QN + kk];
-                t2n += db * Tf[3 * C::QN + kk];
-                dnn += bb * Tf[5 * C::QN + kk];
+        for (int q1 = 0; q1 < Q; ++q1) {
+            gv[0][q1] = fn[Q * q1];
+            if (!cmp) {
+                gv[1][q1] = fn[Q * q1 + Q2];
+                gv[2][q1] = fn[Q * q1 + 2 * Q2];
             }
-            const int64_t fid = s ? cid : (int64_t)nb;
-            const double *fd = face + (fid * 3 + d) * 7 * Q2 + k;
-            const int go = s ? 0 : 3, gn = s ? 3 : 0;
-            const double flux = fd[go * Q2] * dno + fd[(go + 1) * Q2] * t1o + fd[(go + 2) * Q2] * t2o +
-                                fd[gn * Q2] * dnn + fd[(gn + 1) * Q2] * t1n + fd[(gn + 2) * Q2] * t2n;
-            const double jump = s ? (vo - vn) : (vn - vo);
-            const double sg = s ? 1.0 : -1.0;
-            const double hj = -0.5 * jump;
-            P[k] = sg * (-0.5 * flux + fd[6 * Q2] * jump);            // value weight
-            P[Q2 + k] = hj * fd[(go + 1) * Q2];                       // e1-derivative weight
-            P[2 * Q2 + k] = hj * fd[(go + 2) * Q2];                   // e2-derivative weight
-            P[3 * Q2 + k] = hj * fd[go * Q2];                         // normal-derivative weight
         }
-        __syncthreads();
-        // back along a: item (s, e1, b)
-        for (int it = t; it < 2 * C::QN; it += blockDim.x) {
-            const int s = it / C::QN, k = it - s * C::QN;
-            if (nbs[s] < 0) continue;
-            const double *P = U1 + s * FACE1 + 4 * NF + 6 * C::QN;
-            double *Gf = U1 + s * FACE1 + 4 * NF + 6 * C::QN + 4 * Q2;
-            const int e1 = k % N, b = k / N;
-            double g = 0, h = 0, kk = 0;
-#pragma unroll
-            for (int a = 0; a < Q; ++a) {
-                const double ba = sB[a * N + e1], da = sD[a * N + e1];
-                const int pk = a + Q * b;
-                g += ba * P[pk] + da * P[Q2 + pk];
-                h += ba * P[2 * Q2 + pk];
-                kk += ba * P[3 * Q2 + pk];
-            }
-            Gf[0 * C::QN + k] = g;
-            Gf[1 * C::QN + k] = h;
-            Gf[2 * C::QN + k] = kk;
-        }
-        __syncthreads();
-        // back along b: item (s, e1, e2)
-        for (int it = t; it < 2 * NF; it += blockDim.x) {
-            const int s = it / NF, k = it - s * NF;
-            if (nbs[s] < 0) continue;
-            const double *Gf = U1 + s * FACE1 + 4 * NF + 6 * C::QN + 4 * Q2;
-            const int e1 = k % N, e2 = k / N;
-            double f0 = 0.0, f1 = 0.0;
-#pragma unroll
-            for (int b = 0; b < Q; ++b) {
-                const double bb = sB[b * N + e2], db = sD[b * N + e2];
-                const int gk = e1 + N * b;
-                f0 += bb * Gf[0 * C::QN + gk] + db * Gf[1 * C::QN + gk];
-                f1 += bb * Gf[2 * C::QN + gk];
-            }
-            FA[2 * d + s][0][k] = f0;
-            FA[2 * d + s][1][k] = f1;
-        }
-        __syncthreads();
     }
+    auto step1 = [&](const double (&l)[N], const double (&d)[N]) {
+        double g[Q];
+        up<N, 0>(l, g);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) gc[q * N + p] = g[q];
+        up<N, 1>(l, g);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) gc[QN + q * N + p] = g[q];
+        up<N, 0>(d, g);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) gc[2 * QN + q * N + p] = g[q];
+    };
+    if (cl) step1(L, D);
+    wave_sync();
+    // step 2, neighbour's side: flux and value at (q1, q2)
+    double fnb[Q], vnb[Q];
+    if (rl) {
+        double h0[N], h1[N], h2[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            h0[i] = gr[i];
+            h1[i] = gr[QN + i];
+            h2[i] = gr[2 * QN + i];
+        }
+        double v0 = 0.0, v1 = 0.0, v2 = 0.0;
+        if (cmp) {
+            v0 = kf[gn];
+            v1 = kf[gn + 1];
+            v2 = kf[gn + 2];
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            double v = 0.0, t1 = 0.0, t2 = 0.0, dn = 0.0;
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                v += tq<N>(q, i) * h0[i];
+                t1 += tdq<N>(q, i) * h0[i];
+                t2 += tq<N>(q, i) * h1[i];
+                dn += tq<N>(q, i) * h2[i];
+            }
+            vnb[q] = v;
+            if (cmp) {
+                fnb[q] = gv[0][q] * (v0 * dn + v1 * t1 + v2 * t2);
+                vnb[q] = v;
+                gv[1][q] = gv[0][q];   // beta w of the neighbour's side, for the penalty
+            } else {
+                fnb[q] = gv[0][q] * dn + gv[1][q] * t1 + gv[2][q] * t2;
+            }
+        }
+    }
+    wave_sync();
+    // step 1, own side
+    if (cl) {
+        const int m0 = sc ? (N - 1) * sm : 0, dm = sc ? -sm : sm;
+        const double sgn = sc ? -1.0 : 1.0;
+        const double *uo = S + p * sp + m0;
+#pragma unroll
+        for (int r = 0; r < N; ++r) {
+            double s = 0.0;
+#pragma unroll
+            for (int m = 0; m < N; ++m) s += KDL<N>::d[m] * uo[r * sr + m * dm];
+            D[r] = sgn * s;
+            L[r] = uo[r * sr];
+        }
+        step1(L, D);
+    }
+    wave_sync();
+    // steps 2 and 3, own side: flux terms point by point and the transposed
+    // sweep along the first direction, written over the row read; the next
+    // point's data always in flight
+    if (rl) {
+        double h0[N], h1[N], h2[N], A0[N], A1[N], A2[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            h0[i] = gr[i];
+            h1[i] = gr[QN + i];
+            h2[i] = gr[2 * QN + i];
+            A0[i] = A1[i] = A2[i] = 0.0;
+        }
+        double w0 = 0.0, w1 = 0.0, w2 = 0.0, sd = 0.0;
+        if (cmp) {
+            w0 = kf[go];
+            w1 = kf[go + 1];
+            w2 = kf[go + 2];
+            sd = kf[6];
+        }
+        const double sg = sr_ ? 1.0 : -1.0;
+        double nx[4];
+        auto request = [&](int q) {
+            nx[0] = fo[Q * q];
+            if (!cmp) {
+                nx[1] = fo[Q * q + Q2];
+                nx[2] = fo[Q * q + 2 * Q2];
+                nx[3] = fd[Q * q + 6 * Q2];
+            }
+        };
+        request(0);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            double g0 = nx[0], g1 = nx[1], g2 = nx[2], pen = nx[3];
+            if (q + 1 < Q) request(q + 1);
+            if (cmp) {
+                const double bo = g0;
+                g0 = bo * w0;
+                g1 = bo * w1;
+                g2 = bo * w2;
+                pen = sd * (bo + gv[1][q]);
+            }
+            double v = 0.0, t1 = 0.0, t2 = 0.0, dn = 0.0;
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                v += tq<N>(q, i) * h0[i];
+                t1 += tdq<N>(q, i) * h0[i];
+                t2 += tq<N>(q, i) * h1[i];
+                dn += tq<N>(q, i) * h2[i];
+            }
+            const double flux = g0 * dn + g1 * t1 + g2 * t2 + fnb[q];
+            const double jump = sr_ ? (v - vnb[q]) : (vnb[q] - v);
+            const double cv = sg * (-0.5 * flux + pen * jump), hj = -0.5 * jump;
+            const double ct1 = hj * g1, ct2 = hj * g2, cn = hj * g0;
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                A0[i] += tq<N>(q, i) * cv + tdq<N>(q, i) * ct1;
+                A1[i] += tq<N>(q, i) * ct2;
+                A2[i] += tq<N>(q, i) * cn;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            gr[i] = A0[i];
+            gr[QN + i] = A1[i];
+            gr[2 * QN + i] = A2[i];
+        }
+    }
+    wave_sync();
+    // step 4, column lanes: transposed sweep along the second direction, in
+    // place (a column lane reads and writes its own column only)
+    if (cl0) {
+        double o0[N], o1[N];
+#pragma unroll
+        for (int r = 0; r < N; ++r) o0[r] = o1[r] = 0.0;
+        if (cl)
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const double b0 = gc[q * N + p], b1 = gc[QN + q * N + p], b2 = gc[2 * QN + q * N + p];
+#pragma unroll
+                for (int r = 0; r < N; ++r) {
+                    o0[r] += tq<N>(q, r) * b0 + tdq<N>(q, r) * b1;
+                    o1[r] += tq<N>(q, r) * b2;
+                }
+            }
+#pragma unroll
+        for (int r = 0; r < N; ++r) {
+            gc[r * N + p] = o0[r];
+            gc[QN + r * N + p] = o1[r];
+        }
+    }
+}
+
+template <int N>
+__global__ void __launch_bounds__(QCfg<N>::NT, N <= 4 ? 4 : (N <= 5 ? 3 : (N <= 7 ? 2 : 1)))
+k_apply_q(const double *__restrict__ x, double *__restrict__ y, const double *__restrict__ cell,
+          const double *__restrict__ face, const int32_t *__restrict__ nbr,
+          const uint8_t *__restrict__ ctype, const double *__restrict__ kk, int nwg)
+{
+    using C = QCfg<N>;
+    constexpr int ND = C::ND, NF = C::NF, QN = C::QN, QNN = C::QNN, QQN = C::QQN, FPW = C::FPW;
+    __shared__ double sU[2 * QNN], sV[3 * QQN], sX[C::FW][ND], sF[6 * 3 * QN];
+    // contiguous ranges of the cells per XCD
+    const int bid = blockIdx.x;
+    const int q8 = nwg / NXCD, r8 = nwg % NXCD, xcd = bid % NXCD;
+    const int64_t cid = xcd * q8 + (xcd < r8 ? xcd : r8) + bid / NXCD;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    // affine cell: the same for the whole workgroup, so branches on it are
+    // uniform
+    const bool aff = __builtin_amdgcn_readfirstlane(ctype[cid]);
+    if (wave > 0) {
+        q_faces<N>(x, face, nbr, ctype, aff, cid, lane, (wave - 1) * FPW, sX[wave - 1],
+                   sF + (wave - 1) * FPW * 3 * QN);
+        __syncthreads();
+        return;
+    }
+    double Y[N];
+    if (aff) q_cell<N, true>(x, cell, kk, cid, lane, sU, sV, Y);
+    else q_cell<N, false>(x, cell, kk, cid, lane, sU, sV, Y);
     __syncthreads();
     // pencil owners (j, l) add the six faces
-    if (t < NF) {
-        const int j = t % N, l = t / N;
-        double Yp[N];
+    if (lane >= NF) return;
+    const int j = lane % N, l = lane / N;
+    auto dl = [&](int s, int k) {   // derivative weight of a lane-dependent node
+        double v = 0.0;
 #pragma unroll
-        for (int i = 0; i < N; ++i) Yp[i] = sY[i + N * j + NF * l];
-        for (int s = 0; s < 2; ++s) {
-            const int layer = s ? N - 1 : 0;
-            // x faces: normal coordinate i, (e1, e2) = (j, l)
-            {
-                const double f0 = FA[s][0][j + N * l], f1 = FA[s][1][j + N * l];
-                for (int i = 0; i < N; ++i) Yp[i] += sDL[s][i] * f1 + (i == layer ? f0 : 0.0);
-            }
-            // y faces: normal coordinate j, (e1, e2) = (i, l)
-            for (int i = 0; i < N; ++i)
-                Yp[i] += sDL[s][j] * FA[2 + s][1][i + N * l] + (j == layer ? FA[2 + s][0][i + N * l] : 0.0);
-            // z faces: normal coordinate l, (e1, e2) = (i, j)
-            for (int i = 0; i < N; ++i)
-                Yp[i] += sDL[s][l] * FA[4 + s][1][i + N * j] + (l == layer ? FA[4 + s][0][i + N * j] : 0.0);
+        for (int m = 0; m < N; ++m)
+            if (m == k) v = KDL<N>::d[s * N + m];
+        return v;
+    };
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const int layer = s ? N - 1 : 0;
+        const double *F = sF + s * 3 * QN;
+        // x faces: normal coordinate i, (p, r) = (j, l)
+        {
+            const double f0 = F[j + N * l], f1 = F[QN + j + N * l];
+#pragma unroll
+            for (int i = 0; i < N; ++i) Y[i] += KDL<N>::d[s * N + i] * f1 + (i == layer ? f0 : 0.0);
         }
-        for (int i = 0; i < N; ++i) y[cid * ND + i + N * j + NF * l] = Yp[i];
+        // y faces: normal coordinate j, (p, r) = (i, l)
+        const double ey = dl(s, j), ez = dl(s, l);
+        const double *Fy = F + 6 * QN + N * l, *Fz = F + 12 * QN + N * j;
+#pragma unroll
+        for (int i = 0; i < N; ++i) Y[i] += ey * Fy[QN + i] + (j == layer ? Fy[i] : 0.0);
+        // z faces: normal coordinate l, (p, r) = (i, j)
+#pragma unroll
+        for (int i = 0; i < N; ++i) Y[i] += ez * Fz[QN + i] + (l == layer ? Fz[i] : 0.0);
     }
+#pragma unroll
+    for (int i = 0; i < N; ++i) y[cid * ND + N * lane + i] = Y[i];
 }
 
 template <int N>
 hipError_t apply_q_n(hx_ctx *c, const double *x, double *y)
 {
-    constexpr int Q = 2 * N - 1;
-    hipLaunchKernelGGL(k_apply_q<N>, dim3((unsigned)c->n_cells), dim3(QCfg<N, Q>::NT), 0,
-                       c->stream, x, y, c->qcell, c->qface, c->nbr, c->refq, c->ref, (int)c->n_cells);
+    hipLaunchKernelGGL(k_apply_q<N>, dim3((unsigned)c->n_cells), dim3(QCfg<N>::NT), 0, c->stream, x, y,
+                       c->qcell, c->qface, c->nbr, c->ctype, c->kk64, (int)c->n_cells);
     return hipGetLastError();
 }
 
