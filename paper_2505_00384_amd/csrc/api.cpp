@@ -49,7 +49,7 @@ static void free_mesh(hx_ctx *c)
                      (void **)&c->bjL64, (void **)&c->bjL32, (void **)&c->bjC64,
                      (void **)&c->bjC32, (void **)&c->coef_feat, (void **)&c->work64,
                      (void **)&c->work32, (void **)&c->psW, (void **)&c->psWC, (void **)&c->psMr,
-                     (void **)&c->psMd, (void **)&c->psFn, (void **)&c->psFh, (void **)&c->psWork,
+                     (void **)&c->psMd, (void **)&c->psHr, (void **)&c->psK, (void **)&c->psFn, (void **)&c->psFh, (void **)&c->psWork,
                      (void **)&c->refq, (void **)&c->qcell, (void **)&c->qface, (void **)&c->chebw,
                      (void **)&c->mg_cptr, (void **)&c->mg_clist, (void **)&c->mg_child8, (void **)&c->mgw,
                      (void **)&c->mgw32, (void **)&c->chebw32, (void **)&c->ctype,
@@ -552,6 +552,8 @@ hx_status hx_set_pressure_system(hx_ctx *c, const double *rho, const double *h, 
         al(&c->psWC, (size_t)nc * 9 * c->nd);
         al(&c->psMr, (size_t)n);
         al(&c->psMd, (size_t)n);
+        al(&c->psHr, (size_t)n);
+        al(&c->psK, (size_t)nc * 16);
         al(&c->psFn, (size_t)nc * 18 * c->nf);
         al(&c->psFh, (size_t)nc * 6 * c->nf);
         al(&c->psWork, (size_t)7 * n);

@@ -130,6 +130,8 @@ struct hx_ctx {
     double *psWC = nullptr;       // [n_cells][9][nd]  h rho w detJ J^-1
     double *psMr = nullptr;       // [n_cells][nd]     rho w detJ (velocity mass)
     double *psMd = nullptr;       // [n_cells][nd]     w detJ / (gamma - 1) (internal-energy mass)
+    double *psHr = nullptr;       // [n_cells][nd]     h rho at the Gauss points
+    double *psK = nullptr;        // [n_cells][16]     detJ J^-1 (9), detJ / (gamma - 1) of affine cells
     double *psFn = nullptr;       // [n_cells][6][3][nf] outward ds n on the own faces
     double *psFh = nullptr;       // [n_cells][6][nf]  h rho on the own faces
     double *psWork = nullptr;     // [7][n_dofs]       velocity temporaries and C A^-1 B x

@@ -1108,14 +1108,16 @@ namespace {
 // C U + D P = G).  At cell Gauss point q of cell c:
 //   W[c][3d+e][q]  = w detJ (J^-1)_{de}   (so that (grad phi)_e = sum_d W ... / (w detJ))
 //   WC[c][3d+e][q] = hr_q W[c][3d+e][q]   (hr = h rho formed at the nodes, interpolated)
-//   mr[c][q] = rho_q w detJ,  md[c][q] = w detJ / (gamma - 1);
+//   mr[c][q] = rho_q w detJ,  md[c][q] = w detJ / (gamma - 1),  hr[c][q] = hr_q;
+//   kc[c][3d+e] = detJ (J^-1)_{de}, kc[c][9] = detJ / (gamma - 1) at the first
+//   point (the cell's constants when it is affine; rows of 16);
 // at Gauss point (a, b) of the cell's own face f = 2d + s:
 //   fn[c][f][e][a + N b] = ds n_e (outward),  fh[c][f][a + N b] = hr.
 // -------------------------------------------------------------------------
 __global__ void k_press_cell(const double *__restrict__ nodes, int ng, int n, int64_t n_cells,
                              const RefTab64 *__restrict__ T, const double *__restrict__ rho,
                              const double *__restrict__ h, double inv_gm1, double *W, double *WC,
-                             double *mr, double *md)
+                             double *mr, double *md, double *hr, double *kc)
 {
     const int nd = n * n * n;
     const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -1148,6 +1150,12 @@ __global__ void k_press_cell(const double *__restrict__ nodes, int ng, int n, in
         }
     mr[c * nd + q] = rq * w;
     md[c * nd + q] = w * inv_gm1;
+    hr[c * nd + q] = hq;
+    if (q == 0) {
+        for (int d = 0; d < 3; ++d)
+            for (int e = 0; e < 3; ++e) kc[c * 16 + 3 * d + e] = det * Ji[d][e];
+        kc[c * 16 + 9] = det * inv_gm1;
+    }
 }
 
 __global__ void k_press_face(const double *__restrict__ nodes, int ng, int n, int64_t n_cells,
@@ -1188,7 +1196,7 @@ hipError_t launch_press_setup(hx_ctx *c, const double *rho, const double *h, dou
     const int64_t nt = c->n_cells * c->nd;
     hipLaunchKernelGGL(k_press_cell, dim3(nblk(nt, 128)), dim3(128), 0, c->stream, c->nodes, c->g + 1,
                        c->n, c->n_cells, c->ref, rho, h, 1.0 / (gamma - 1.0), c->psW, c->psWC,
-                       c->psMr, c->psMd);
+                       c->psMr, c->psMd, c->psHr, c->psK);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int64_t nf = c->n_cells * 6 * c->nf;

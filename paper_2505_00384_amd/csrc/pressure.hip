@@ -57,6 +57,24 @@ constexpr int GRAD_T = 64, DIV_T = 128;
 template <int N> constexpr int grad_nt() { return PCfg<N, GRAD_T>::NT; }
 template <int N> constexpr int div_nt() { return PCfg<N, DIV_T>::NT; }
 
+// lanes per cell of the operator's traversal records (op_cells_per_wave)
+constexpr int op_lanes(int n)
+{
+    const int need = n * n > 6 * n ? n * n : 6 * n;
+    int p = 1;
+    while (p < need) p *= 2;
+    return p < 64 ? p : 64;
+}
+
+// order of LDS accesses between the lanes of one wave, whose LDS operations
+// execute in order: only the compiler has to keep them so
+__device__ __forceinline__ void press_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // cell-local index of face-layer node (e1, e2) at normal coordinate m of
 // direction d; e1, e2 run along the tangential directions t1 < t2
 template <int N>
@@ -254,165 +272,6 @@ __device__ __forceinline__ void grad_t(double *F0, double *F1, double *F2, bool 
     __syncthreads();
 }
 
-// M^{-1} y for three fields at once, M = B3^T diag(m) B3 the cell mass block
-// with Gauss-point weights m (m[a + N b + N^2 q] for the lane's z pencil):
-// y holds the lane's x pencils (lane (a, b) = (j, l)) on entry and on exit;
-// F[0..2] are scratch fields
-template <int N>
-__device__ __forceinline__ void mass_inv3(double *F0, double *F1, double *F2, bool act, int a, int b,
-                                          const double *m, double (&y)[3][N])
-{
-    constexpr int NF = N * N;
-    double *F[3] = {F0, F1, F2};
-    // B^-T along x, in registers
-    if (act)
-#pragma unroll
-        for (int e = 0; e < 3; ++e)
-#pragma unroll
-            for (int q = 0; q < N; ++q) {
-                double s = 0.0;
-#pragma unroll
-                for (int i = 0; i < N; ++i) s += tBi<N>(i, q) * y[e][i];
-                F[e][q + N * a + NF * b] = s;
-            }
-    __syncthreads();
-    // B^-T along y: lane (qx=a, l=b)
-    double w[3][N];
-    if (act)
-#pragma unroll
-        for (int e = 0; e < 3; ++e) {
-            double v[N];
-#pragma unroll
-            for (int j = 0; j < N; ++j) v[j] = F[e][a + N * j + NF * b];
-#pragma unroll
-            for (int q = 0; q < N; ++q) {
-                double s = 0.0;
-#pragma unroll
-                for (int j = 0; j < N; ++j) s += tBi<N>(j, q) * v[j];
-                w[e][q] = s;
-            }
-        }
-    __syncthreads();
-    if (act)
-#pragma unroll
-        for (int e = 0; e < 3; ++e)
-#pragma unroll
-            for (int q = 0; q < N; ++q) F[e][a + N * q + NF * b] = w[e][q];
-    __syncthreads();
-    // B^-T along z, 1/m, B^-1 along z: lane (qx=a, qy=b)
-    if (act) {
-        double mi[N];
-#pragma unroll
-        for (int q = 0; q < N; ++q) mi[q] = 1.0 / m[NF * q];
-#pragma unroll
-        for (int e = 0; e < 3; ++e) {
-            double v[N], t[N];
-#pragma unroll
-            for (int l = 0; l < N; ++l) v[l] = F[e][a + N * b + NF * l];
-#pragma unroll
-            for (int q = 0; q < N; ++q) {
-                double s = 0.0;
-#pragma unroll
-                for (int l = 0; l < N; ++l) s += tBi<N>(l, q) * v[l];
-                t[q] = s * mi[q];
-            }
-#pragma unroll
-            for (int l = 0; l < N; ++l) {
-                double s = 0.0;
-#pragma unroll
-                for (int q = 0; q < N; ++q) s += tBi<N>(l, q) * t[q];
-                w[e][l] = s;
-            }
-        }
-    }
-    __syncthreads();
-    if (act)
-#pragma unroll
-        for (int e = 0; e < 3; ++e)
-#pragma unroll
-            for (int l = 0; l < N; ++l) F[e][a + N * b + NF * l] = w[e][l];
-    __syncthreads();
-    // B^-1 along y: lane (qx=a, l=b)
-    if (act)
-#pragma unroll
-        for (int e = 0; e < 3; ++e) {
-            double v[N];
-#pragma unroll
-            for (int q = 0; q < N; ++q) v[q] = F[e][a + N * q + NF * b];
-#pragma unroll
-            for (int j = 0; j < N; ++j) {
-                double s = 0.0;
-#pragma unroll
-                for (int q = 0; q < N; ++q) s += tBi<N>(j, q) * v[q];
-                w[e][j] = s;
-            }
-        }
-    __syncthreads();
-    if (act)
-#pragma unroll
-        for (int e = 0; e < 3; ++e)
-#pragma unroll
-            for (int j = 0; j < N; ++j) F[e][a + N * j + NF * b] = w[e][j];
-    __syncthreads();
-    // B^-1 along x: lane (j=a, l=b), back into y
-    if (act)
-#pragma unroll
-        for (int e = 0; e < 3; ++e) {
-            double v[N];
-#pragma unroll
-            for (int q = 0; q < N; ++q) v[q] = F[e][q + N * a + NF * b];
-#pragma unroll
-            for (int i = 0; i < N; ++i) {
-                double s = 0.0;
-#pragma unroll
-                for (int q = 0; q < N; ++q) s += tBi<N>(i, q) * v[q];
-                y[e][i] = s;
-            }
-        }
-    __syncthreads();
-}
-
-// y = B3^T t: transposed interpolation of Gauss-point values t (the lane's
-// z pencil) back to the nodes (the lane's x pencil); F a scratch field
-template <int N>
-__device__ __forceinline__ void interp_t(double *F, bool act, int a, int b, const double (&t)[N],
-                                         double (&y)[N])
-{
-    constexpr int NF = N * N;
-    if (act)
-#pragma unroll
-        for (int l = 0; l < N; ++l) {
-            double s = 0.0;
-#pragma unroll
-            for (int q = 0; q < N; ++q) s += tB<N>(q, l) * t[q];
-            F[a + N * b + NF * l] = s;
-        }
-    __syncthreads();
-    double r[N];
-    if (act)
-#pragma unroll
-        for (int j = 0; j < N; ++j) {
-            double s = 0.0;
-#pragma unroll
-            for (int q = 0; q < N; ++q) s += tB<N>(q, j) * F[a + N * q + NF * b];
-            r[j] = s;
-        }
-    __syncthreads();
-    if (act)
-#pragma unroll
-        for (int j = 0; j < N; ++j) F[a + N * j + NF * b] = r[j];
-    __syncthreads();
-    if (act)
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            double s = 0.0;
-#pragma unroll
-            for (int q = 0; q < N; ++q) s += tB<N>(q, i) * F[q + N * a + NF * b];
-            y[i] = s;
-        }
-    __syncthreads();
-}
-
 // add face-layer contributions A[f][e1 + N e2] of the six faces to the x
 // pencil (i, j=a, l=b) of the lane
 // add the contribution of face f, computed on its face layer (e1, e2), to
@@ -432,14 +291,12 @@ __device__ __forceinline__ void add_face(const double *A, int f, int a, int b, d
     }
 }
 
-// MINV: the output is A^-1 B p (the rho-weighted mass inverse of each
-// component applied in the epilogue, weights mr), else B p
-template <int N, bool MINV>
+// u3 = B p
+template <int N>
 __global__ void __launch_bounds__(grad_nt<N>())
 k_grad(const double *__restrict__ p, double *__restrict__ u3, int64_t nt,
        const double *__restrict__ W, const double *__restrict__ fn, const int32_t *__restrict__ visit,
-       const RefTab64 *__restrict__ T, double tau, int n_cells, int nwg,
-       const double *__restrict__ mr)
+       const RefTab64 *__restrict__ T, double tau, int n_cells, int nwg)
 {
     constexpr int NF = PCfg<N, GRAD_T>::NF, ND = PCfg<N, GRAD_T>::ND, CPB = PCfg<N, GRAD_T>::CPB;
     __shared__ double sB[NF];
@@ -540,8 +397,6 @@ k_grad(const double *__restrict__ p, double *__restrict__ u3, int64_t nt,
 #pragma unroll
             for (int ec = 0; ec < 3; ++ec) add_face<N>(sA[lc][ec], f, a, b, Y[ec]);
     }
-    if (MINV)
-        mass_inv3<N>(sF[lc][0], sF[lc][1], sF[lc][2], act, a, b, mr + cid * ND + a + N * b, Y);
     if (act)
 #pragma unroll
         for (int ec = 0; ec < 3; ++ec) {
@@ -550,14 +405,12 @@ k_grad(const double *__restrict__ p, double *__restrict__ u3, int64_t nt,
         }
 }
 
-// DP: the output is D x - C u (or bv - (D x - C u) when bv is given), with
-// D the mass of Gauss-point weights md, else C u
-template <int N, bool DP>
+// qv = C u
+template <int N>
 __global__ void __launch_bounds__(div_nt<N>())
 k_div(const double *__restrict__ u3, double *__restrict__ qv, int64_t nt,
       const double *__restrict__ WC, const double *__restrict__ fn, const double *__restrict__ fh,
-      const int32_t *__restrict__ visit, const RefTab64 *__restrict__ T, double tau, int n_cells, int nwg,
-      const double *__restrict__ xv, const double *__restrict__ md, const double *__restrict__ bv)
+      const int32_t *__restrict__ visit, const RefTab64 *__restrict__ T, double tau, int n_cells, int nwg)
 {
     constexpr int NF = PCfg<N, DIV_T>::NF, ND = PCfg<N, DIV_T>::ND, CPB = PCfg<N, DIV_T>::CPB;
     __shared__ double sB[NF];
@@ -693,100 +546,637 @@ k_div(const double *__restrict__ u3, double *__restrict__ qv, int64_t nt,
     if (act)
 #pragma unroll
         for (int i = 0; i < N; ++i) Y[i] += Yf[i];
-    if (DP) {
-        // D x: x at the Gauss points, times md, back to the nodes (x and md
-        // requested together)
-        double xl[N], mdq[N];
-#pragma unroll
-        for (int u = 0; u < N; ++u) {
-            xl[u] = xv[cid * ND + tt + u * NF];
-            mdq[u] = md[cid * ND + a + N * b + NF * u];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if (act) {
-#pragma unroll
-            for (int u = 0; u < N; ++u) sU[lc][0][tt + u * NF] = xl[u];
-        }
-        __syncthreads();
-        double xq[N], dx[N];
-        to_gauss<N>(sU[lc][0], sF[lc], act, a, b, xq);
-        if (act)
-#pragma unroll
-            for (int q = 0; q < N; ++q) xq[q] *= mdq[q];
-        interp_t<N>(sF[lc], act, a, b, xq, dx);
-        if (act)
-#pragma unroll
-            for (int i = 0; i < N; ++i) Y[i] = dx[i] - Y[i];
-    }
     if (act) {
         const int64_t o = cid * ND + N * a + NF * b;
-        if (DP && bv)
-            for (int i = 0; i < N; ++i) qv[o + i] = bv[o + i] - Y[i];
-        else
-            for (int i = 0; i < N; ++i) qv[o + i] = Y[i];
+        for (int i = 0; i < N; ++i) qv[o + i] = Y[i];
+    }
+}
+
+// ---------------------------------------------------------------------------
+// S x = D x - C A^-1 B x in two passes, in the basis of the Gauss points.
+//
+// With as many Gauss points as nodes the interpolation B3 to the points is
+// square, so the Lagrange basis of the points spans the same space and the
+// weak forms may be tested with it; the nodal result is B3^T of that.  In
+// this basis the mass matrices are diagonal (their point weights), so A^-1 is
+// a division and D a product, the interpolations between B, A^-1 and C
+// cancel, a derivative is one N x N matrix DG = BD B^-1 along its direction,
+// and on a face the basis is already at the face's points: the trace is the
+// extrapolation E along the normal line (E_s(q), rows 0 and N - 1 of B^-1)
+// and the test function lifts a face value by E along that line.
+//
+// k_sys_cell (one wave, CPW cells): x at the points; the neighbours' traces
+// from their face layers (column and row lanes as in the operator kernel);
+//   g_e = tau [ -sum_d DG_d^T (x W_de) + sum_f E_f x^ (ds n_e) ],
+//   v_e = g_e / mr,   own flux of face f: hr sum_e v_e ds n_e,
+//   r = md x + tau sum_d DG_d^T (hr sum_e W_de v_e)
+// (D x and the cell part of -C v); it writes r (point values) and the own
+// fluxes.  k_sys_face: r - tau sum_f E_f (own - neighbour's flux) / 2, then
+// B3^T.  Every lane (a, b) works on its x, y and z line of points in turn, and
+// the geometric factors of direction d are loaded in the layout of the lines
+// along d, where they are used; only sums pass through LDS.
+//
+// Affine cells (constant J^-1, W_de = w K_de, ds n_e = +-w_a w_b K_de): with
+//   H_d = w_a w_b tau [ -DG_d^T (w x) + E_1 x^_1 - E_0 x^_0 ],
+// g_e = sum_d K_de H_d, and with a_d = sum_e K_de v_e the fluxes are
+// +-hr w_a w_b E a_d and the cell part of C needs hr w a_d: three scalar lines
+// and ten constants per cell instead of 27 numbers per point.
+//
+// Bound by memory: at degree 4 a general cell moves 152 + 35 bytes per dof
+// in the two passes, an affine one 51 + 35 (the former form, one pass each
+// for A^-1 B and for D - C through nodal values, 133 + 24 and 142 + 16, and
+// LDS-bound at 83 and 75 % of its cycles).  64x32x32 cells, degree 4: 0.713 ->
+// 0.280 ms.
+// ---------------------------------------------------------------------------
+template <int N>
+struct SysCfg {
+    static constexpr int NF = N * N, ND = NF * N;
+    // cells per wave as the traversal's records have them, so that a wave's
+    // cells are of one kind; at N = 2 that would leave 12 of 16 lanes without
+    // a line (49 us at 65,536 cells, the former form 44), so 16 cells share
+    // a wave, all of them on the general data, and a lane takes three columns
+    // of the faces
+    static constexpr bool OWN = N == 2;
+    static constexpr int LPC = OWN ? NF : op_lanes(N), CPW = 64 / LPC;
+    static constexpr int COLS = (6 * N + LPC - 1) / LPC;      // face columns per lane
+    // waves per SIMD asked for: at N = 3 three (145 -> 135 us at 65,536 cells);
+    // above, the factors of a cell's points stay in registers instead
+    static constexpr int WAVES = N == 3 ? 3 : 1;
+    static constexpr int FPWV = 64 / NF;                      // cells per wave of the face pass
+};
+
+// lines of N contiguous values, two at a time where possible
+typedef double dbl2 __attribute__((ext_vector_type(2), aligned(8)));
+template <int N>
+__device__ __forceinline__ void load_line(const double *__restrict__ p, double (&v)[N])
+{
+#pragma unroll
+    for (int i = 0; i + 1 < N; i += 2) {
+        const dbl2 t = *(const dbl2 *)(p + i);
+        v[i] = t.x;
+        v[i + 1] = t.y;
+    }
+    if (N & 1) v[N - 1] = p[N - 1];
+}
+template <int N>
+__device__ __forceinline__ void load_line(const double *__restrict__ p, int stride, double (&v)[N])
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = p[i * stride];
+}
+
+// DG(q, r) = sum_i BD(q, i) B^-1(i, r): derivative at point q of the basis
+// function of point r; E(s, r): that function at end s
+template <int N>
+__device__ __forceinline__ constexpr double tDG(int q, int r)
+{
+    double s = 0.0;
+    for (int i = 0; i < N; ++i) s += tD<N>(q, i) * tBi<N>(i, r);
+    return s;
+}
+template <int N>
+__device__ __forceinline__ constexpr double tE(int s, int r) { return tBi<N>(s ? N - 1 : 0, r); }
+template <int N>
+struct DGTab {
+    double d[N * N];
+    constexpr DGTab() : d()
+    {
+        for (int q = 0; q < N; ++q)
+            for (int r = 0; r < N; ++r) {
+                double s = 0.0;
+                for (int i = 0; i < N; ++i) s += KBD<N>::d[q * N + i] * KBI<N>::d[i * N + r];
+                d[q * N + r] = s;
+            }
+    }
+};
+
+// y += sc DG^T u
+template <int N>
+__device__ __forceinline__ void add_dgt(const double (&u)[N], double sc, double (&y)[N])
+{
+    constexpr DGTab<N> G{};
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < N; ++q) s += G.d[q * N + r] * u[q];
+        y[r] += sc * s;
+    }
+}
+// value at end s of the line u
+template <int N>
+__device__ __forceinline__ double at_end(int s, const double (&u)[N])
+{
+    double v = 0.0;
+#pragma unroll
+    for (int q = 0; q < N; ++q) v += tE<N>(s, q) * u[q];
+    return v;
+}
+// B u along a line
+template <int N>
+__device__ __forceinline__ void to_points(const double (&u)[N], double (&y)[N])
+{
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < N; ++i) s += tB<N>(q, i) * u[i];
+        y[q] = s;
+    }
+}
+
+// a field of the cell in LDS as the lane's lines along x, y and z
+template <int N>
+struct Lines {
+    int x, y, z;   // first element
+    __device__ __forceinline__ Lines(int a, int b) : x(N * a + N * N * b), y(a + N * N * b), z(a + N * b) {}
+    template <int D>
+    __device__ __forceinline__ int at(int i) const
+    {
+        return D == 0 ? x + i : (D == 1 ? y + N * i : z + N * N * i);
+    }
+    template <int D>
+    __device__ __forceinline__ void get(const double *F, double (&v)[N]) const
+    {
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = F[at<D>(i)];
+    }
+    template <int D>
+    __device__ __forceinline__ void put(double *F, const double (&v)[N]) const
+    {
+#pragma unroll
+        for (int i = 0; i < N; ++i) F[at<D>(i)] = v[i];
+    }
+};
+
+template <int N, bool AFF>
+__device__ __forceinline__ void sys_cell(const double *__restrict__ x, double *__restrict__ r,
+                                         double *__restrict__ flux, const double *__restrict__ W,
+                                         const double *__restrict__ kc, const double *__restrict__ fn,
+                                         const double *__restrict__ fh, const double *__restrict__ mr,
+                                         const double *__restrict__ md, const double *__restrict__ hr,
+                                         const int32_t *__restrict__ rec, const RefTab64 *__restrict__ T,
+                                         double tau, bool valid, int64_t cid, int ln,
+                                         double *__restrict__ F /* [3][ND] */, double *__restrict__ P /* [6][NF] */)
+{
+    constexpr int NF = SysCfg<N>::NF, ND = SysCfg<N>::ND;
+    const bool cl = valid && ln < NF;
+    const int a = ln % N, b = (ln / N) % N;
+    const Lines<N> L(a, b);
+    const int64_t o = cid * ND;
+    // ---- loads: the nodal x line, the neighbours' face columns, and the
+    // factors of the x lines
+    double u[N];
+    if (cl) load_line<N>(x + o + L.x, u);
+    constexpr int COLS = SysCfg<N>::COLS, LPC = SysCfg<N>::LPC;
+    double h[COLS][N], hq[N];
+    bool fl[COLS];
+#pragma unroll
+    for (int c = 0; c < COLS; ++c) {
+        // column rr (first tangential direction) of the layer of face f's
+        // neighbour
+        const int col = ln + c * LPC, f = col < 6 * N ? col / N : 0, rr = col % N, fd = f >> 1, fs = f & 1;
+        const int32_t nb = (valid && col < 6 * N) ? rec[1 + f] : -1;
+        fl[c] = nb >= 0;
+        if (!fl[c]) continue;
+        const int sm = fd == 0 ? 1 : (fd == 1 ? N : NF), sp = fd == 0 ? N : 1, sr = fd == 2 ? N : NF;
+        load_line<N>(x + (int64_t)nb * ND + (fs ? 0 : (N - 1) * sm) + rr * sp, sr, h[c]);
+    }
+    bool inner[6];
+#pragma unroll
+    for (int e = 0; e < 6; ++e) inner[e] = valid && rec[1 + e] >= 0;
+    double K[AFF ? 10 : 1], wq[N], wab = 0.0;
+    double Wx[AFF ? 1 : 3][N], Wy[AFF ? 1 : 3][N], Wz[AFF ? 1 : 3][N], n6[AFF ? 1 : 6][3], h6[6];
+    if constexpr (AFF) {
+#pragma unroll
+        for (int q = 0; q < N; ++q) wq[q] = T->wq[q];
+        wab = T->wq[a] * T->wq[b];
+    }
+    if (cl) {
+        if constexpr (AFF) {
+#pragma unroll
+            for (int k = 0; k < 10; ++k) K[k] = kc[16 * cid + k];
+        } else {
+#pragma unroll
+            for (int e = 0; e < 3; ++e) {
+                load_line<N>(W + (cid * 9 + e) * ND + L.x, Wx[e]);
+                load_line<N>(W + (cid * 9 + 3 + e) * ND + L.y, N, Wy[e]);
+                load_line<N>(W + (cid * 9 + 6 + e) * ND + L.z, NF, Wz[e]);
+            }
+#pragma unroll
+            for (int g = 0; g < 6; ++g)
+#pragma unroll
+                for (int e = 0; e < 3; ++e) n6[g][e] = fn[((cid * 6 + g) * 3 + e) * NF + ln];
+        }
+#pragma unroll
+        for (int g = 0; g < 6; ++g) h6[g] = fh[(cid * 6 + g) * NF + ln];
+    }
+    // ---- the neighbours' traces at the face points: second tangential
+    // direction by the column lanes, then the first by the row lanes, in place
+#pragma unroll
+    for (int c = 0; c < COLS; ++c) {
+        if (!fl[c]) continue;
+        const int col = ln + c * LPC;
+        double *Pf = P + col / N * NF;
+        to_points<N>(h[c], hq);
+#pragma unroll
+        for (int q = 0; q < N; ++q) Pf[q * N + col % N] = hq[q];
+    }
+    // ---- x at the points: pz (z line), px, py
+    double px[N], py[N], pz[N], t[N];
+    if (cl) {
+        to_points<N>(u, t);
+        L.template put<0>(F, t);
+    }
+    press_sync();
+#pragma unroll
+    for (int c = 0; c < COLS; ++c) {
+        if (!fl[c]) continue;
+        double *Pr = P + (ln + c * LPC) * N;
+#pragma unroll
+        for (int i = 0; i < N; ++i) h[c][i] = Pr[i];
+        to_points<N>(h[c], hq);
+#pragma unroll
+        for (int q = 0; q < N; ++q) Pr[q] = hq[q];
+    }
+    if (cl) {
+        L.template get<1>(F, u);
+        to_points<N>(u, t);
+        L.template put<1>(F, t);
+    }
+    press_sync();
+    if (cl) {
+        L.template get<2>(F, u);
+        to_points<N>(u, pz);
+        L.template put<2>(F, pz);
+    }
+    press_sync();
+    // ---- face means x^ at the lane's point of each face (a: first, b: second
+    // tangential direction), times tau
+    double ph[6];
+    if (cl) {
+        L.template get<0>(F, px);
+        L.template get<1>(F, py);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            ph[s] = at_end<N>(s, px);
+            ph[2 + s] = at_end<N>(s, py);
+            ph[4 + s] = at_end<N>(s, pz);
+        }
+#pragma unroll
+        for (int g = 0; g < 6; ++g) ph[g] = tau * (inner[g] ? 0.5 * (ph[g] + P[g * NF + ln]) : ph[g]);
+    }
+    press_sync();
+    double rz[N], fx[6];
+    if constexpr (AFF) {
+        // H_d along the lines of d; H_x and H_y pass to the z lines in F0, F1
+        double H[N], mi[N], hz[N], wl[N];
+        auto line = [&](const double (&p)[N], double e0, double e1, double (&out)[N]) {
+#pragma unroll
+            for (int q = 0; q < N; ++q) {
+                wl[q] = wq[q] * p[q];
+                out[q] = wab * (tE<N>(1, q) * e1 - tE<N>(0, q) * e0);
+            }
+            add_dgt<N>(wl, -tau * wab, out);
+        };
+        if (cl) {
+            line(px, ph[0], ph[1], H);
+            L.template put<0>(F, H);
+            line(py, ph[2], ph[3], H);
+            L.template put<1>(F + ND, H);
+            line(pz, ph[4], ph[5], hz);
+            load_line<N>(mr + o + L.z, NF, mi);
+        }
+        press_sync();
+        // v_e = sum_d K_de H_d / mr and a_d = sum_e K_de v_e
+        if (cl) {
+            double hx[N], hy[N];
+            L.template get<2>(F, hx);
+            L.template get<2>(F + ND, hy);
+#pragma unroll
+            for (int q = 0; q < N; ++q) {
+                const double im = 1.0 / mi[q];
+                double v[3];
+#pragma unroll
+                for (int e = 0; e < 3; ++e) v[e] = im * (K[e] * hx[q] + K[3 + e] * hy[q] + K[6 + e] * hz[q]);
+                hx[q] = K[0] * v[0] + K[1] * v[1] + K[2] * v[2];
+                hy[q] = K[3] * v[0] + K[4] * v[1] + K[5] * v[2];
+                hz[q] = K[6] * v[0] + K[7] * v[1] + K[8] * v[2];
+            }
+            L.template put<2>(F, hx);
+            L.template put<2>(F + ND, hy);
+        }
+        press_sync();
+        auto cline = [&](const double (&ad)[N], const double (&hl)[N], double &f0, double &f1, double (&out)[N]) {
+            f0 = -wab * at_end<N>(0, ad);
+            f1 = wab * at_end<N>(1, ad);
+#pragma unroll
+            for (int q = 0; q < N; ++q) wl[q] = wq[q] * hl[q] * ad[q];
+            add_dgt<N>(wl, tau * wab, out);
+        };
+        double hl[N], ad[N], c0[N], c1[N];
+#pragma unroll
+        for (int q = 0; q < N; ++q) c0[q] = c1[q] = rz[q] = 0.0;
+        if (cl) {
+            L.template get<0>(F, ad);
+            load_line<N>(hr + o + L.x, hl);
+            cline(ad, hl, fx[0], fx[1], c0);
+            L.template get<1>(F + ND, ad);
+            load_line<N>(hr + o + L.y, N, hl);
+            cline(ad, hl, fx[2], fx[3], c1);
+            load_line<N>(hr + o + L.z, NF, hl);
+            cline(hz, hl, fx[4], fx[5], rz);
+#pragma unroll
+            for (int q = 0; q < N; ++q) rz[q] += K[9] * wab * wq[q] * pz[q];
+        }
+        press_sync();
+        if (cl) {
+            L.template put<0>(F, c0);
+            L.template put<1>(F + ND, c1);
+        }
+        press_sync();
+        if (cl) {
+            L.template get<2>(F, c0);
+            L.template get<2>(F + ND, c1);
+#pragma unroll
+            for (int q = 0; q < N; ++q) rz[q] += c0[q] + c1[q];
+        }
+    } else {
+        // g_e: the x lines' part to F_e, the y lines add theirs, the z lines
+        // collect
+        auto gline = [&](const double (&p)[N], const double (&w)[N], double e0, double e1, double (&out)[N]) {
+            double tw[N];
+#pragma unroll
+            for (int q = 0; q < N; ++q) {
+                tw[q] = p[q] * w[q];
+                out[q] += tE<N>(0, q) * e0 + tE<N>(1, q) * e1;
+            }
+            add_dgt<N>(tw, -tau, out);
+        };
+        double v[3][N];
+        if (cl)
+#pragma unroll
+            for (int e = 0; e < 3; ++e) {
+                double g[N] = {};
+                gline(px, Wx[e], ph[0] * n6[0][e], ph[1] * n6[1][e], g);
+                L.template put<0>(F + e * ND, g);
+            }
+        press_sync();
+        if (cl)
+#pragma unroll
+            for (int e = 0; e < 3; ++e) {
+                double g[N];
+                L.template get<1>(F + e * ND, g);
+                gline(py, Wy[e], ph[2] * n6[2][e], ph[3] * n6[3][e], g);
+                L.template put<1>(F + e * ND, g);
+            }
+        press_sync();
+        if (cl) {
+            double mi[N];
+            load_line<N>(mr + o + L.z, NF, mi);
+#pragma unroll
+            for (int q = 0; q < N; ++q) mi[q] = 1.0 / mi[q];
+#pragma unroll
+            for (int e = 0; e < 3; ++e) {
+                L.template get<2>(F + e * ND, v[e]);
+                gline(pz, Wz[e], ph[4] * n6[4][e], ph[5] * n6[5][e], v[e]);
+#pragma unroll
+                for (int q = 0; q < N; ++q) v[e][q] *= mi[q];
+                L.template put<2>(F + e * ND, v[e]);
+            }
+        }
+        press_sync();
+        // own fluxes and hr sum_e W_de v_e on the lines of d, its DG^T
+        auto cline = [&](const double (&ve)[3][N], const double (&w)[3][N], const double (&hl)[N], int f0,
+                         double (&out)[N]) {
+            double tw[N];
+#pragma unroll
+            for (int q = 0; q < N; ++q)
+                tw[q] = hl[q] * (w[0][q] * ve[0][q] + w[1][q] * ve[1][q] + w[2][q] * ve[2][q]);
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                double sum = 0.0;
+#pragma unroll
+                for (int e = 0; e < 3; ++e) sum += at_end<N>(s, ve[e]) * n6[f0 + s][e];
+                fx[f0 + s] = sum;
+            }
+            add_dgt<N>(tw, tau, out);
+        };
+        double hl[N], c0[N], c1[N];
+#pragma unroll
+        for (int q = 0; q < N; ++q) c0[q] = c1[q] = rz[q] = 0.0;
+        if (cl) {
+            load_line<N>(hr + o + L.z, NF, hl);
+            cline(v, Wz, hl, 4, rz);
+            double mq[N];
+            load_line<N>(md + o + L.z, NF, mq);
+#pragma unroll
+            for (int q = 0; q < N; ++q) rz[q] += mq[q] * pz[q];
+#pragma unroll
+            for (int e = 0; e < 3; ++e) L.template get<0>(F + e * ND, v[e]);
+            load_line<N>(hr + o + L.x, hl);
+            cline(v, Wx, hl, 0, c0);
+#pragma unroll
+            for (int e = 0; e < 3; ++e) L.template get<1>(F + e * ND, v[e]);
+            load_line<N>(hr + o + L.y, N, hl);
+            cline(v, Wy, hl, 2, c1);
+        }
+        press_sync();
+        if (cl) {
+            L.template put<0>(F, c0);
+            L.template put<1>(F + ND, c1);
+        }
+        press_sync();
+        if (cl) {
+            L.template get<2>(F, c0);
+            L.template get<2>(F + ND, c1);
+#pragma unroll
+            for (int q = 0; q < N; ++q) rz[q] += c0[q] + c1[q];
+        }
+    }
+    if (cl) {
+#pragma unroll
+        for (int q = 0; q < N; ++q) r[o + L.z + NF * q] = rz[q];
+#pragma unroll
+        for (int g = 0; g < 6; ++g) flux[(cid * 6 + g) * NF + ln] = h6[g] * fx[g];
+    }
+}
+
+// MODE: the waves' cells are general (0), affine (1) or of either kind, the
+// first record of a wave telling which (2), as in the operator kernel
+template <int N, int MODE>
+__global__ void __launch_bounds__(64, SysCfg<N>::WAVES)
+k_sys_cell(const double *__restrict__ x, double *__restrict__ r, double *__restrict__ flux,
+           const double *__restrict__ W, const double *__restrict__ kc, const double *__restrict__ fn,
+           const double *__restrict__ fh, const double *__restrict__ mr, const double *__restrict__ md,
+           const double *__restrict__ hr, const int32_t *__restrict__ visit, const RefTab64 *__restrict__ T,
+           double tau, int n_slots, int nwg)
+{
+    constexpr int LPC = SysCfg<N>::LPC, CPW = SysCfg<N>::CPW;
+    __shared__ double sF[CPW][3 * SysCfg<N>::ND], sP[CPW][6 * SysCfg<N>::NF];
+    const int bid = blockIdx.x;
+    const int q8 = nwg / NXCD, r8 = nwg % NXCD, xcd = bid % NXCD;
+    const int wg = xcd * q8 + (xcd < r8 ? xcd : r8) + bid / NXCD;
+    const int cs = threadIdx.x / LPC, ln = threadIdx.x % LPC;
+    const int slot = wg * CPW + cs;
+    const int32_t *rec = visit + (int64_t)(slot < n_slots ? slot : 0) * 8;
+    const int32_t rc = rec[0];
+    const bool valid = slot < n_slots && rc >= 0;
+    const int64_t cid = valid ? rc : 0;
+    const bool waff = MODE == 2 ? visit[(int64_t)wg * CPW * 8 + 7] & 1 : MODE == 1;
+    if (MODE == 1 || (MODE == 2 && waff))
+        sys_cell<N, true>(x, r, flux, W, kc, fn, fh, mr, md, hr, rec, T, tau, valid, cid, ln, sF[cs], sP[cs]);
+    else if (MODE != 1)
+        sys_cell<N, false>(x, r, flux, W, kc, fn, fh, mr, md, hr, rec, T, tau, valid, cid, ln, sF[cs], sP[cs]);
+}
+
+// y (or b - y) = B3^T (r - tau sum_f E_f (own - neighbour's flux) / 2); 64 / NF
+// cells per wave, lane (a, b) of a cell
+template <int N>
+__global__ void __launch_bounds__(64)
+k_sys_face(const double *__restrict__ r, const double *__restrict__ flux, const int32_t *__restrict__ visit,
+           double tau, const double *__restrict__ bv, double *__restrict__ y, int n_cells, int nwg)
+{
+    constexpr int NF = SysCfg<N>::NF, ND = SysCfg<N>::ND, CPW = SysCfg<N>::FPWV;
+    __shared__ double sF[CPW][ND], sP[CPW][4 * NF];
+    const int bid = blockIdx.x;
+    const int q8 = nwg / NXCD, r8 = nwg % NXCD, xcd = bid % NXCD;
+    const int wg = xcd * q8 + (xcd < r8 ? xcd : r8) + bid / NXCD;
+    const int cs = threadIdx.x / NF, ln = threadIdx.x % NF;
+    const int slot = wg * CPW + cs;
+    const bool cl = cs < CPW && slot < n_cells;
+    const int32_t *rec = visit + (int64_t)(cl ? slot : 0) * 8;
+    const int64_t cid = rec[0];
+    const int a = ln % N, b = ln / N;
+    const Lines<N> L(a, b);
+    double *F = sF[cs < CPW ? cs : 0], *P = sP[cs < CPW ? cs : 0];
+    double u[N], t[N], g[6];
+    if (cl) {
+        load_line<N>(r + cid * ND + L.z, NF, u);
+#pragma unroll
+        for (int f = 0; f < 6; ++f) {
+            const int32_t nb = rec[1 + f];
+            const double own = flux[(cid * 6 + f) * NF + ln];
+            const double nbr = flux[((nb >= 0 ? (int64_t)nb : cid) * 6 + (f ^ 1)) * NF + ln];
+            g[f] = nb >= 0 ? -0.5 * tau * (own - nbr) : 0.0;
+        }
+        // the x and y faces' values where the z lines read them
+#pragma unroll
+        for (int f = 0; f < 4; ++f) P[f * NF + ln] = g[f];
+    }
+    press_sync();
+    if (cl) {
+        double ex[2] = {0.0, 0.0}, ey[2] = {0.0, 0.0};   // E at the lane's x and y index
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int m = 0; m < N; ++m) {
+                if (m == a) ex[s] = tE<N>(s, m);
+                if (m == b) ey[s] = tE<N>(s, m);
+            }
+        // lane (qx = a, qy = b): x faces' points (qy, qz), y faces' (qx, qz)
+#pragma unroll
+        for (int q = 0; q < N; ++q)
+            u[q] += tE<N>(0, q) * g[4] + tE<N>(1, q) * g[5] + ex[0] * P[b + N * q] + ex[1] * P[NF + b + N * q] +
+                    ey[0] * P[2 * NF + a + N * q] + ey[1] * P[3 * NF + a + N * q];
+    }
+    auto back = [&](const double (&w)[N], double (&z)[N]) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            double s = 0.0;
+#pragma unroll
+            for (int q = 0; q < N; ++q) s += tB<N>(q, i) * w[q];
+            z[i] = s;
+        }
+    };
+    if (cl) {
+        back(u, t);
+        L.template put<2>(F, t);
+    }
+    press_sync();
+    if (cl) {
+        L.template get<1>(F, u);
+        back(u, t);
+        L.template put<1>(F, t);
+    }
+    press_sync();
+    if (cl) {
+        L.template get<0>(F, u);
+        back(u, t);
+        double *yo = y + cid * ND + L.x;
+        if (bv) {
+            load_line<N>(bv + cid * ND + L.x, u);
+#pragma unroll
+            for (int i = 0; i < N; ++i) t[i] = u[i] - t[i];
+        }
+#pragma unroll
+        for (int i = 0; i + 1 < N; i += 2) *(dbl2 *)(yo + i) = dbl2{t[i], t[i + 1]};
+        if (N & 1) yo[N - 1] = t[N - 1];
     }
 }
 
 template <int N>
-hipError_t grad_n(hx_ctx *c, const double *p, double *u3, bool minv)
+hipError_t grad_n(hx_ctx *c, const double *p, double *u3)
 {
     const int cpb = PCfg<N, GRAD_T>::CPB;
     const int nb = (int)((c->n_cells + cpb - 1) / cpb);
-    if (minv)
-        hipLaunchKernelGGL((k_grad<N, true>), dim3(nb), dim3(PCfg<N, GRAD_T>::NT), 0, c->stream, p, u3,
-                           c->n_dofs, c->psW, c->psFn, c->visitp, c->ref, c->ps_tau, (int)c->n_cells,
-                           nb, c->psMr);
-    else
-        hipLaunchKernelGGL((k_grad<N, false>), dim3(nb), dim3(PCfg<N, GRAD_T>::NT), 0, c->stream, p,
-                           u3, c->n_dofs, c->psW, c->psFn, c->visitp, c->ref, c->ps_tau,
-                           (int)c->n_cells, nb, (const double *)nullptr);
+    hipLaunchKernelGGL(k_grad<N>, dim3(nb), dim3(PCfg<N, GRAD_T>::NT), 0, c->stream, p, u3, c->n_dofs,
+                       c->psW, c->psFn, c->visitp, c->ref, c->ps_tau, (int)c->n_cells, nb);
     return hipGetLastError();
 }
 
 template <int N>
-hipError_t div_n(hx_ctx *c, const double *u3, double *q, const double *x, const double *b)
+hipError_t div_n(hx_ctx *c, const double *u3, double *q)
 {
     const int cpb = PCfg<N, DIV_T>::CPB;
     const int nb = (int)((c->n_cells + cpb - 1) / cpb);
-    if (x)
-        hipLaunchKernelGGL((k_div<N, true>), dim3(nb), dim3(PCfg<N, DIV_T>::NT), 0, c->stream, u3, q,
-                           c->n_dofs, c->psWC, c->psFn, c->psFh, c->visitp, c->ref, c->ps_tau,
-                           (int)c->n_cells, nb, x, c->psMd, b);
-    else
-        hipLaunchKernelGGL((k_div<N, false>), dim3(nb), dim3(PCfg<N, DIV_T>::NT), 0, c->stream, u3, q,
-                           c->n_dofs, c->psWC, c->psFn, c->psFh, c->visitp, c->ref, c->ps_tau,
-                           (int)c->n_cells, nb, (const double *)nullptr, (const double *)nullptr,
-                           (const double *)nullptr);
+    hipLaunchKernelGGL(k_div<N>, dim3(nb), dim3(PCfg<N, DIV_T>::NT), 0, c->stream, u3, q, c->n_dofs,
+                       c->psWC, c->psFn, c->psFh, c->visitp, c->ref, c->ps_tau, (int)c->n_cells, nb);
     return hipGetLastError();
 }
 
-hipError_t grad_dispatch(hx_ctx *c, const double *p, double *u3, bool minv)
+// y = S x, or b - S x when b is given
+template <int N>
+hipError_t sys_n(hx_ctx *c, const double *x, double *y, const double *b)
 {
-    switch (c->n) {
-    case 2: return grad_n<2>(c, p, u3, minv);
-    case 3: return grad_n<3>(c, p, u3, minv);
-    case 4: return grad_n<4>(c, p, u3, minv);
-    case 5: return grad_n<5>(c, p, u3, minv);
-    case 6: return grad_n<6>(c, p, u3, minv);
-    case 7: return grad_n<7>(c, p, u3, minv);
-    case 8: return grad_n<8>(c, p, u3, minv);
-    default: return hipErrorInvalidValue;
+    const int cpw = SysCfg<N>::CPW;
+    const bool own = SysCfg<N>::OWN;
+    const int32_t *visit = own ? c->visitp : c->visit;
+    const int64_t slots = own ? c->n_cells : c->n_vis_op;
+    const int mode = own ? 0 : c->vis_mode;
+    const int nw = (int)((slots + cpw - 1) / cpw);
+    double *r = c->psWork + 3 * c->n_dofs, *flux = r + c->n_dofs;
+#define HX_SYS(MODE)                                                                              \
+    hipLaunchKernelGGL((k_sys_cell<N, MODE>), dim3(nw), dim3(64), 0, c->stream, x, r, flux, c->psW, \
+                       c->psK, c->psFn, c->psFh, c->psMr, c->psMd, c->psHr, visit, c->ref,          \
+                       c->ps_tau, (int)slots, nw)
+    if constexpr (!SysCfg<N>::OWN) {
+        if (mode == 2) HX_SYS(2);
+        else if (mode == 1) HX_SYS(1);
+        else HX_SYS(0);
+    } else {
+        HX_SYS(0);
     }
+#undef HX_SYS
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const int nf = (int)((c->n_cells + SysCfg<N>::FPWV - 1) / SysCfg<N>::FPWV);
+    hipLaunchKernelGGL(k_sys_face<N>, dim3(nf), dim3(64), 0, c->stream, r, flux, c->visitp, c->ps_tau, b, y,
+                       (int)c->n_cells, nf);
+    return hipGetLastError();
 }
 
-hipError_t div_dispatch(hx_ctx *c, const double *u3, double *q, const double *x, const double *b)
-{
-    switch (c->n) {
-    case 2: return div_n<2>(c, u3, q, x, b);
-    case 3: return div_n<3>(c, u3, q, x, b);
-    case 4: return div_n<4>(c, u3, q, x, b);
-    case 5: return div_n<5>(c, u3, q, x, b);
-    case 6: return div_n<6>(c, u3, q, x, b);
-    case 7: return div_n<7>(c, u3, q, x, b);
-    case 8: return div_n<8>(c, u3, q, x, b);
-    default: return hipErrorInvalidValue;
+#define HX_BY_DEGREE(F, ...)                      \
+    switch (c->n) {                               \
+    case 2: return F<2>(__VA_ARGS__);             \
+    case 3: return F<3>(__VA_ARGS__);             \
+    case 4: return F<4>(__VA_ARGS__);             \
+    case 5: return F<5>(__VA_ARGS__);             \
+    case 6: return F<6>(__VA_ARGS__);             \
+    case 7: return F<7>(__VA_ARGS__);             \
+    case 8: return F<8>(__VA_ARGS__);             \
+    default: return hipErrorInvalidValue;         \
     }
-}
 
 // h = gamma p / ((gamma - 1) rho): specific enthalpy of an ideal gas
 __global__ void k_enthalpy(int64_t n, const double *__restrict__ p, const double *__restrict__ rho,
@@ -806,18 +1196,13 @@ hipError_t launch_enthalpy(hx_ctx *c, const double *p, const double *rho, double
     return hipGetLastError();
 }
 
-hipError_t launch_grad(hx_ctx *c, const double *p, double *u3) { return grad_dispatch(c, p, u3, false); }
+hipError_t launch_grad(hx_ctx *c, const double *p, double *u3) { HX_BY_DEGREE(grad_n, c, p, u3) }
 
-hipError_t launch_div(hx_ctx *c, const double *u3, double *q) { return div_dispatch(c, u3, q, nullptr, nullptr); }
+hipError_t launch_div(hx_ctx *c, const double *u3, double *q) { HX_BY_DEGREE(div_n, c, u3, q) }
 
-// y = S x = D x - C A^-1 B x, or y = b - S x when b is given: two passes,
-// v = A^-1 B x (the mass inverse in the gradient's epilogue), then
-// D x - C v (the mass of x in the divergence's epilogue)
 hipError_t press_apply64(hx_ctx *c, const double *x, double *y, const double *b)
 {
-    double *v3 = c->psWork + 3 * c->n_dofs;
-    hipError_t e = grad_dispatch(c, x, v3, true);
-    return e != hipSuccess ? e : div_dispatch(c, v3, y, x, b);
+    HX_BY_DEGREE(sys_n, c, x, y, b)
 }
 
 }  // namespace hx

@@ -224,3 +224,27 @@ def test_sampled_parity_full_size_terrain():
     del s
     assert _close(ss, ref.apply_cells(pv, cells), 1e-11), "S"
     ctx.close()
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 6, 7])
+def test_system_on_affine_and_general_cells(k):
+    """S at every degree on a ragged channel with both kinds of cells (the
+    cells far from the ridge are affine, with their own form of the kernel;
+    degree 1 treats every cell as general): against the oracle, and with every
+    cell taken as general, to 1e-11 as the other checks of S (both sides round
+    differently; S is a difference of its terms)."""
+    hx = _hx()
+    p, ref, ctx = _setup("terrain-7x1x3-g2", lambda: si.terrain_mesh(7, 1, 3, g=2), k)
+    try:
+        counts, _ = ctx.operator_info()
+        assert 0 < counts["affine_cells"] < counts["cells"]
+        x = si.random_vector(p.n_dofs, 70 + k)
+        sr = ref.apply(x)
+        s1 = ctx.apply_pressure_part(hx.HX_PS_SYSTEM, to_dev(x)).cpu().numpy()
+        assert _close(s1, sr, 1e-11)
+        ctx.set_cell_compression(False)
+        s2 = ctx.apply_pressure_part(hx.HX_PS_SYSTEM, to_dev(x)).cpu().numpy()
+        assert _close(s2, sr, 1e-11) and _close(s1, s2, 1e-11)
+        ctx.set_cell_compression(True)
+    finally:
+        ctx.close()
