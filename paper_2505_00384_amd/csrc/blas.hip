@@ -141,6 +141,48 @@ __device__ void sum_rows(const double *__restrict__ part, int nrows, int nb, int
     }
 }
 
+// The wave sums of K values per lane at once.  Lanes o apart share the
+// values out between them before they add: each keeps one half and hands
+// over the other, so a step costs half the shuffles of the step before
+// (K + K/2 + .. instead of 6 K); from an odd count on both keep all.  Value q
+// of the S that are left in v[] is number base + q.  The pairs that
+// are added are those of wave_sum: the sums are the same to the last bit.
+// The sums of one value at a time were a third of k_dcgs_dot on systems whose
+// basis stays in the caches (0.5 M values, 28 vectors: 31.8 us, now 21.6; 16:
+// 19.6 and 13.4; 8: 10.8 and 8).
+template <int K, int O = 32>
+__device__ __forceinline__ void wave_sums(double *v, int lane, int &base)
+{
+    if constexpr (O > 0) {
+        if constexpr (K % 2 == 0) {
+            const bool up = lane & O;
+#pragma unroll
+            for (int q = 0; q < K / 2; ++q) {
+                const double keep = up ? v[q + K / 2] : v[q];
+                const double give = up ? v[q] : v[q + K / 2];
+                v[q] = keep + __shfl_xor(give, O, 64);
+            }
+            if (up) base += K / 2;
+            wave_sums<K / 2, O / 2>(v, lane, base);
+        } else {
+#pragma unroll
+            for (int q = 0; q < K; ++q) v[q] += __shfl_xor(v[q], O, 64);
+            wave_sums<K, O / 2>(v, lane, base);
+        }
+    }
+}
+
+// the values that a lane holds after wave_sums<K>, and the lanes (low bits)
+// that hold the same ones
+constexpr int wave_sums_left(int k, int o = 32)
+{
+    return o == 0 ? k : wave_sums_left(k % 2 == 0 ? k / 2 : k, o / 2);
+}
+constexpr int wave_sums_copies(int k, int o = 32)
+{
+    return o == 0 ? 1 : (k % 2 == 0 ? wave_sums_copies(k / 2, o / 2) : 2 * o);
+}
+
 // MC: vectors per workgroup row (a multiple of 4 at least the chunk's
 // count, so few loads are wasted on padding); NT: streaming loads of the
 // basis (vectors far larger than the caches; on small systems the basis is
@@ -155,9 +197,9 @@ __global__ void __launch_bounds__(RT) k_dcgs_dot(int64_t n, int j, const double 
     const int v0 = blockIdx.y * MC;
     const int mc = (m - v0) < MC ? (m - v0) : MC;
     const double *t = V + (int64_t)j * ldv;
-    double sa[MC], sb[MC];
+    double sv[2 * MC];   // with t, then with w
 #pragma unroll
-    for (int k = 0; k < MC; ++k) sa[k] = sb[k] = 0.0;
+    for (int k = 0; k < 2 * MC; ++k) sv[k] = 0.0;
     const int64_t stride = (int64_t)gridDim.x * RT;
     // rows past the chunk's last vector repeat that vector (same cache
     // lines, results unused), so the loads issue without branches
@@ -174,19 +216,17 @@ __global__ void __launch_bounds__(RT) k_dcgs_dot(int64_t n, int j, const double 
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int k = 0; k < MC; ++k) {
-            sa[k] += v[k] * ai;
-            sb[k] += v[k] * bi;
+            sv[k] += v[k] * ai;
+            sv[MC + k] += v[k] * bi;
         }
     }
     // per-wave sums, then the waves in a fixed order
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    int base = 0;
+    wave_sums<2 * MC>(sv, lane, base);
+    if (lane % wave_sums_copies(2 * MC) == 0) {
 #pragma unroll
-    for (int k = 0; k < MC; ++k) {
-        const double ra = wave_sum(sa[k]), rb = wave_sum(sb[k]);
-        if (lane == 0) {
-            wsum[wv][k] = ra;
-            wsum[wv][MC + k] = rb;
-        }
+        for (int q = 0; q < wave_sums_left(2 * MC); ++q) wsum[wv][base + q] = sv[q];
     }
     __syncthreads();
     if ((int)threadIdx.x < 2 * mc) {
