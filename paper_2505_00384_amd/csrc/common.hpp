@@ -15,6 +15,18 @@ namespace hx {
 constexpr int MAXK = 7;             // highest supported polynomial degree
 constexpr int MAXN = MAXK + 1;      // points per direction
 constexpr int MAXG = 8;             // highest geometry degree
+// FP32 face data with n points per direction: the components of a point side
+// by side ([point][component]).  The operator's lane then has its seven values
+// of a point in a load of 16 and one of 12 bytes, where the component order
+// takes seven of 4 bytes, each of which touches the lines of up to twelve
+// faces: the vector cache's address path is what bounds that kernel.  At
+// n = 8 a row of one component is a whole 32-byte sector and the component
+// order is the better one.  Operator on general cells, component / point
+// order: degree 1 167 / 139 us (128x64x64), 2 208 / 169 (128x32x64), 4 145 /
+// 117 (64x32x32), 6 103 / 92 (32x16x32), 7 58.7 / 60.8 (32x16x16).  FP64 loads
+// of 16 bytes move no more per cycle than those of 8: no change there (345 /
+// 346 us at 128x32x32, degree 4), so its data stay in component order.
+constexpr bool face32_by_point(int n) { return n < 8; }
 constexpr int NXCD = 8;             // accelerator complex dies of the MI355X
 
 // Reference data of one degree (host side, FP64).
@@ -79,7 +91,7 @@ struct hx_ctx {
     double *cellgeo = nullptr;    // [n_cells][7][nd] geometric factors of the cell data
     double *facegeo = nullptr;    // [n_cells][3][7][nf] geometric factors of the face data
     double *face64 = nullptr;     // [n_cells][3][7][N (1st tangential)][N (2nd)]
-    float *face32 = nullptr;
+    float *face32 = nullptr;      // same, or [n_cells][3][nf][7] where face32_by_point
     // compressed data of affine cells (one Jacobian per cell): the operator
     // reads these instead of cell64/face64 for affine cells and for faces
     // between two affine cells (bits of the traversal record's last word)
@@ -100,7 +112,7 @@ struct hx_ctx {
     double *kk64 = nullptr;       // [n_cells][8]      J^-1 J^-T (6 unique entries), detJ, 0
     float *kk32 = nullptr;
     double *aface64 = nullptr;    // [n_cells][3][2][nf] beta- w, beta+ w on the +d face (affine pair)
-    float *aface32 = nullptr;
+    float *aface32 = nullptr;     // same, or [n_cells][3][nf][2] where face32_by_point
     double *fc64 = nullptr;       // [n_cells][3][8]   v- (3), v+ (3), sigma ds0 / 2, 0 of the +d face
     float *fc32 = nullptr;
     // non-conforming (2:1) quarter faces: records {C, fc, F, s} (face fc of

@@ -783,7 +783,9 @@ k_set_face(int64_t n_cells, const int32_t *__restrict__ visit, const RefTab64 *_
            float *__restrict__ aface32)
 {
     constexpr int NF = SCfg<N>::NF, ND = SCfg<N>::ND, LPC = SCfg<N>::FLPC, CPW = SCfg<N>::FCPW;
+    constexpr bool PT = face32_by_point(N);
     __shared__ double sT[CPW][6][NF], sV[CPW][6][NF];
+    __shared__ float sF[CPW][3][7 * NF];   // FP32 data, put into their own order
     const int cs = threadIdx.x / LPC, ln = threadIdx.x % LPC;
     const int64_t slot = xcd_range() * CPW + cs;
     // the traversal record {cell, neighbours, mask}; bit 2 + 2 e of the mask:
@@ -856,13 +858,11 @@ k_set_face(int64_t n_cells, const int32_t *__restrict__ visit, const RefTab64 *_
         for (int q = 0; q < N; ++q) sV[cs][f][q * N + p] = y[q];
     }
     __syncthreads();
-    if (!valid) return;
 #pragma unroll
     for (int e = 0; e < 3; ++e) {
         const int64_t cd = 3 * cid + e;
-        if (FULL || !cmp[e]) {
+        if (valid && (FULL || !cmp[e])) {
             double *dst = face64 + cd * 7 * NF;
-            float *dstf = face32 + cd * 7 * NF;
 #pragma unroll
             for (int u = 0; u < GPL; ++u) {
                 const int k = ln + u * LPC;
@@ -871,7 +871,7 @@ k_set_face(int64_t n_cells, const int32_t *__restrict__ visit, const RefTab64 *_
                 const double bm = sV[cs][2 * e][pt], bp = sV[cs][2 * e + 1][pt];
                 const double out = (s < 3 ? bm : (s < 6 ? bp : sg[e] * (bm + bp))) * g[e][u];
                 dst[k] = out;
-                dstf[k] = (float)out;
+                sF[cs][e][PT ? 7 * pt + s : k] = (float)out;
             }
         }
         if (cmp[e]) {
@@ -882,10 +882,21 @@ k_set_face(int64_t n_cells, const int32_t *__restrict__ visit, const RefTab64 *_
                 const int k = ln + u * LPC;
                 if (k >= 2 * NF) break;
                 const int s = k / NF, pt = k - s * NF;
-                const double out = sV[cs][2 * e + s][pt] * (T->wq[pt / N] * T->wq[pt % N]);
-                dst[k] = out;
-                dstf[k] = (float)out;
+                dst[k] = sV[cs][2 * e + s][pt] * (T->wq[pt / N] * T->wq[pt % N]);
+                const int pf = PT ? k >> 1 : pt, sf = PT ? k & 1 : s;
+                dstf[k] = (float)(sV[cs][2 * e + sf][pf] * (T->wq[pf / N] * T->wq[pf % N]));
             }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+        if (!valid || (!FULL && cmp[e])) continue;
+        float *dstf = face32 + (3 * cid + e) * 7 * NF;
+#pragma unroll
+        for (int u = 0; u < GPL; ++u) {
+            const int k = ln + u * LPC;
+            if (k < 7 * NF) dstf[k] = sF[cs][e][k];
         }
     }
 }
@@ -936,7 +947,8 @@ __global__ void k_expand_cell(int64_t total, int nd, const uint8_t *__restrict__
 
 __global__ void k_expand_face(int64_t total, int nf, const int32_t *__restrict__ nbr,
                               const uint8_t *__restrict__ ctype, const double *__restrict__ aface,
-                              const double *__restrict__ fc, double *face64, float *face32)
+                              const double *__restrict__ fc, bool by_point, double *face64,
+                              float *face32)
 {
     const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (t >= total) return;
@@ -948,7 +960,7 @@ __global__ void k_expand_face(int64_t total, int nf, const int32_t *__restrict__
     for (int s = 0; s < 7; ++s) {
         const double v = s < 6 ? (s < 3 ? bm : bp) * fc[cd * 8 + s] : fc[cd * 8 + 6] * (bm + bp);
         face64[(cd * 7 + s) * nf + pt] = v;
-        face32[(cd * 7 + s) * nf + pt] = (float)v;
+        face32[by_point ? t * 7 + s : (cd * 7 + s) * nf + pt] = (float)v;
     }
 }
 
@@ -1046,7 +1058,7 @@ hipError_t launch_expand_general(hx_ctx *c)
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_expand_face, dim3(nblk(nf, 256)), dim3(256), 0, c->stream, nf, c->nf, c->nbr,
-                       c->ctype, c->aface64, c->fc64, c->face64, c->face32);
+                       c->ctype, c->aface64, c->fc64, face32_by_point(c->n), c->face64, c->face32);
     return hipGetLastError();
 }
 

@@ -17,7 +17,8 @@
 //    along the second tangential direction in registers; after one LDS
 //    transpose lane (f, q2) finishes the first direction, the pointwise flux
 //    terms at the Gauss points (face data laid out [comp][q1][q2], so these
-//    loads are contiguous across lanes too) and the transposed sweep; a second
+//    loads are contiguous across lanes too; FP32 mostly [q1][q2][comp], see
+//    face32_by_point) and the transposed sweep; a second
 //    transpose returns to columns for the last transposed sweep.  The two
 //    sides pass through the same three fields of LDS one after the other, and
 //    the transposed sweeps write over what they read, so a face needs 3 N^2
@@ -200,6 +201,23 @@ template <typename T>
 __device__ __forceinline__ T ld_stream(const T *p)
 {
     return __builtin_nontemporal_load(p);
+}
+
+// K neighbouring values, aligned as one of them, in loads of 16 bytes as far
+// as they go
+template <typename T, int K>
+__device__ __forceinline__ void load_values(const T *__restrict__ p, T (&v)[K])
+{
+    constexpr int W = 16 / sizeof(T);
+    typedef T vec __attribute__((ext_vector_type(W), aligned(sizeof(T))));
+#pragma unroll
+    for (int i = 0; i + W <= K; i += W) {
+        const vec t = *(const vec *)(p + i);
+#pragma unroll
+        for (int k = 0; k < W; ++k) v[i + k] = t[k];
+    }
+#pragma unroll
+    for (int i = K / W * W; i < K; ++i) v[i] = p[i];
 }
 
 // PART: 0 the whole operator, 1 the cell integrals only, 2 the face terms only;
@@ -489,7 +507,8 @@ __device__ __forceinline__ void apply_body(
             gf[2 * NF + q * N + rr] = g2[q];
         }
     };
-    // face data of this row: [comp][q1][q2], components g-(3), g+(3), s
+    // face data of this row: [comp][q1][q2] (or, FP32, [q1][q2][comp]),
+    // components g-(3), g+(3), s
     const int64_t fid = s ? cid : (int64_t)nb;
     const T *fd = face + (fid * 3 + d) * 7 * NF + rr;
     // g of the neighbour side: g+ if the own cell is the minus cell
@@ -501,7 +520,37 @@ __device__ __forceinline__ void apply_body(
     // side (in gow[0]) and the face's constants v-, v+, sd (in fcv)
     T gnb[3][N], gow[3][N], pn[N], fcv[7];
     if (fl) {
-        if (fcmp) {
+        if constexpr (sizeof(T) == 4 && face32_by_point(N)) {
+            // the values of a point side by side
+            if (fcmp) {
+                const T *af = aface + ((fid * 3 + d) * NF + rr) * 2;
+                T v[N][2];
+#pragma unroll
+                for (int q1 = 0; q1 < N; ++q1) load_values<T, 2>(af + 2 * N * q1, v[q1]);
+#pragma unroll
+                for (int q1 = 0; q1 < N; ++q1) {
+                    gnb[0][q1] = s ? v[q1][1] : v[q1][0];
+                    gow[0][q1] = s ? v[q1][0] : v[q1][1];
+                }
+                const T *fp = fcon + (fid * 3 + d) * 8;
+#pragma unroll
+                for (int k = 0; k < 7; ++k) fcv[k] = fp[k];
+            } else {
+                const T *fp = face + ((fid * 3 + d) * NF + rr) * 7;
+                T v[N][7];
+#pragma unroll
+                for (int q1 = 0; q1 < N; ++q1) load_values<T, 7>(fp + 7 * N * q1, v[q1]);
+#pragma unroll
+                for (int q1 = 0; q1 < N; ++q1) {
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        gnb[k][q1] = s ? v[q1][3 + k] : v[q1][k];
+                        gow[k][q1] = s ? v[q1][k] : v[q1][3 + k];
+                    }
+                    pn[q1] = v[q1][6];
+                }
+            }
+        } else if (fcmp) {
             const T *af = aface + (fid * 3 + d) * 2 * NF + rr;
             const int bn_off = s ? NF : 0, bo_off = s ? 0 : NF;
 #pragma unroll

@@ -63,3 +63,29 @@ def test_forms_of_the_coefficient_update(k):
         assert normwise(y32, ref)[0] <= 2e-6
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 6, 7])
+def test_single_precision_face_data(k):
+    """The FP32 face data have an order of their own up to degree 6: the FP32
+    operator with compressed data, with general data written by the update and
+    with general data rebuilt from the compressed ones.  Tolerance 2e-6, as for
+    the FP32 operator above (rounded data and about 3 (k + 1) roundings a
+    sweep, 6e-8 each)."""
+    p = problem(si.terrain_mesh(7, 1, 3, g=2), k, coef="terrain")
+    x = si.random_vector(p.n_dofs, 80 + k)
+    ref = p.apply(x)
+    ctx = gpu_context(p)
+    try:
+        def apply(what):
+            print(f"[coef32] k={k} {what}", flush=True)
+            y = ctx.apply_operator(to_dev(x.astype(np.float32))).cpu().numpy()
+            assert normwise(y, ref)[0] <= 2e-6, what
+
+        apply("compressed")
+        ctx.set_cell_compression(False)
+        apply("rebuilt")
+        ctx.set_coefficients(p.alpha, p.beta, p.P)
+        apply("written")
+    finally:
+        ctx.close()
