@@ -283,6 +283,10 @@ hipError_t launch_cg_massinv32(hx_ctx *c, float *x, float *r, const float *p, co
 // operator: y = A x, or y = b - A x when b != nullptr
 hipError_t launch_apply64(hx_ctx *c, const double *x, double *y, const double *b);
 hipError_t launch_apply32(hx_ctx *c, const float *x, float *y, const float *b);
+// d = ca M^-1 (b - A x) + cb d (d read only with read_d), xo = x + d in one
+// launch, M the block Jacobi; xo another buffer than x; conforming meshes only
+hipError_t launch_apply32_cheb(hx_ctx *c, const float *x, const float *b, float *xo, float *d, double ca,
+                               double cb, int read_d);
 // non-conforming faces: geometry and penalties, merged data from nodal
 // beta, and y += (y -= with residual) the quarter faces' terms of A x
 hipError_t launch_hang_geometry(hx_ctx *c);

@@ -44,6 +44,7 @@
 //    columns swept layer by layer, in one contiguous range per XCD, so the
 //    neighbours a cell reads were touched recently by the same XCD's L2.
 #include "common.hpp"
+#include "bj_cell.hpp"
 
 #include <type_traits>
 
@@ -220,18 +221,30 @@ __device__ __forceinline__ void load_values(const T *__restrict__ p, T (&v)[K])
     for (int i = K / W * W; i < K; ++i) v[i] = p[i];
 }
 
+// One step of the Chebyshev iteration around the block Jacobi (CHEB; see
+// k_bj): d = ca M^-1 (b - A x) + cb d (d read only with read_d), xo = x + d,
+// with S, L, C the cells' separable block
+template <typename T>
+struct ChebArgs {
+    const T *S, *L, *C;
+    T *d, *xo;
+    T ca, cb;
+    int read_d;
+};
+
 // PART: 0 the whole operator, 1 the cell integrals only, 2 the face terms only;
 // AFF: the wave serves affine cells (compressed cell data; faces compressed
 // where the record's mask says so) or general cells (general data only)
-template <int N, typename T, bool DOT, int PART, bool AFF>
+template <int N, typename T, bool DOT, int PART, bool AFF, bool CHEB = false>
 __device__ __forceinline__ void apply_body(
     const T *__restrict__ x, T *__restrict__ y, const T *__restrict__ bvec,
     const T *__restrict__ cell, const T *__restrict__ face, const T *__restrict__ acell,
     const T *__restrict__ kk, const T *__restrict__ aface, const T *__restrict__ fcon,
     const int32_t *__restrict__ visit, int n_cells, int wg, int bid, double *__restrict__ dpart,
     T (&sU)[Cfg<N>::CPW][Cfg<N>::ND], T (&sG)[Cfg<N>::CPW][Cfg<N>::GS],
-    T (&sXd)[DOT ? Cfg<N>::CPW : 1][DOT ? Cfg<N>::ND : 1])
+    T (&sXd)[DOT ? Cfg<N>::CPW : 1][DOT ? Cfg<N>::ND : 1], const ChebArgs<T> &ch = {})
 {
+    static_assert(!CHEB || (PART == 0 && !DOT), "a Chebyshev step needs the whole residual");
     constexpr bool DO_CELL = PART != 2, DO_FACE = PART != 1;
     constexpr int NF = Cfg<N>::NF, ND = Cfg<N>::ND, LPC = Cfg<N>::LPC, CPW = Cfg<N>::CPW;
 
@@ -320,6 +333,8 @@ __device__ __forceinline__ void apply_body(
     __syncthreads();
 
     T Y[N];
+    constexpr int NLS = (3 * N + NF - 1) / NF;   // eigenvalue loads per lane
+    T chb[CHEB ? N : 1], chx[CHEB ? N : 1], chd[CHEB ? N : 1], chS[3], chL[NLS], chC = 0;
     // =========================================================== cell part
     // x sweep: lane (j=a, l=b): B u and BD u along x
     if constexpr (!DO_CELL) {
@@ -693,6 +708,25 @@ __device__ __forceinline__ void apply_body(
         }
     }
     __syncthreads();
+    // Chebyshev step: what its end needs is requested here, in the order in
+    // which the lanes of a cell keep it (values N^2 apart)
+    if (CHEB && cl) {
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int64_t gi = cid * ND + ln + u * NF;
+            chb[u] = bvec[gi];
+            chx[u] = x[gi];
+            chd[u] = ch.read_d ? ch.d[gi] : T(0);
+        }
+#pragma unroll
+        for (int u = 0; u < 3; ++u) chS[u] = ch.S[cid * 3 * NF + ln + u * NF];
+#pragma unroll
+        for (int u = 0; u < NLS; ++u) {
+            const int e = ln + u * NF;
+            chL[u] = e < 3 * N ? ch.L[cid * 3 * N + e] : T(0);
+        }
+        if (ln < 4) chC = ch.C[cid * 4 + ln];
+    }
     // step 4, lane (f, p): transposed sweep along the second direction, in
     // place: layer weights (F0) and normal-derivative weights (F1) of column p
     // in fields 0 and 1, [field][r][p]
@@ -760,9 +794,43 @@ __device__ __forceinline__ void apply_body(
             for (int i = 0; i < N; ++i) Y[i] += e1 * F1[i] + (on ? F0[i] : T(0));
         }
         }   // DO_FACE
-        const int64_t o = cid * ND + N * a + NF * b;
+        if constexpr (CHEB) {
 #pragma unroll
-        for (int i = 0; i < N; ++i) y[o + i] = bvec ? bvec[o + i] - Y[i] : Y[i];
+            for (int i = 0; i < N; ++i) U[i + N * a + NF * b] = Y[i];
+        } else {
+            const int64_t o = cid * ND + N * a + NF * b;
+#pragma unroll
+            for (int i = 0; i < N; ++i) y[o + i] = bvec ? bvec[o + i] - Y[i] : Y[i];
+        }
+    }
+    if constexpr (CHEB) {
+        // the residual in U and the block's matrices in the work area, whose
+        // face contributions are read by now
+        T *sS = G, *sL = G + 3 * NF, *sC = sL + 3 * N;
+        __syncthreads();
+        if (cl) {
+#pragma unroll
+            for (int u = 0; u < N; ++u) U[ln + u * NF] = chb[u] - U[ln + u * NF];
+#pragma unroll
+            for (int u = 0; u < 3; ++u) sS[ln + u * NF] = chS[u];
+#pragma unroll
+            for (int u = 0; u < NLS; ++u)
+                if (ln + u * NF < 3 * N) sL[ln + u * NF] = chL[u];
+            if (ln < 4) sC[ln] = chC;
+        }
+        __syncthreads();
+        double rz = 0.0;
+        bj_cell_solve<N, T, true>(U, (const T(*)[NF])sS, (const T(*)[N])sL, sC, a, b, cl, rz);
+        if (cl) {
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                const int64_t gi = cid * ND + ln + u * NF;
+                T dn = ch.ca * U[ln + u * NF];
+                if (ch.read_d) dn += ch.cb * chd[u];
+                ch.d[gi] = dn;
+                ch.xo[gi] = chx[u] + dn;
+            }
+        }
     }
     // x.(A x) of the wave's cells (fixed-order wave sum), for CG's p.q; the
     // lane's input pencil comes from the copy of the input cells kept in LDS
@@ -815,6 +883,55 @@ k_apply(const T *__restrict__ x, T *__restrict__ y, const T *__restrict__ bvec,
         apply_body<N, T, DOT, PART, MODE == 1>(x, y, bvec, cell, face, acell, kk, aface, fcon, visit,
                                                n_cells, wg, bid, dpart, sU, sG, sXd);
     }
+}
+
+// One smoothing step in one launch: the residual b - A x as in k_apply, each
+// wave then solves its cells' blocks and forms d and xo (another buffer than x,
+// which the neighbours still read).
+// A wave has its cells' residuals in the lanes that the cell solve wants them
+// in, so the residual's way through memory and a launch are saved and the
+// solve's work hides behind the operator's loads.  One step at degree 4,
+// operator and block Jacobi / this kernel: 64x32x32 cells 110.6 + 34.2 / 128.3
+// us, 32x16x16 19.2 + 8.2 / 23.0, 16x8x8 7.6 + 4.7 / 9.0.  FP32 only: the FP64
+// operator already uses all of its registers.
+template <int N, typename T, int MODE>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MODE ? Occ<N, T>::WA : Occ<N, T>::W,
+                                                                         MODE ? Occ<N, T>::WA : Occ<N, T>::W)))
+k_apply_cheb(const T *__restrict__ x, const T *__restrict__ bvec, const T *__restrict__ cell,
+             const T *__restrict__ face, const T *__restrict__ acell, const T *__restrict__ kk,
+             const T *__restrict__ aface, const T *__restrict__ fcon,
+             const int32_t *__restrict__ visit, int n_cells, int nwg, ChebArgs<T> ch)
+{
+    constexpr int ND = Cfg<N>::ND, CPW = Cfg<N>::CPW, GS = Cfg<N>::GS;
+    static_assert(GS >= 3 * N * N + 3 * N + 4, "the block's matrices fit in the work area");
+    __shared__ T sU[CPW][ND];
+    __shared__ T sG[CPW][GS];
+    __shared__ T none[1][1];
+    const int bid = blockIdx.x;
+    const int q8 = nwg / NXCD, r8 = nwg % NXCD, xcd = bid % NXCD;
+    const int wg = xcd * q8 + (xcd < r8 ? xcd : r8) + bid / NXCD;
+    T *const y = nullptr;
+    double *const dpart = nullptr;
+    if (MODE == 2 ? (visit[(int64_t)wg * CPW * 8 + 7] & 1) : MODE == 1)
+        apply_body<N, T, false, 0, true, true>(x, y, bvec, cell, face, acell, kk, aface, fcon, visit,
+                                               n_cells, wg, bid, dpart, sU, sG, none, ch);
+    else
+        apply_body<N, T, false, 0, false, true>(x, y, bvec, cell, face, acell, kk, aface, fcon, visit,
+                                                n_cells, wg, bid, dpart, sU, sG, none, ch);
+}
+
+template <int N>
+hipError_t apply_cheb_n(hx_ctx *c, const float *x, const float *b, const ChebArgs<float> &ch)
+{
+    const int cpw = Cfg<N>::CPW, nrec = (int)c->n_vis_op, nwg = (nrec + cpw - 1) / cpw;
+#define HX_CHEB(MODE)                                                                            \
+    hipLaunchKernelGGL((k_apply_cheb<N, float, MODE>), dim3(nwg), dim3(64), 0, c->stream, x, b,  \
+                       c->cell32, c->face32, c->acell32, c->kk32, c->aface32, c->fc32, c->visit, nrec, nwg, ch)
+    if (c->vis_mode == 2) HX_CHEB(2);
+    else if (c->vis_mode == 1) HX_CHEB(1);
+    else HX_CHEB(0);
+#undef HX_CHEB
+    return hipGetLastError();
 }
 
 template <int N, typename T>
@@ -892,6 +1009,23 @@ hipError_t launch_apply64(hx_ctx *c, const double *x, double *y, const double *b
 hipError_t launch_apply32(hx_ctx *c, const float *x, float *y, const float *b)
 {
     return apply_dispatch<float>(c, x, y, b);
+}
+
+hipError_t launch_apply32_cheb(hx_ctx *c, const float *x, const float *b, float *xo, float *d, double ca,
+                               double cb, int read_d)
+{
+    if (c->n_hang) return hipErrorInvalidValue;
+    const ChebArgs<float> ch{c->bjS32, c->bjL32, c->bjC32, d, xo, (float)ca, (float)cb, read_d};
+    switch (c->n) {
+    case 2: return apply_cheb_n<2>(c, x, b, ch);
+    case 3: return apply_cheb_n<3>(c, x, b, ch);
+    case 4: return apply_cheb_n<4>(c, x, b, ch);
+    case 5: return apply_cheb_n<5>(c, x, b, ch);
+    case 6: return apply_cheb_n<6>(c, x, b, ch);
+    case 7: return apply_cheb_n<7>(c, x, b, ch);
+    case 8: return apply_cheb_n<8>(c, x, b, ch);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_apply_part64(hx_ctx *c, int part, const double *x, double *y)

@@ -802,6 +802,12 @@ hipError_t cheb_iterate64(hx_ctx *c, const double *b, double *x, bool x_zero)
 
 hipError_t cheb_apply64(hx_ctx *c, const double *r, double *z) { return cheb_iterate64(c, r, z, true); }
 
+// On conforming meshes a step's residual, cell solve and update are one
+// launch, which writes the new iterate into another buffer than the one it
+// reads (the residual's, not needed then): an even number of such steps ends
+// in x.  From zero the first step, which has no residual, starts in the
+// buffer that makes it so; from a given x an odd count leaves the first step
+// to the two kernels, which update x in place.
 hipError_t cheb_iterate32(hx_ctx *c, const float *b, float *x, bool x_zero)
 {
     const int64_t n = c->n_dofs;
@@ -809,17 +815,28 @@ hipError_t cheb_iterate32(hx_ctx *c, const float *b, float *x, bool x_zero)
     const double theta = 0.5 * (c->cheb_hi + c->cheb_lo), delta = 0.5 * (c->cheb_hi - c->cheb_lo);
     const double sigma = theta / delta;
     double rho = 1.0 / sigma;
+    const bool fused = c->n_hang == 0;
+    float *cur = x, *other = res;
     hipError_t e = hipSuccess;
-    const float *v = b;
-    if (!x_zero) {
+    if (x_zero) {
+        if (fused && c->cheb_deg % 2 == 0) std::swap(cur, other);
+        e = launch_bj_cheb32(c, b, d, cur, 1.0 / theta, 0.0, 0, 0);
+    } else if (fused && c->cheb_deg % 2 == 0) {
+        e = launch_apply32_cheb(c, cur, b, other, d, 1.0 / theta, 0.0, 0);
+        std::swap(cur, other);
+    } else {
         e = launch_apply32(c, x, res, b);
-        v = res;
+        if (e == hipSuccess) e = launch_bj_cheb32(c, res, d, x, 1.0 / theta, 0.0, 0, 1);
     }
-    if (e == hipSuccess) e = launch_bj_cheb32(c, v, d, x, 1.0 / theta, 0.0, 0, !x_zero);
     for (int k = 1; k < c->cheb_deg && e == hipSuccess; ++k) {
         const double rn = 1.0 / (2.0 * sigma - rho);
-        e = launch_apply32(c, x, res, b);
-        if (e == hipSuccess) e = launch_bj_cheb32(c, res, d, x, 2.0 * rn / delta, rn * rho, 1, 1);
+        if (fused) {
+            e = launch_apply32_cheb(c, cur, b, other, d, 2.0 * rn / delta, rn * rho, 1);
+            std::swap(cur, other);
+        } else {
+            e = launch_apply32(c, x, res, b);
+            if (e == hipSuccess) e = launch_bj_cheb32(c, res, d, x, 2.0 * rn / delta, rn * rho, 1, 1);
+        }
         rho = rn;
     }
     return e;

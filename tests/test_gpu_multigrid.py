@@ -223,3 +223,40 @@ def test_multigrid_errors():
     cc.close()
     assert status(lambda: cf.mg_transfer(0, b, b.clone())) == hx.HX_ERR_STATE
     _close([cf, co])
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 6, 7])
+@pytest.mark.parametrize("mesh", ["terrain", "general", "cube"])
+def test_single_precision_smoothing_steps(mesh, k):
+    """The FP32 cycle, whose smoothing steps are one launch each on two
+    buffers in turn, against the FP64 cycle of the same levels: Chebyshev
+    degrees of both parities (from zero and from a given iterate), on meshes
+    with affine and general cells, general ones only and affine ones only.
+    Tolerance: 2e-6 per FP32 operator application (its own test), at most 18
+    of them, times 5 for the cell solves: 2e-4; a step on the wrong iterate is
+    off by 1e-2 and more."""
+    hx = _hx()
+    if mesh == "cube":
+        fine, coarse = si.cube_mesh(4), si.cube_mesh(2)
+        parent, octant = si.refinement_parents(2, 2, 2)
+        coef = "const"
+    else:
+        fine, coarse = si.terrain_mesh(14, 2, 6, g=2), si.terrain_mesh(7, 1, 3, g=2)
+        parent, octant = si.refinement_parents(7, 1, 3)
+        coef = "terrain"
+    ctxs = [gpu_context(problem(m, k, coef=coef)) for m in (fine, coarse)]
+    try:
+        b = [to_dev(si.random_vector(c.n_dofs, 90 + k)) for c in ctxs]
+        for c in ctxs:
+            c.set_cell_compression(mesh != "general")
+        bounds = [c.estimate_eigenvalues(v, 15) for c, v in zip(ctxs, b)]
+        ctxs[0].set_multigrid(ctxs[1], parent, octant)
+        for degree in (1, 2, 3, 4):
+            print(f"[mg32] {mesh} k={k} degree={degree}", flush=True)
+            for c, (lo, hi) in zip(ctxs, bounds):
+                c.set_chebyshev(degree, 1.1 * hi / 15.0, 1.1 * hi)
+            z = [ctxs[0].apply_preconditioner(b[0], kind=kind).cpu().numpy()
+                 for kind in (hx.HX_PC_MULTIGRID, hx.HX_PC_MULTIGRID_MIXED)]
+            assert np.linalg.norm(z[1] - z[0]) <= 2e-4 * np.linalg.norm(z[0])
+    finally:
+        _close(ctxs)
