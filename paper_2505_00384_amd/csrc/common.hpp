@@ -41,6 +41,8 @@ struct RefTab64 {
     double Binv[MAXN * MAXN];              // Binv[i*n+q]: inverse of B (n points = n nodes)
     double Eh[2][MAXN * MAXN];             // Eh[o][i*n+j] = l_j((o + xl_i)/2): the basis at the
                                            // nodes of the lower (o = 0) or upper half interval
+    double Bh[2][2][MAXN * MAXN];          // Bh[o][0][q*n+i] = l_i((o + xq_q)/2), Bh[o][1] = l_i':
+                                           // the basis at the points of a half interval
 };
 
 void sym_eig(int n, double *a, double *w, double *v);

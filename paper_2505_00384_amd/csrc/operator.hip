@@ -45,6 +45,7 @@
 //    neighbours a cell reads were touched recently by the same XCD's L2.
 #include "common.hpp"
 #include "bj_cell.hpp"
+#include "hang_quarter.hpp"
 
 #include <type_traits>
 
@@ -885,6 +886,56 @@ k_apply(const T *__restrict__ x, T *__restrict__ y, const T *__restrict__ bvec,
     }
 }
 
+// The operator of a mesh with 2:1 faces: the first nhp workgroups (the
+// quarters, filled up to whole rounds of the XCDs) compute the quarters'
+// contributions into the staging buffer, one each, the others the conforming
+// part.  The quarters need x only; for 32x8x16 cells refined over the ridge,
+// degree 4, they took 7.8 of 46.9 us in a launch of their own after it, and
+// all takes 40.9 us now.
+template <typename T>
+struct HangArgs {
+    const int32_t *hang;
+    const RefTab64 *ref;
+    const T *hd;
+    T *contrib;
+    int n_hang, nhp;
+};
+
+template <int N, typename T, int MODE>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MODE ? Occ<N, T>::WA : Occ<N, T>::W,
+                                                                         MODE ? Occ<N, T>::WA : Occ<N, T>::W)))
+k_apply_hang(const T *__restrict__ x, T *__restrict__ y, const T *__restrict__ bvec,
+             const T *__restrict__ cell, const T *__restrict__ face, const T *__restrict__ acell,
+             const T *__restrict__ kk, const T *__restrict__ aface, const T *__restrict__ fcon,
+             const int32_t *__restrict__ visit, int n_cells, int nwg, HangArgs<T> hg)
+{
+    constexpr int ND = Cfg<N>::ND, CPW = Cfg<N>::CPW, GS = Cfg<N>::GS;
+    struct Cells {
+        T U[CPW][ND], G[CPW][GS];
+    };
+    union Lds {
+        Cells c;
+        HangLds<N, T> h;
+    };
+    __shared__ Lds sh;
+    __shared__ T none[1][1];
+    if ((int)blockIdx.x < hg.nhp) {
+        if ((int)blockIdx.x < hg.n_hang)
+            hang_quarter<N, T>(blockIdx.x, hg.hang, hg.ref, hg.hd, x, hg.contrib, sh.h);
+        return;
+    }
+    const int bid = blockIdx.x - hg.nhp;
+    const int q8 = nwg / NXCD, r8 = nwg % NXCD, xcd = bid % NXCD;
+    const int wg = xcd * q8 + (xcd < r8 ? xcd : r8) + bid / NXCD;
+    double *const dpart = nullptr;
+    if (MODE == 2 ? (visit[(int64_t)wg * CPW * 8 + 7] & 1) : MODE == 1)
+        apply_body<N, T, false, 0, true>(x, y, bvec, cell, face, acell, kk, aface, fcon, visit, n_cells,
+                                         wg, bid, dpart, sh.c.U, sh.c.G, none);
+    else
+        apply_body<N, T, false, 0, false>(x, y, bvec, cell, face, acell, kk, aface, fcon, visit, n_cells,
+                                          wg, bid, dpart, sh.c.U, sh.c.G, none);
+}
+
 // One smoothing step in one launch: the residual b - A x as in k_apply, each
 // wave then solves its cells' blocks and forms d and xo (another buffer than x,
 // which the neighbours still read).
@@ -948,6 +999,21 @@ hipError_t apply_n(hx_ctx *c, const T *x, T *y, const T *b, double *dpart, int *
     const int64_t nrec = c->n_vis_op;
     const int nwg = (int)((nrec + cpw - 1) / cpw);
     if (nwg_out) *nwg_out = nwg;
+    if constexpr (hang_in_operator(N)) {
+    if (c->n_hang && part == 0) {
+        const HangArgs<T> hg{c->hang, c->ref, F64 ? (const T *)c->hdata64 : (const T *)c->hdata32,
+                             F64 ? (T *)c->hcontrib64 : (T *)c->hcontrib32, (int)c->n_hang,
+                             (int)((c->n_hang + NXCD - 1) / NXCD * NXCD)};
+#define HX_HANG(MODE)                                                                                 \
+    hipLaunchKernelGGL((k_apply_hang<N, T, MODE>), dim3(hg.nhp + nwg), dim3(64), 0, c->stream, x, y, b, \
+                       cell, face, acell, kk, aface, fcon, c->visit, (int)nrec, nwg, hg)
+        if (c->vis_mode == 2) HX_HANG(2);
+        else if (c->vis_mode == 1) HX_HANG(1);
+        else HX_HANG(0);
+#undef HX_HANG
+        return hipGetLastError();
+    }
+    }
 #define HX_APPLY(DOT, PART, MODE)                                                                \
     hipLaunchKernelGGL((k_apply<N, T, DOT, PART, MODE>), dim3(nwg), dim3(64), 0, c->stream, x, y, b, \
                        cell, face, acell, kk, aface, fcon, c->visit, (int)nrec, nwg, dpart)
@@ -984,8 +1050,8 @@ hipError_t apply_conforming(hx_ctx *c, const T *x, T *y, const T *b, double *dpa
     }
 }
 
-// the operator, then the terms of the non-conforming quarter faces (face
-// part); with quarter faces the fused x.(A x) of the CG variant is not used
+// the operator, with the terms of the non-conforming quarter faces in its
+// launch or in one of their own, and their addition after it; with quarter faces the fused x.(A x) of the CG variant is not used
 // (the callers take the dot product after the whole operator)
 template <typename T>
 hipError_t apply_dispatch(hx_ctx *c, const T *x, T *y, const T *b, double *dpart = nullptr,
@@ -993,10 +1059,11 @@ hipError_t apply_dispatch(hx_ctx *c, const T *x, T *y, const T *b, double *dpart
 {
     hipError_t e = apply_conforming<T>(c, x, y, b, dpart, nwg, part);
     if (e != hipSuccess || c->n_hang == 0 || part == 1) return e;
+    const bool own = part != 0 || !hang_in_operator(c->n);   // the quarters' own launch
     if constexpr (sizeof(T) == 8)
-        return launch_hang_apply64(c, (const double *)x, (double *)y, b != nullptr);
+        return launch_hang_apply64(c, own ? (const double *)x : nullptr, (double *)y, b != nullptr);
     else
-        return launch_hang_apply32(c, (const float *)x, (float *)y, b != nullptr);
+        return launch_hang_apply32(c, own ? (const float *)x : nullptr, (float *)y, b != nullptr);
 }
 
 }  // namespace

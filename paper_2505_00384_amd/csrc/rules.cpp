@@ -184,6 +184,9 @@ void build_ref_tables(int n, RefTab64 &t)
             t.BD[q * n + i] = d[i];
         }
     }
+    for (int o = 0; o < 2; ++o)
+        for (int q = 0; q < n; ++q)
+            lagrange_eval(n, t.xl, 0.5 * (o + t.xq[q]), t.Bh[o][0] + q * n, t.Bh[o][1] + q * n);
     for (int e = 0; e < 2; ++e) {
         lagrange_eval(n, xl, e ? 1.0 : 0.0, v, d);
         for (int i = 0; i < n; ++i) t.DL[e][i] = d[i];

@@ -174,3 +174,28 @@ def test_hanging_setup_errors_and_unsupported_features():
     assert np.linalg.norm(ctx.apply_preconditioner(to_dev(x)).cpu().numpy() - p3.bj_apply(x)) <= \
         1e-11 * np.linalg.norm(p3.bj_apply(x))
     ctx.close()
+
+
+@pytest.mark.parametrize("k", [4, 5, 6, 7])
+@pytest.mark.parametrize("mesh", [0, 1, 3])
+def test_hanging_operator_high_degrees(mesh, k):
+    """The quarters in the operator's launch and in one of their own (from
+    degree 6), with one and two rounds of items per wave, on affine and
+    general cells and with the compression off: the tolerances of the parity
+    test above."""
+    hx = _hx()
+    name, mk = MESHES[mesh]
+    p = problem(mk(), k, coef="terrain" if name.startswith("terrain") else "random", seed=k)
+    print(f"[hanging] k={k} mesh={name}", flush=True)
+    ctx = gpu_context(p)
+    x = si.random_vector(p.n_dofs, 140 + k)
+    b = si.random_vector(p.n_dofs, 150 + k)
+    ref = p.apply(x)
+    for compress in (True, False):
+        ctx.set_cell_compression(compress)
+        _check(ctx.apply_operator(to_dev(x)).cpu().numpy(), ref)
+        y32 = ctx.apply_operator(to_dev(x.astype(np.float32))).cpu().numpy()
+        assert np.linalg.norm(y32 - ref) <= 2e-6 * np.linalg.norm(ref)
+    _check(ctx.residual(to_dev(b), to_dev(x)).cpu().numpy(), b - ref)
+    _check(ctx.apply_operator_part(hx.HX_PART_FACE, to_dev(x)).cpu().numpy(), p.apply(x, oracle.OR_FACE))
+    ctx.close()
