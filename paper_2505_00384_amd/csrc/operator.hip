@@ -234,22 +234,35 @@ struct ChebArgs {
 };
 
 // PART: 0 the whole operator, 1 the cell integrals only, 2 the face terms only;
+// ROLE: 0 the wave does all of it; 1 the cell integrals, and at the end, past a
+// barrier, everything after the faces, whose contributions it finds in sF; 2
+// the face terms, up to that barrier (before it only the order of a wave's own
+// LDS accesses matters);
 // AFF: the wave serves affine cells (compressed cell data; faces compressed
 // where the record's mask says so) or general cells (general data only)
-template <int N, typename T, bool DOT, int PART, bool AFF, bool CHEB = false>
+template <int N, typename T, bool DOT, int PART, bool AFF, bool CHEB = false, int ROLE = 0>
 __device__ __forceinline__ void apply_body(
     const T *__restrict__ x, T *__restrict__ y, const T *__restrict__ bvec,
     const T *__restrict__ cell, const T *__restrict__ face, const T *__restrict__ acell,
     const T *__restrict__ kk, const T *__restrict__ aface, const T *__restrict__ fcon,
     const int32_t *__restrict__ visit, int n_cells, int wg, int bid, double *__restrict__ dpart,
     T (&sU)[Cfg<N>::CPW][Cfg<N>::ND], T (&sG)[Cfg<N>::CPW][Cfg<N>::GS],
-    T (&sXd)[DOT ? Cfg<N>::CPW : 1][DOT ? Cfg<N>::ND : 1], const ChebArgs<T> &ch = {})
+    T (&sXd)[DOT ? Cfg<N>::CPW : 1][DOT ? Cfg<N>::ND : 1], const ChebArgs<T> &ch = {},
+    T (*sF)[Cfg<N>::GS] = nullptr)
 {
     static_assert(!CHEB || (PART == 0 && !DOT), "a Chebyshev step needs the whole residual");
-    constexpr bool DO_CELL = PART != 2, DO_FACE = PART != 1;
+    constexpr bool DO_CELL = PART != 2 && ROLE != 2, DO_FACE = PART != 1 && ROLE != 1;
+    static_assert(ROLE == 0 || PART == 0, "roles share the whole operator");
+    // (a one-wave workgroup's barrier costs nothing)
+    auto sync = [] {
+        if constexpr (ROLE == 0) __syncthreads();
+        else lds_wave_sync();
+    };
     constexpr int NF = Cfg<N>::NF, ND = Cfg<N>::ND, LPC = Cfg<N>::LPC, CPW = Cfg<N>::CPW;
 
-    const int lane = threadIdx.x;
+    // (the mask in the one-wave form too changes the compiler's schedule for
+    // the worse: 49 / 53 us for 16x16x16 affine cells, N = 8, FP64)
+    const int lane = ROLE == 0 ? threadIdx.x : (threadIdx.x & 63);
     const int cs = lane / LPC;             // cell slot in the wave
     const int ln = lane - cs * LPC;        // lane within the cell
     const int slot = wg * CPW + cs;
@@ -318,7 +331,7 @@ __device__ __forceinline__ void apply_body(
         const int e = ln + k * LPC;
         if (valid && e < ND) {
             U[e] = xv[k];
-            if constexpr (DOT) sXd[cs][e] = xv[k];   // kept for x.(A x)
+            if constexpr (DOT && ROLE != 2) sXd[cs][e] = xv[k];   // kept for x.(A x)
         }
     }
 
@@ -331,11 +344,33 @@ __device__ __forceinline__ void apply_body(
 #pragma unroll
         for (int s2 = 0; s2 < 6; ++s2) kq[s2] = kk[cid * 8 + s2];
     }
-    __syncthreads();
+    sync();
 
     T Y[N];
     constexpr int NLS = (3 * N + NF - 1) / NF;   // eigenvalue loads per lane
     T chb[CHEB ? N : 1], chx[CHEB ? N : 1], chd[CHEB ? N : 1], chS[3], chL[NLS], chC = 0;
+    // Chebyshev step: what its end needs is requested ahead, in the order in
+    // which the lanes of a cell keep it (values N^2 apart)
+    auto request_cheb = [&] {
+        if constexpr (CHEB) {
+        if (!cl) return;
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int64_t gi = cid * ND + ln + u * NF;
+            chb[u] = bvec[gi];
+            chx[u] = x[gi];
+            chd[u] = ch.read_d ? ch.d[gi] : T(0);
+        }
+#pragma unroll
+        for (int u = 0; u < 3; ++u) chS[u] = ch.S[cid * 3 * NF + ln + u * NF];
+#pragma unroll
+        for (int u = 0; u < NLS; ++u) {
+            const int e = ln + u * NF;
+            chL[u] = e < 3 * N ? ch.L[cid * 3 * N + e] : T(0);
+        }
+        if (ln < 4) chC = ch.C[cid * 4 + ln];
+        }
+    };
     // =========================================================== cell part
     // x sweep: lane (j=a, l=b): B u and BD u along x
     if constexpr (!DO_CELL) {
@@ -356,7 +391,7 @@ __device__ __forceinline__ void apply_body(
             G[ND + q + N * a + NF * b] = s1[q];
         }
     }
-    __syncthreads();
+    sync();
     // quadrature-point data, requested before the y sweep so that the
     // stream is in flight while it runs
     T cdat[7][N];
@@ -388,7 +423,7 @@ __device__ __forceinline__ void apply_body(
             contract<T, N, 1, false>(x0, c1);
             contract<T, N, 0, false>(x1, c2);
         }
-        __syncthreads();
+        sync();
         if (cl) {
 #pragma unroll
             for (int q = 0; q < N; ++q) {
@@ -398,7 +433,7 @@ __device__ __forceinline__ void apply_body(
             }
         }
     }
-    __syncthreads();
+    sync();
     // z sweep, quadrature-point operation and transposed z sweep: lane (qx=a, qy=b)
     {
         T t0[N], t1[N], t2[N];
@@ -449,7 +484,7 @@ __device__ __forceinline__ void apply_body(
             contract<T, N, 0, true>(EvenOdd<T, N>(fyq), t1);
             contract<T, N, 0, true>(EvenOdd<T, N>(fxq), t2);
         }
-        __syncthreads();
+        sync();
         if (cl) {
 #pragma unroll
             for (int l = 0; l < N; ++l) {
@@ -459,7 +494,7 @@ __device__ __forceinline__ void apply_body(
             }
         }
     }
-    __syncthreads();
+    sync();
     // transposed y sweep: lane (qx=a, l=b)
     {
         T s0v[N], s1v[N];
@@ -474,7 +509,7 @@ __device__ __forceinline__ void apply_body(
             contract_t2<T, N>(p0, p1, s0v);
             contract<T, N, 0, true>(EvenOdd<T, N>(p2), s1v);
         }
-        __syncthreads();
+        sync();
         if (cl) {
 #pragma unroll
             for (int j = 0; j < N; ++j) {
@@ -483,7 +518,7 @@ __device__ __forceinline__ void apply_body(
             }
         }
     }
-    __syncthreads();
+    sync();
     // transposed x sweep: lane (j=a, l=b) keeps its output pencil in Y
     if (cl) {
         T p0[N], p1[N];
@@ -494,7 +529,7 @@ __device__ __forceinline__ void apply_body(
         }
         contract_t2<T, N>(p0, p1, Y);
     }
-    __syncthreads();
+    sync();
     }   // DO_CELL
 
     // =========================================================== face part
@@ -590,7 +625,7 @@ __device__ __forceinline__ void apply_body(
         }
     }
     if (fl) interp_t2(Ln, Nn);
-    __syncthreads();
+    sync();
     // step 2, neighbour side, lane (f, q2): flux and value at (q1, q2)
     T fnb[N], vnb[N];
     if (fl) {
@@ -621,7 +656,7 @@ __device__ __forceinline__ void apply_body(
                 fnb[q1] = gnb[0][q1] * dnn[q1] + gnb[1][q1] * t1n[q1] + gnb[2][q1] * t2n[q1];
         }
     }
-    __syncthreads();
+    sync();
     // step 1, own side, lane (f, p): layer and normal derivative from the
     // values in LDS
     if (fl) {
@@ -640,9 +675,9 @@ __device__ __forceinline__ void apply_body(
         }
         interp_t2(Lo, No);
     }
-    __syncthreads();
+    sync();
     // the own values are no longer needed: the output pencils wait in sU
-    if (cl) {
+    if (ROLE == 0 && cl) {
 #pragma unroll
         for (int i = 0; i < N; ++i) sU[cs][i + N * a + NF * b] = Y[i];
     }
@@ -708,26 +743,8 @@ __device__ __forceinline__ void apply_body(
             gf[2 * NF + rr * N + p] = A2[p];
         }
     }
-    __syncthreads();
-    // Chebyshev step: what its end needs is requested here, in the order in
-    // which the lanes of a cell keep it (values N^2 apart)
-    if (CHEB && cl) {
-#pragma unroll
-        for (int u = 0; u < N; ++u) {
-            const int64_t gi = cid * ND + ln + u * NF;
-            chb[u] = bvec[gi];
-            chx[u] = x[gi];
-            chd[u] = ch.read_d ? ch.d[gi] : T(0);
-        }
-#pragma unroll
-        for (int u = 0; u < 3; ++u) chS[u] = ch.S[cid * 3 * NF + ln + u * NF];
-#pragma unroll
-        for (int u = 0; u < NLS; ++u) {
-            const int e = ln + u * NF;
-            chL[u] = e < 3 * N ? ch.L[cid * 3 * N + e] : T(0);
-        }
-        if (ln < 4) chC = ch.C[cid * 4 + ln];
-    }
+    sync();
+    if constexpr (CHEB && ROLE == 0) request_cheb();
     // step 4, lane (f, p): transposed sweep along the second direction, in
     // place: layer weights (F0) and normal-derivative weights (F1) of column p
     // in fields 0 and 1, [field][r][p]
@@ -753,14 +770,21 @@ __device__ __forceinline__ void apply_body(
             for (int r = 0; r < N; ++r) gf[r * N + rr] = gf[NF + r * N + rr] = 0;
         }
     }
-    __syncthreads();
+    sync();
     }   // DO_FACE
+    if constexpr (ROLE != 0) {
+        // the face wave's contributions are in its work area
+        if constexpr (CHEB && ROLE == 1) request_cheb();
+        __syncthreads();
+        if constexpr (ROLE == 2) return;
+    }
     // pencil owners (j=a, l=b) add the six faces' contributions
     if (cl) {
-        if constexpr (DO_FACE) {
+        if constexpr (DO_FACE || ROLE == 1) {
+        if constexpr (ROLE == 0)
 #pragma unroll
-        for (int i = 0; i < N; ++i) Y[i] = sU[cs][i + N * a + NF * b];
-        const T *F = G;
+            for (int i = 0; i < N; ++i) Y[i] = sU[cs][i + N * a + NF * b];
+        const T *F = ROLE == 0 ? G : &sF[cs][0];
         // x faces: normal coordinate i, (p, r) = (j, l)
 #pragma unroll
         for (int sx = 0; sx < 2; ++sx) {
@@ -808,7 +832,7 @@ __device__ __forceinline__ void apply_body(
         // the residual in U and the block's matrices in the work area, whose
         // face contributions are read by now
         T *sS = G, *sL = G + 3 * NF, *sC = sL + 3 * N;
-        __syncthreads();
+        sync();
         if (cl) {
 #pragma unroll
             for (int u = 0; u < N; ++u) U[ln + u * NF] = chb[u] - U[ln + u * NF];
@@ -819,7 +843,7 @@ __device__ __forceinline__ void apply_body(
                 if (ln + u * NF < 3 * N) sL[ln + u * NF] = chL[u];
             if (ln < 4) sC[ln] = chC;
         }
-        __syncthreads();
+        sync();
         double rz = 0.0;
         bj_cell_solve<N, T, true>(U, (const T(*)[NF])sS, (const T(*)[N])sL, sC, a, b, cl, rz);
         if (cl) {
@@ -885,6 +909,57 @@ k_apply(const T *__restrict__ x, T *__restrict__ y, const T *__restrict__ bvec,
                                                n_cells, wg, bid, dpart, sU, sG, sXd);
     }
 }
+
+// Two waves per workgroup: the cell integrals and the face terms of the same
+// cells side by side, joined at one barrier before the first wave adds the
+// faces and stores (CHEB: and does the Chebyshev step).  What a wave computes
+// is half as long a chain, at twice the waves and with the own values read
+// twice: for launches that cannot fill the chip with the one-wave form
+// (SPLIT_MAX below).
+template <int N, typename T, bool DOT, int MODE, bool CHEB>
+__global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(MODE ? Occ<N, T>::WA : Occ<N, T>::W,
+                                                                          MODE ? Occ<N, T>::WA : Occ<N, T>::W)))
+k_apply_split(const T *__restrict__ x, T *__restrict__ y, const T *__restrict__ bvec,
+              const T *__restrict__ cell, const T *__restrict__ face, const T *__restrict__ acell,
+              const T *__restrict__ kk, const T *__restrict__ aface, const T *__restrict__ fcon,
+              const int32_t *__restrict__ visit, int n_cells, int nwg, double *__restrict__ dpart,
+              ChebArgs<T> ch)
+{
+    constexpr int ND = Cfg<N>::ND, CPW = Cfg<N>::CPW, GS = Cfg<N>::GS;
+    __shared__ T sU[2][CPW][ND];
+    __shared__ T sG[2][CPW][GS];
+    __shared__ T sXd[DOT ? CPW : 1][DOT ? ND : 1];
+    const int bid = blockIdx.x;
+    const int q8 = nwg / NXCD, r8 = nwg % NXCD, xcd = bid % NXCD;
+    const int wg = xcd * q8 + (xcd < r8 ? xcd : r8) + bid / NXCD;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool aff = MODE == 2 ? (visit[(int64_t)wg * CPW * 8 + 7] & 1) : MODE == 1;
+#define HX_ROLE(AFF, ROLE)                                                                              \
+    apply_body<N, T, DOT, 0, AFF, CHEB, ROLE>(x, y, bvec, cell, face, acell, kk, aface, fcon, visit, n_cells, \
+                                              wg, bid, dpart, sU[ROLE - 1], sG[ROLE - 1], sXd, ch, sG[1])
+    if (wave == 0) {
+        if constexpr (MODE != 0)
+            if (aff) HX_ROLE(true, 1);
+        if constexpr (MODE != 1)
+            if (!aff) HX_ROLE(false, 1);
+    } else {
+        if constexpr (MODE != 0)
+            if (aff) HX_ROLE(true, 2);
+        if constexpr (MODE != 1)
+            if (!aff) HX_ROLE(false, 2);
+    }
+#undef HX_ROLE
+}
+
+// The two-wave form where a launch of nwg one-wave workgroups leaves at most
+// one to a SIMD (256 CUs of 4): its time is then a single wave's chain.  One
+// wave / two, FP64, 8x8x8 cells: degree 3 6.7 / 5.8 us, 4 7.6 / 6.1, 5 10.0 /
+// 7.7, 6 12.2 / 9.3, 7 15.9 / 11.2; 16x8x8 cells, degree 6 14.3 / 11.9; FP32
+// 8x8x8 degree 4 6.4 / 6.0, 7 11.0 / 8.2.  With two waves per SIMD the one-wave
+// form catches up (degree 6, 16x16x8 cells: 21.0 / 22.0).  At degree 1, and in
+// FP32 at degree 2, the launch itself takes the time (5.1 / 6.0).
+constexpr int SPLIT_MAX = 1024;
+constexpr bool split_degree(int n, bool f64) { return n >= (f64 ? 3 : 4); }
 
 // The operator of a mesh with 2:1 faces: the first nhp workgroups (the
 // quarters, filled up to whole rounds of the XCDs) compute the quarters'
@@ -978,6 +1053,19 @@ hipError_t apply_cheb_n(hx_ctx *c, const float *x, const float *b, const ChebArg
 #define HX_CHEB(MODE)                                                                            \
     hipLaunchKernelGGL((k_apply_cheb<N, float, MODE>), dim3(nwg), dim3(64), 0, c->stream, x, b,  \
                        c->cell32, c->face32, c->acell32, c->kk32, c->aface32, c->fc32, c->visit, nrec, nwg, ch)
+#define HX_CHEB2(MODE)                                                                                   \
+    hipLaunchKernelGGL((k_apply_split<N, float, false, MODE, true>), dim3(nwg), dim3(128), 0, c->stream, \
+                       x, (float *)nullptr, b, c->cell32, c->face32, c->acell32, c->kk32, c->aface32,    \
+                       c->fc32, c->visit, nrec, nwg, (double *)nullptr, ch)
+    if constexpr (split_degree(N, false)) {
+        if (nwg <= SPLIT_MAX) {
+            if (c->vis_mode == 2) HX_CHEB2(2);
+            else if (c->vis_mode == 1) HX_CHEB2(1);
+            else HX_CHEB2(0);
+            return hipGetLastError();
+        }
+    }
+#undef HX_CHEB2
     if (c->vis_mode == 2) HX_CHEB(2);
     else if (c->vis_mode == 1) HX_CHEB(1);
     else HX_CHEB(0);
@@ -1014,6 +1102,26 @@ hipError_t apply_n(hx_ctx *c, const T *x, T *y, const T *b, double *dpart, int *
         return hipGetLastError();
     }
     }
+#define HX_SPLIT(DOT, MODE)                                                                              \
+    hipLaunchKernelGGL((k_apply_split<N, T, DOT, MODE, false>), dim3(nwg), dim3(128), 0, c->stream, x, y, b, \
+                       cell, face, acell, kk, aface, fcon, c->visit, (int)nrec, nwg, dpart, ChebArgs<T>{})
+#define HX_SPLIT_MODE(MODE)           \
+    if (dpart) HX_SPLIT(true, MODE); \
+    else HX_SPLIT(false, MODE)
+    if constexpr (split_degree(N, F64)) {
+        if (part == 0 && nwg <= SPLIT_MAX) {
+            if (c->vis_mode == 2) {
+                HX_SPLIT_MODE(2);
+            } else if (c->vis_mode == 1) {
+                HX_SPLIT_MODE(1);
+            } else {
+                HX_SPLIT_MODE(0);
+            }
+            return hipGetLastError();
+        }
+    }
+#undef HX_SPLIT_MODE
+#undef HX_SPLIT
 #define HX_APPLY(DOT, PART, MODE)                                                                \
     hipLaunchKernelGGL((k_apply<N, T, DOT, PART, MODE>), dim3(nwg), dim3(64), 0, c->stream, x, y, b, \
                        cell, face, acell, kk, aface, fcon, c->visit, (int)nrec, nwg, dpart)

@@ -225,13 +225,14 @@ def test_multigrid_errors():
     _close([cf, co])
 
 
-@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 6, 7])
-@pytest.mark.parametrize("mesh", ["terrain", "general", "cube"])
+@pytest.mark.parametrize("mesh,k", [(m, k) for m in ("terrain", "general", "cube") for k in range(1, 8)]
+                         + [("large", 4), ("large", 6)])
 def test_single_precision_smoothing_steps(mesh, k):
     """The FP32 cycle, whose smoothing steps are one launch each on two
     buffers in turn, against the FP64 cycle of the same levels: Chebyshev
     degrees of both parities (from zero and from a given iterate), on meshes
-    with affine and general cells, general ones only and affine ones only.
+    with affine and general cells, general ones only and affine ones only, and
+    on one with more than 1024 workgroups (the operator's one-wave form).
     Tolerance: 2e-6 per FP32 operator application (its own test), at most 18
     of them, times 5 for the cell solves: 2e-4; a step on the wrong iterate is
     off by 1e-2 and more."""
@@ -241,8 +242,9 @@ def test_single_precision_smoothing_steps(mesh, k):
         parent, octant = si.refinement_parents(2, 2, 2)
         coef = "const"
     else:
-        fine, coarse = si.terrain_mesh(14, 2, 6, g=2), si.terrain_mesh(7, 1, 3, g=2)
-        parent, octant = si.refinement_parents(7, 1, 3)
+        nx, ny, nz = (22, 4, 3) if mesh == "large" else (7, 1, 3)
+        fine, coarse = si.terrain_mesh(2 * nx, 2 * ny, 2 * nz, g=2), si.terrain_mesh(nx, ny, nz, g=2)
+        parent, octant = si.refinement_parents(nx, ny, nz)
         coef = "terrain"
     ctxs = [gpu_context(problem(m, k, coef=coef)) for m in (fine, coarse)]
     try:

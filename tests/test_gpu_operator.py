@@ -260,3 +260,41 @@ def test_affine_compression_on_a_mixed_mesh():
     r = si.rhs_terrain(2)(*p.dof_coords()) - p.apply(xs.cpu().numpy())
     assert np.linalg.norm(r) <= 1.01e-10 * np.linalg.norm(si.rhs_terrain(2)(*p.dof_coords()))
     ctx.close()
+
+
+@pytest.mark.parametrize("k,dims", [(2, (43, 8, 6)), (3, (16, 16, 8)), (3, (43, 8, 6)), (4, (43, 8, 6)),
+                                    (5, (16, 8, 8)), (5, (13, 10, 8)), (6, (13, 10, 8)), (7, (13, 10, 8))])
+def test_operator_on_both_sides_of_the_two_wave_rule(k, dims):
+    """Meshes of at most and of just over 1024 one-wave workgroups (1 or 2
+    cells each), on which the operator takes its two-wave and its one-wave
+    form, with affine and general cells and with general ones only: operator,
+    residual and the operator with its dot product (conjugate gradients, two
+    steps against the same steps by hand).  FP64 to 1e-12 and FP32 to 2e-6, as
+    above; the steps' x to 1e-10 (a dozen operations of 1e-12 each)."""
+    import paper_2505_00384_amd as hx
+    m = si.terrain_mesh(*dims, g=2)
+    p = problem(m, k, coef="terrain")
+    x = si.random_vector(p.n_dofs, 30 + k)
+    b = si.random_vector(p.n_dofs, 31 + k)
+    ref = p.apply(x)
+    ctx = gpu_context(p)
+    for compress in (True, False):
+        print(f"[op] k={k} {dims} compress={compress}", flush=True)
+        ctx.set_cell_compression(compress)
+        y = ctx.apply_operator(to_dev(x)).cpu().numpy()
+        assert max(normwise(y, ref)) <= 1e-12
+        r = ctx.residual(to_dev(b), to_dev(x)).cpu().numpy()
+        assert max(normwise(r, b - ref)) <= 1e-12
+        y32 = ctx.apply_operator(to_dev(x.astype(np.float32))).cpu().numpy()
+        assert normwise(y32, ref)[0] <= 2e-6
+        xs, _ = ctx.solve(to_dev(b), params=hx.default_params(method=0, rtol=1e-14, max_iter=2,
+                                                              pc=hx.HX_PC_NONE))
+        xr, res, d = np.zeros_like(b), b.copy(), b.copy()
+        for _ in range(2):
+            q = p.apply(d)
+            rr = res @ res
+            al = rr / (d @ q)
+            xr, res = xr + al * d, res - al * q
+            d = res + (res @ res) / rr * d
+        assert np.linalg.norm(xs.cpu().numpy() - xr) <= 1e-10 * np.linalg.norm(xr)
+    ctx.close()
