@@ -285,9 +285,21 @@ def time_call(fn, reps, torch):
     return e0.elapsed_time(e1) / reps
 
 
+def consistent_bytes_per_dof(ctx, k):
+    """Algorithmic bytes per dof of the operator with 2k+1 Gauss points: x and
+    y, seven values per cell and face point, or on affine cells and faces
+    between two of them two values per point and their constants."""
+    q = 2 * k + 1
+    n, _ = ctx.operator_info()
+    gc, gf = n["cells"] - n["affine_cells"], n["interior_faces"] - n["affine_faces"]
+    values = (7 * (gc * q ** 3 + gf * q ** 2) + n["affine_cells"] * (2 * q ** 3 + 6) +
+              n["affine_faces"] * (2 * q ** 2 + 7))
+    return 16 + 8 * values / (n["cells"] * (k + 1) ** 3)
+
+
 def consistent_suite(ctx, torch, k, reps=10):
     """The operator with consistent integration (2k+1 Gauss points): time per
-    application, algorithmic bytes (7 nq^3 + 21 nq^2 numbers per cell, plus x
+    application, algorithmic bytes (consistent_bytes_per_dof: cell and face data, x
     and y), and its difference to the fast operator on a smooth field (the
     aliasing of the (k+1)-point rule)."""
     import synth_inputs as si
@@ -303,8 +315,8 @@ def consistent_suite(ctx, torch, k, reps=10):
     y = torch.empty_like(x)
     ms = time_call(lambda: ctx.apply_consistent(x, y), reps, torch)
     n = ctx.n_dofs
-    nq, nd = 2 * k + 1, (k + 1) ** 3
-    bpd = (7 * nq ** 3 + 21 * nq ** 2) * 8 / nd + 16
+    nq = 2 * k + 1
+    bpd = consistent_bytes_per_dof(ctx, k)
     yf = ctx.apply_operator(x)
     alias = float(torch.linalg.norm(yf - y) / torch.linalg.norm(y))
     # the same for a rough field (seeded normal entries)
@@ -469,9 +481,7 @@ def kernels_suite(hx, ctx, torch, dev, dims, k, reps):
     # consistent integration
     fa, fb = si.terrain_coefficients()
     ctx.set_consistent(field_on_device(fa, xyz, torch), field_on_device(fb, xyz, torch))
-    nq = 2 * k + 1
-    rec("operator_consistent", lambda: ctx.apply_consistent(x, y),
-        (7 * nq ** 3 + 21 * nq ** 2) * 8 / nd + 16)
+    rec("operator_consistent", lambda: ctx.apply_consistent(x, y), consistent_bytes_per_dof(ctx, k))
     # multigrid transfers to the 2x coarser channel
     nx, ny, nz = dims
     mc = si.terrain_mesh(nx // 2, ny // 2, nz // 2, g=4)

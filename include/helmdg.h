@@ -267,7 +267,9 @@ typedef struct {
     double ms_total;     /* wall time of the solve (host clock) */
     double ms_op, ms_pc, ms_orth;  /* device time per phase (HIP events): operator,
                                       preconditioner, orthogonalisation (FGMRES) or
-                                      vector updates and dot products (CG) */
+                                      vector updates and dot products (CG); with a
+                                      cheap preconditioner on small systems every
+                                      seventh step is timed and scaled */
     double *history;     /* optional HOST buffer: residual estimate per iteration */
     int history_len;     /* in: capacity of history; out: entries written */
 } hx_solve_info;
