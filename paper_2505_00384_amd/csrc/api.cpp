@@ -136,6 +136,7 @@ static hx_status update_visit_masks(hx_ctx *c)
 static hx_status expand_general(hx_ctx *c)
 {
     if (!c->has_coef || !c->lean) return HX_OK;
+    HX_HIP(c, hipSetDevice(c->device));
     HX_HIP(c, launch_expand_general(c));
     c->lean = false;
     return HX_OK;

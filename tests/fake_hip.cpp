@@ -1,0 +1,204 @@
+// A program that runs the library's host code without a GPU: it defines the
+// HIP entry points that libhelmdg calls, on host memory, so that the library
+// binds to these instead of the runtime's.  Kernels do not run; of a few of
+// them the launch writes the values that the host code goes on with.  Built and
+// run by test_host_paths.py; the first argument names the scenario.
+#include <cstdint>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <functional>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "../include/helmdg.h"
+
+namespace {
+
+struct Launch {
+    std::string name;
+    int device;
+    unsigned grid;
+    void **args;
+};
+
+struct State {
+    std::map<const void *, std::string> kernels;     // host stub -> name
+    std::map<char *, size_t> live;                   // allocations
+    int n_dev = 1, dev = 0;
+    std::function<void(const Launch &)> on_launch;
+};
+// (the library registers its kernels before this program's own objects exist)
+State &st()
+{
+    static State s;
+    return s;
+}
+
+template <typename T>
+T arg(const Launch &l, int i) { return *(T *)l.args[i]; }
+
+// what the set-up reads back from its kernels
+void default_launch(const Launch &l)
+{
+    auto is = [&](const char *n) { return l.name.find(n) != std::string::npos; };
+    if (is("k_cell_geometry")) {
+        for (int64_t i = 0; i < arg<int64_t>(l, 3); ++i) arg<double *>(l, 7)[i] = 1.0;
+    } else if (is("k_affine_detect")) {
+        for (int64_t i = 0; i < arg<int64_t>(l, 3); ++i) arg<uint8_t *>(l, 6)[i] = 1;
+    }
+}
+
+struct Dim3 {
+    uint32_t x, y, z;
+};
+struct Config {
+    Dim3 grid, block;
+    size_t shmem;
+    void *stream;
+} g_config;
+
+int failures = 0;
+void check(bool ok, const char *what)
+{
+    if (!ok) {
+        ++failures;
+        printf("FAILED: %s\n", what);
+    }
+}
+
+// a mesh of 2 x 1 x 1 unit cells, set up in c
+void small_mesh(hx_ctx *c, int degree)
+{
+    std::vector<double> nodes;
+    for (int cell = 0; cell < 2; ++cell)
+        for (int v = 0; v < 8; ++v)
+            for (double x : {double(cell + (v & 1)), double(v >> 1 & 1), double(v >> 2)}) nodes.push_back(x);
+    const int64_t nbr[12] = {-1, 1, -1, -1, -1, -1, 0, -1, -1, -1, -1, -1};
+    check(hx_setup_mesh(c, degree, 2, 1, nodes.data(), nbr) == HX_OK, "setup_mesh");
+}
+
+hx_ctx *context(int device, int degree)
+{
+    hx_ctx *c = nullptr;
+    check(hx_create(&c, device, nullptr) == HX_OK, "create");
+    small_mesh(c, degree);
+    return c;
+}
+
+void coefficients(hx_ctx *c)
+{
+    const std::vector<double> one(hx_num_dofs(c), 1.0);
+    check(hx_set_coefficients(c, one.data(), one.data(), 2.0, 0) == HX_OK, "set_coefficients");
+}
+
+// Calls that rebuild the general cell and face data launch their kernels on
+// the context's device whatever the caller's current device is.
+void device_of_expansion()
+{
+    st().n_dev = 2;
+    hx_ctx *c = context(1, 2);
+    int launches = 0;
+    st().on_launch = [&](const Launch &l) {
+        ++launches;
+        check(l.device == 1, ("launch on the caller's device: " + l.name).c_str());
+    };
+    std::vector<double> out(2 * 7 * 27);
+    for (int call = 0; call < 3; ++call) {
+        check(hx_set_cell_compression(c, 1) == HX_OK, "compression on");
+        coefficients(c);
+        st().dev = 0;
+        launches = 0;
+        if (call == 0) check(hx_set_cell_compression(c, 0) == HX_OK, "compression off");
+        else
+            check(hx_debug_export(c, call == 1 ? HX_EXPORT_CELL_DATA : HX_EXPORT_FACE_DATA, out.data(),
+                                  8 * (int64_t)out.size()) == HX_OK, "export");
+        check(launches == 2, "the general data are rebuilt");
+    }
+    st().on_launch = nullptr;
+    hx_destroy(c);
+}
+
+}  // namespace
+
+extern "C" {
+
+void **__hipRegisterFatBinary(const void *)
+{
+    static void *handle;
+    return &handle;
+}
+void __hipUnregisterFatBinary(void **) {}
+void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
+void __hipRegisterFunction(void **, const void *host, char *, const char *name, unsigned, void *, void *,
+                           void *, void *, int *)
+{
+    st().kernels[host] = name;
+}
+int __hipPushCallConfiguration(Dim3 grid, Dim3 block, size_t shmem, void *stream)
+{
+    g_config = {grid, block, shmem, stream};
+    return 0;
+}
+int __hipPopCallConfiguration(Dim3 *grid, Dim3 *block, size_t *shmem, void **stream)
+{
+    *grid = g_config.grid;
+    *block = g_config.block;
+    *shmem = g_config.shmem;
+    *stream = g_config.stream;
+    return 0;
+}
+int hipLaunchKernel(const void *f, Dim3 grid, Dim3, void **args, size_t, void *)
+{
+    const Launch l{st().kernels[f], st().dev, grid.x, args};
+    default_launch(l);
+    if (st().on_launch) st().on_launch(l);
+    return 0;
+}
+int hipGetDeviceCount(int *n) { return *n = st().n_dev, 0; }
+int hipSetDevice(int d) { return st().dev = d, 0; }
+int hipDeviceGetAttribute(int *v, int, int) { return *v = 256, 0; }
+int hipDeviceSynchronize() { return 0; }
+int hipStreamSynchronize(void *) { return 0; }
+int hipGetLastError() { return 0; }
+const char *hipGetErrorString(int) { return "refused"; }
+int hipMalloc(void **p, size_t n)
+{
+    *p = calloc(n, 1);
+    st().live[(char *)*p] = n;
+    return 0;
+}
+int hipFree(void *p)
+{
+    check(st().live.erase((char *)p) == 1, "free of an address that is not allocated");
+    free(p);
+    return 0;
+}
+int hipHostMalloc(void **p, size_t n, unsigned) { return *p = calloc(n, 1), 0; }
+int hipHostFree(void *p) { return free(p), 0; }
+int hipHostGetDevicePointer(void **d, void *h, unsigned) { return *d = h, 0; }
+int hipGetSymbolAddress(void **p, const void *)
+{
+    static char scratch[1 << 20];
+    return *p = scratch, 0;
+}
+int hipMemcpy(void *d, const void *s, size_t n, int) { return memmove(d, s, n), 0; }
+int hipMemcpyAsync(void *d, const void *s, size_t n, int, void *) { return memmove(d, s, n), 0; }
+int hipMemsetAsync(void *d, int v, size_t n, void *) { return memset(d, v, n), 0; }
+int hipEventCreateWithFlags(double **e, unsigned) { return *e = new double(0.0), 0; }
+int hipEventDestroy(double *e) { return delete e, 0; }
+int hipEventRecord(double *, void *) { return 0; }
+int hipEventSynchronize(double *) { return 0; }
+int hipEventElapsedTime(float *t, double *, double *) { return *t = 0.0f, 0; }
+}
+
+int main(int argc, char **argv)
+{
+    const std::string what = argc > 1 ? argv[1] : "";
+    if (what == "device") device_of_expansion();
+    else check(false, "unknown scenario");
+    check(st().live.empty(), "device memory left allocated");
+    printf("%s: %d failures\n", what.c_str(), failures);
+    return failures ? 1 : 0;
+}
