@@ -37,6 +37,24 @@ def test_consistent_operator_matches_oracle(name, mk, k):
     ctx.close()
 
 
+@pytest.mark.parametrize("k", range(1, 8))
+def test_consistent_on_affine_and_general_cells(k):
+    """Affine and general cells side by side, with faces of both kinds around
+    one cell, at every degree (each has a division of its own into waves and
+    rounds)."""
+    print(f"[consistent] affine and general cells, k={k}", flush=True)
+    p = problem(si.terrain_mesh(7, 1, 3, g=2), k, coef="random")
+    ctx = gpu_context(p)
+    n, _ = ctx.operator_info()
+    assert 0 < n["affine_cells"] < n["cells"] and 0 < n["affine_faces"] < n["interior_faces"], n
+    ctx.set_consistent(p.alpha, p.beta)
+    x = si.random_vector(p.n_dofs, 31 + k)
+    y = ctx.apply_consistent(to_dev(x)).cpu().numpy()
+    e2, einf = normwise(y, p.apply_q(x, 2 * k + 1))
+    assert e2 <= 1e-12 and einf <= 1e-12, (k, e2, einf)
+    ctx.close()
+
+
 def test_consistent_sampled_full_size():
     import torch
     free = torch.cuda.mem_get_info()[0]
