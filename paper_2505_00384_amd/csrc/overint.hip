@@ -5,11 +5,11 @@
 // interpolation B (nq x n) and its derivative BD are rectangular now, so the
 // sweeps change pencil lengths (n nodes <-> nq points).
 //
-// A workgroup serves one cell: wave 0 the cell integrals, one further wave
-// (two for N > 5) the face terms, at the same time; they meet at one barrier,
-// after which wave 0 adds the faces and writes its output pencils.  Inside a
-// wave only the order of its LDS accesses matters, so there are no other
-// barriers.
+// A workgroup serves one cell: wave 0 (two waves for N = 8) the cell integrals,
+// one further wave (two for N > 5) the face terms, at the same time; they meet
+// at one barrier, after which wave 0 adds the faces and writes its output
+// pencils.  Inside a wave only the order of its LDS accesses matters, so there
+// are no other barriers, except with two cell waves.
 //  * cell: x sweep by lanes (j, l), y sweep by items (qx, l), z sweep,
 //    quadrature-point operation and transposed z sweep by items (qx, qy), two
 //    rounds of lanes for N = 5, then back; fields in LDS between the sweeps;
@@ -23,10 +23,26 @@
 // The 1-D tables are compile-time scalars.  What bounds it: the quadrature
 // data stream (452 bytes per dof at degree 4, 140 on affine cells, which read
 // two values per point and their constants) and the LDS traffic between the
-// sweeps.  The former form (two waves per cell in lock step, 23 barriers, face
-// contractions with both operands and the tables from LDS) was bound by LDS:
-// 0.500 ms at 64x16x32 cells, degree 4, and no faster with the compressed
-// data of the affine cells (0.508); this one 0.381 ms.
+// sweeps, and with them how many waves the registers leave room for.  The
+// former form (two waves per cell in lock step, 23 barriers, face contractions
+// with both operands and the tables from LDS) was bound by LDS: 0.500 ms at
+// 64x16x32 cells, degree 4, and no faster with the compressed data of the
+// affine cells (0.508); this one 0.369 ms.
+//
+// The lanes of a face wave hold faces of both kinds.  A branch on the kind at
+// every point made the compiler carry the four interpolated values of all 2N-1
+// points of a row past it (8 N doubles: 206 registers at N = 6, two waves per
+// SIMD where there is room for three, and spills at N = 4), so a compressed
+// face takes the same loads, from the one place it has, and the factors of
+// the other kind are ones.  From N = 6 on the neighbour's side keeps two points
+// in flight instead of the whole row.  64x16x32 cells, branch / without:
+// degree 2 125 / 106 us, 3 239 / 196, 4 380 / 369, 5 1082 / 727 (the former form
+// 862); at degree 1 the branch is the better one (49.6 / 52.0).  N = 7 and 8
+// read the own values where they are needed instead of keeping them in LDS, so
+// that at N = 8 two workgroups share a CU's 160 KB, and its cell integrals
+// take two waves: degree 6 1826 / 1697 us, 7 4799 / 2557; 96 cells, degree 7,
+// 36.3 / 26.3 (the former form 29.5).  N = 6 is slower without the LDS copy
+// (923 us), and two cell waves lose at N = 5 (521), 6 (1032) and 7 (1783).
 #include "common.hpp"
 
 namespace hx {
@@ -54,7 +70,11 @@ struct QCfg {
     static constexpr int QN = Q * N, QNN = Q * N * N, QQN = Q * Q * N;
     static constexpr int FW = 6 * Q <= 64 ? 1 : 2;   // face waves
     static constexpr int FPW = 6 / FW;               // faces per face wave
-    static constexpr int NT = 64 * (1 + FW);
+    static constexpr int CW = N <= 7 ? 1 : 2;        // cell waves
+    static constexpr bool OWN_LDS = N <= 6;          // own values by way of LDS (face waves)
+    static constexpr bool BRANCH = N == 2;           // a branch on the kind of a face at every point
+    static constexpr int AHEAD = N <= 5 ? Q : 2;     // points of the neighbour's side in flight
+    static constexpr int NT = 64 * (CW + FW);
     static_assert(NF <= 64 && FPW * Q <= 64, "one row lane per face row");
 };
 
@@ -64,6 +84,15 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// between the sweeps: the waves of a role wait for each other, if there are two
+// by the workgroup's barrier, which the other role then meets as often
+template <int N>
+__device__ __forceinline__ void q_sync()
+{
+    if constexpr (QCfg<N>::CW > 1) __syncthreads();
+    else wave_sync();
 }
 
 // y = B u (W = 0) or BD u (W = 1), n -> nq
@@ -79,8 +108,8 @@ __device__ __forceinline__ void up(const double (&u)[N], double (&y)[2 * N - 1])
     }
 }
 
-// Cell integrals by one wave; U0, U1 (Q N^2 each) and V0, V1, V2 (Q^2 N each)
-// in LDS, U overlaying V0; the output pencil of lane (j, l) in Y.
+// Cell integrals by CW waves (lane: 0 .. 64 CW - 1); U0, U1 (Q N^2 each) and
+// V0, V1, V2 (Q^2 N each) in LDS; the output pencil of lane (j, l) in Y.
 template <int N, bool AFF>
 __device__ __forceinline__ void q_cell(const double *__restrict__ x, const double *__restrict__ cell,
                                        const double *__restrict__ kk, int64_t cid, int lane,
@@ -112,10 +141,10 @@ __device__ __forceinline__ void q_cell(const double *__restrict__ x, const doubl
             U1[q + Q * lane] = s1[q];
         }
     }
-    wave_sync();
+    q_sync<N>();
     // y sweep: item (qx, l): u, d/deta (from u) and d/dxi (from U1) at
     // (qx, qy, l), layout qx + Q (qy + Q l)
-    for (int it = lane; it < QN; it += 64) {
+    for (int it = lane; it < QN; it += 64 * C::CW) {
         const int qx = it % Q, l = it / Q;
         double v0[N], v1[N], s0[Q], s1[Q], s2[Q];
 #pragma unroll
@@ -133,10 +162,10 @@ __device__ __forceinline__ void q_cell(const double *__restrict__ x, const doubl
             V2[qx + Q * (q + Q * l)] = s2[q];
         }
     }
-    wave_sync();
+    q_sync<N>();
     // z sweep, quadrature-point operation, transposed z sweep: item (qx, qy),
     // in place (an item reads and writes its own columns only)
-    for (int it = lane; it < Q2; it += 64) {
+    for (int it = lane; it < Q2; it += 64 * C::CW) {
         double a0[N], a1[N], a2[N], w0[N], w1[N], w2[N];
 #pragma unroll
         for (int l = 0; l < N; ++l) {
@@ -146,7 +175,7 @@ __device__ __forceinline__ void q_cell(const double *__restrict__ x, const doubl
             w0[l] = w1[l] = w2[l] = 0.0;
         }
         // (the last plane requests the next round's first one)
-        const int nit = it + 64 < Q2 ? it + 64 : it;
+        const int nit = it + 64 * C::CW < Q2 ? it + 64 * C::CW : it;
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             double cd[7];
@@ -187,10 +216,10 @@ __device__ __forceinline__ void q_cell(const double *__restrict__ x, const doubl
             V2[it + Q2 * l] = w2[l];
         }
     }
-    wave_sync();
+    q_sync<N>();
     // transposed y sweep: item (qx, l) -> (qx, j, l): s0 = B^T w0 + BD^T w1,
     // s1 = B^T w2
-    for (int it = lane; it < QN; it += 64) {
+    for (int it = lane; it < QN; it += 64 * C::CW) {
         const int qx = it % Q, l = it / Q;
         double s0[N], s1[N];
 #pragma unroll
@@ -211,7 +240,7 @@ __device__ __forceinline__ void q_cell(const double *__restrict__ x, const doubl
             U1[qx + Q * (j + N * l)] = s1[j];
         }
     }
-    wave_sync();
+    q_sync<N>();
     // transposed x sweep: lane (j, l) keeps its output pencil
 #pragma unroll
     for (int i = 0; i < N; ++i) Y[i] = 0.0;
@@ -224,7 +253,7 @@ __device__ __forceinline__ void q_cell(const double *__restrict__ x, const doubl
         }
 }
 
-// Face terms of faces f0 .. f0 + FPW - 1 by one wave.  S: own values (N^3);
+// Face terms of faces f0 .. f0 + FPW - 1 by one wave.  S: own values (N^3, OWN_LDS);
 // F: three fields of Q x N per face, [field][q2][p], layer weights and
 // normal-derivative weights in fields 0 and 1, [r][p], on return.
 template <int N>
@@ -263,9 +292,11 @@ __device__ __forceinline__ void q_faces(const double *__restrict__ x, const doub
             L[r] = xn[r * sr];
         }
     }
+    if constexpr (C::OWN_LDS) {
 #pragma unroll
-    for (int k = 0; k < (ND + 63) / 64; ++k)
-        if (lane + 64 * k < ND) S[lane + 64 * k] = x[cid * ND + lane + 64 * k];
+        for (int k = 0; k < (ND + 63) / 64; ++k)
+            if (lane + 64 * k < ND) S[lane + 64 * k] = x[cid * ND + lane + 64 * k];
+    }
     // face data of the row: g of the neighbour's side (the plus side's if the
     // own cell is the minus cell), g of the own side, penalty factor; on a
     // face between two affine cells beta w of both sides and constants
@@ -275,17 +306,21 @@ __device__ __forceinline__ void q_faces(const double *__restrict__ x, const doub
     const double *kf = fd - q2 + 2 * Q2;
     const int gn = sr_ ? 3 : 0, go = sr_ ? 0 : 3;
     const double *fn = fd + (cmp ? (sr_ ? 1 : 0) : gn) * Q2, *fo = fd + (cmp ? (sr_ ? 0 : 1) : go) * Q2;
-    double gv[3][Q];
-    if (rl) {
-#pragma unroll
-        for (int q1 = 0; q1 < Q; ++q1) {
-            gv[0][q1] = fn[Q * q1];
-            if (!cmp) {
-                gv[1][q1] = fn[Q * q1 + Q2];
-                gv[2][q1] = fn[Q * q1 + 2 * Q2];
-            }
+    // the second and third component of a point; a compressed face reads the
+    // first one again (st = 0)
+    const int st = cmp ? 0 : Q2;
+    constexpr int AH = C::AHEAD;
+    double gv[AH][3];
+    auto request_nb = [&](int q, double (&g)[3]) {
+        g[0] = fn[Q * q];
+        if (AH < Q || !cmp) {
+            g[1] = fn[Q * q + st];
+            g[2] = fn[Q * q + 2 * st];
         }
-    }
+    };
+    if (rl)
+#pragma unroll
+        for (int q = 0; q < AH; ++q) request_nb(q, gv[q]);
     auto step1 = [&](const double (&l)[N], const double (&d)[N]) {
         double g[Q];
         up<N, 0>(l, g);
@@ -299,7 +334,7 @@ __device__ __forceinline__ void q_faces(const double *__restrict__ x, const doub
         for (int q = 0; q < Q; ++q) gc[2 * QN + q * N + p] = g[q];
     };
     if (cl) step1(L, D);
-    wave_sync();
+    q_sync<N>();
     // step 2, neighbour's side: flux and value at (q1, q2)
     double fnb[Q], vnb[Q];
     if (rl) {
@@ -310,7 +345,7 @@ __device__ __forceinline__ void q_faces(const double *__restrict__ x, const doub
             h1[i] = gr[QN + i];
             h2[i] = gr[2 * QN + i];
         }
-        double v0 = 0.0, v1 = 0.0, v2 = 0.0;
+        double v0 = 1.0, v1 = 1.0, v2 = 1.0;
         if (cmp) {
             v0 = kf[gn];
             v1 = kf[gn + 1];
@@ -327,21 +362,22 @@ __device__ __forceinline__ void q_faces(const double *__restrict__ x, const doub
                 dn += tq<N>(q, i) * h2[i];
             }
             vnb[q] = v;
-            if (cmp) {
-                fnb[q] = gv[0][q] * (v0 * dn + v1 * t1 + v2 * t2);
-                vnb[q] = v;
-                gv[1][q] = gv[0][q];   // beta w of the neighbour's side, for the penalty
+            const double g0 = gv[q % AH][0], g1 = gv[q % AH][1], g2 = gv[q % AH][2];
+            if (q + AH < Q) request_nb(q + AH, gv[q % AH]);
+            if constexpr (AH < Q) {
+                fnb[q] = g0 * v0 * dn + g1 * v1 * t1 + g2 * v2 * t2;
             } else {
-                fnb[q] = gv[0][q] * dn + gv[1][q] * t1 + gv[2][q] * t2;
+                if (cmp) fnb[q] = g0 * (v0 * dn + v1 * t1 + v2 * t2);
+                else fnb[q] = g0 * dn + g1 * t1 + g2 * t2;
             }
         }
     }
-    wave_sync();
+    q_sync<N>();
     // step 1, own side
     if (cl) {
         const int m0 = sc ? (N - 1) * sm : 0, dm = sc ? -sm : sm;
         const double sgn = sc ? -1.0 : 1.0;
-        const double *uo = S + p * sp + m0;
+        const double *uo = (C::OWN_LDS ? S : x + cid * ND) + p * sp + m0;
 #pragma unroll
         for (int r = 0; r < N; ++r) {
             double s = 0.0;
@@ -352,7 +388,7 @@ __device__ __forceinline__ void q_faces(const double *__restrict__ x, const doub
         }
         step1(L, D);
     }
-    wave_sync();
+    q_sync<N>();
     // steps 2 and 3, own side: flux terms point by point and the transposed
     // sweep along the first direction, written over the row read; the next
     // point's data always in flight
@@ -365,7 +401,7 @@ __device__ __forceinline__ void q_faces(const double *__restrict__ x, const doub
             h2[i] = gr[2 * QN + i];
             A0[i] = A1[i] = A2[i] = 0.0;
         }
-        double w0 = 0.0, w1 = 0.0, w2 = 0.0, sd = 0.0;
+        double w0 = 1.0, w1 = 1.0, w2 = 1.0, sd = 1.0;
         if (cmp) {
             w0 = kf[go];
             w1 = kf[go + 1];
@@ -373,27 +409,29 @@ __device__ __forceinline__ void q_faces(const double *__restrict__ x, const doub
             sd = kf[6];
         }
         const double sg = sr_ ? 1.0 : -1.0;
+        // the last value: penalty factor, or beta w of the neighbour's side
+        const double *fp = cmp ? fn : fd + 6 * Q2;
         double nx[4];
         auto request = [&](int q) {
             nx[0] = fo[Q * q];
-            if (!cmp) {
-                nx[1] = fo[Q * q + Q2];
-                nx[2] = fo[Q * q + 2 * Q2];
-                nx[3] = fd[Q * q + 6 * Q2];
+            if (!C::BRANCH || !cmp) {
+                nx[1] = fo[Q * q + st];
+                nx[2] = fo[Q * q + 2 * st];
+                nx[3] = fp[Q * q];
             }
         };
         request(0);
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             double g0 = nx[0], g1 = nx[1], g2 = nx[2], pen = nx[3];
-            if (q + 1 < Q) request(q + 1);
-            if (cmp) {
-                const double bo = g0;
+            if (!C::BRANCH || cmp) {
+                const double bo = nx[0], bn = C::BRANCH ? gv[q % AH][0] : nx[3];
                 g0 = bo * w0;
-                g1 = bo * w1;
-                g2 = bo * w2;
-                pen = sd * (bo + gv[1][q]);
+                g1 = (C::BRANCH ? bo : nx[1]) * w1;
+                g2 = (C::BRANCH ? bo : nx[2]) * w2;
+                if (cmp) pen = sd * (bo + bn);
             }
+            if (q + 1 < Q) request(q + 1);
             double v = 0.0, t1 = 0.0, t2 = 0.0, dn = 0.0;
 #pragma unroll
             for (int i = 0; i < N; ++i) {
@@ -420,7 +458,7 @@ __device__ __forceinline__ void q_faces(const double *__restrict__ x, const doub
             gr[2 * QN + i] = A2[i];
         }
     }
-    wave_sync();
+    q_sync<N>();
     // step 4, column lanes: transposed sweep along the second direction, in
     // place (a column lane reads and writes its own column only)
     if (cl0) {
@@ -446,25 +484,26 @@ __device__ __forceinline__ void q_faces(const double *__restrict__ x, const doub
 }
 
 template <int N>
-__global__ void __launch_bounds__(QCfg<N>::NT, N <= 4 ? 4 : (N <= 5 ? 3 : (N <= 7 ? 2 : 1)))
+__global__ void __launch_bounds__(QCfg<N>::NT, N <= 4 ? 4 : (N <= 5 ? 3 : 2))
 k_apply_q(const double *__restrict__ x, double *__restrict__ y, const double *__restrict__ cell,
           const double *__restrict__ face, const int32_t *__restrict__ nbr,
           const uint8_t *__restrict__ ctype, const double *__restrict__ kk, int nwg)
 {
     using C = QCfg<N>;
     constexpr int ND = C::ND, NF = C::NF, QN = C::QN, QNN = C::QNN, QQN = C::QQN, FPW = C::FPW;
-    __shared__ double sU[2 * QNN], sV[3 * QQN], sX[C::FW][ND], sF[6 * 3 * QN];
+    __shared__ double sU[2 * QNN], sV[3 * QQN], sX[C::OWN_LDS ? C::FW : 1][C::OWN_LDS ? ND : 1], sF[6 * 3 * QN];
     // contiguous ranges of the cells per XCD
     const int bid = blockIdx.x;
     const int q8 = nwg / NXCD, r8 = nwg % NXCD, xcd = bid % NXCD;
     const int64_t cid = xcd * q8 + (xcd < r8 ? xcd : r8) + bid / NXCD;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = wave < C::CW ? threadIdx.x : threadIdx.x & 63;
     // affine cell: the same for the whole workgroup, so branches on it are
     // uniform
     const bool aff = __builtin_amdgcn_readfirstlane(ctype[cid]);
-    if (wave > 0) {
-        q_faces<N>(x, face, nbr, ctype, aff, cid, lane, (wave - 1) * FPW, sX[wave - 1],
-                   sF + (wave - 1) * FPW * 3 * QN);
+    if (wave >= C::CW) {
+        const int fw = wave - C::CW;
+        q_faces<N>(x, face, nbr, ctype, aff, cid, lane, fw * FPW, sX[C::OWN_LDS ? fw : 0], sF + fw * FPW * 3 * QN);
         __syncthreads();
         return;
     }
