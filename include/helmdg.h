@@ -177,8 +177,9 @@ hx_status hx_apply_operator_part(hx_ctx *c, hx_prec prec, int part, const void *
  * values per point instead of 7), and on faces between two affine cells
  * beta- w, beta+ w per point plus 7 constants per face (instead of 7 values
  * per point).  on = 1 (the default after hx_setup_mesh) uses this compressed
- * data; on = 0 makes every cell and face read the general data.  The results
- * agree to rounding. */
+ * data; on = 0 makes every cell and face read the general data.  The operator
+ * with consistent integration keeps the data that hx_set_consistent built, of
+ * the kind that was chosen then.  The results agree to rounding. */
 hx_status hx_set_cell_compression(hx_ctx *c, int on);
 
 /* Counts of the mesh as the operator sees it, counts[4] (HOST, may be NULL)

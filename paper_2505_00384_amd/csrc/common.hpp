@@ -160,6 +160,9 @@ struct hx_ctx {
     hx::RefTabQ *refq = nullptr;  // device tables
     double *qcell = nullptr;      // [n_cells][7][nq^3]   m, Gxx, Gxy, Gxz, Gyy, Gyz, Gzz
     double *qface = nullptr;      // [n_cells][3][7][nq^2] g-(3), g+(3), s of the +d face
+    // qcell and qface hold compressed data on affine cells (alpha w detJ, beta w
+    // detJ) and on faces between two of them (beta- w, beta+ w; v-, v+, sigma ds0 / 2)
+    bool q_lean = false;
     // geometric multigrid: the next coarser level (not owned), the children of
     // each of its cells, and the level vectors
     hx_ctx *mg_coarse = nullptr;

@@ -1228,10 +1228,10 @@ namespace {
 // same quantities as k_cell_geofac / k_set_cell and k_face_geofac /
 // k_set_face, with alpha and beta interpolated from the nodes to the points.
 // Cell point index qx + nq (qy + nq qz); face point b + nq a (a along t1).
-// An affine cell takes alpha w detJ and beta w detJ in the first two of its
-// seven fields, and a face between two affine cells beta- w, beta+ w in its
-// first two and the constants v- (3), v+ (3), sigma ds0 / 2 (ds = w ds0, v = ds0
-// J^-1 n) at the start of the third.
+// With the compression on (ctype given) an affine cell takes alpha w detJ and
+// beta w detJ in the first two of its seven fields, and a face between two
+// affine cells beta- w, beta+ w in its first two and the constants v- (3), v+
+// (3), sigma ds0 / 2 (ds = w ds0, v = ds0 J^-1 n) at the start of the third.
 // -------------------------------------------------------------------------
 __global__ void k_q_cell(const double *__restrict__ nodes, int ng, int n, int64_t n_cells,
                          const RefTabQ *__restrict__ Q, const double *__restrict__ alpha,
@@ -1263,7 +1263,7 @@ __global__ void k_q_cell(const double *__restrict__ nodes, int ng, int n, int64_
         }
     double *dst = qcell + c * 7 * nq3 + q;
     dst[0] = aq * w;
-    if (ctype[c]) {
+    if (ctype && ctype[c]) {
         dst[nq3] = bq * w;
         return;
     }
@@ -1319,7 +1319,7 @@ __global__ void k_q_face(const double *__restrict__ nodes, int ng, int n, int64_
             bp += wgt * beta[(int64_t)nb * nd + layer_idx(n, d, 0, e1, e2)];
         }
     const int dir[3] = {d, t1, t2};
-    if (ctype[c] && ctype[nb]) {
+    if (ctype && ctype[c] && ctype[nb]) {
         const double wab = Q->wq[a] * Q->wq[b];
         dst[0] = bm * wab;
         dst[nq2] = bp * wab;
@@ -1348,14 +1348,16 @@ __global__ void k_q_face(const double *__restrict__ nodes, int ng, int n, int64_
 hipError_t launch_q_setup(hx_ctx *c, const double *alpha, const double *beta)
 {
     const int nq = c->nq;
+    c->q_lean = c->compress != 0;
+    const uint8_t *ctype = c->q_lean ? c->ctype : nullptr;
     const int64_t nt = c->n_cells * nq * nq * nq;
     hipLaunchKernelGGL(k_q_cell, dim3(nblk(nt, 128)), dim3(128), 0, c->stream, c->nodes, c->g + 1, c->n,
-                       c->n_cells, c->refq, alpha, beta, c->ctype, c->qcell);
+                       c->n_cells, c->refq, alpha, beta, ctype, c->qcell);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int64_t nf = 3 * c->n_cells * nq * nq;
     hipLaunchKernelGGL(k_q_face, dim3(nblk(nf, 128)), dim3(128), 0, c->stream, c->nodes, c->g + 1, c->n,
-                       c->n_cells, c->nbr, c->refq, beta, c->sigma, c->ctype, c->qface);
+                       c->n_cells, c->nbr, c->refq, beta, c->sigma, ctype, c->qface);
     return hipGetLastError();
 }
 

@@ -27,7 +27,7 @@
 // former form (two waves per cell in lock step, 23 barriers, face contractions
 // with both operands and the tables from LDS) was bound by LDS: 0.500 ms at
 // 64x16x32 cells, degree 4, and no faster with the compressed data of the
-// affine cells (0.508); this one 0.369 ms.
+// affine cells (0.508); this one 0.365 ms.
 //
 // The lanes of a face wave hold faces of both kinds.  A branch on the kind at
 // every point made the compiler carry the four interpolated values of all 2N-1
@@ -36,12 +36,12 @@
 // face takes the same loads, from the one place it has, and the factors of
 // the other kind are ones.  From N = 6 on the neighbour's side keeps two points
 // in flight instead of the whole row.  64x16x32 cells, branch / without:
-// degree 2 125 / 106 us, 3 239 / 196, 4 380 / 369, 5 1082 / 727 (the former form
-// 862); at degree 1 the branch is the better one (49.6 / 52.0).  N = 7 and 8
+// degree 2 125 / 107 us, 3 230 / 195, 4 378 / 365, 5 1083 / 723 (the former form
+// 862); at degree 1 the branch is the better one (49.5 / 52.0).  N = 7 and 8
 // read the own values where they are needed instead of keeping them in LDS, so
 // that at N = 8 two workgroups share a CU's 160 KB, and its cell integrals
-// take two waves: degree 6 1826 / 1697 us, 7 4799 / 2557; 96 cells, degree 7,
-// 36.3 / 26.3 (the former form 29.5).  N = 6 is slower without the LDS copy
+// take two waves: degree 6 1830 / 1696 us, 7 4794 / 2587; 96 cells, degree 7,
+// 36.4 / 26.4 (the former form 29.5).  N = 6 is slower without the LDS copy
 // (923 us), and two cell waves lose at N = 5 (521), 6 (1032) and 7 (1783).
 #include "common.hpp"
 
@@ -498,9 +498,9 @@ k_apply_q(const double *__restrict__ x, double *__restrict__ y, const double *__
     const int64_t cid = xcd * q8 + (xcd < r8 ? xcd : r8) + bid / NXCD;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = wave < C::CW ? threadIdx.x : threadIdx.x & 63;
-    // affine cell: the same for the whole workgroup, so branches on it are
-    // uniform
-    const bool aff = __builtin_amdgcn_readfirstlane(ctype[cid]);
+    // affine cell with compressed data (no ctype: every cell has the general
+    // ones): the same for the whole workgroup, so branches on it are uniform
+    const bool aff = ctype && __builtin_amdgcn_readfirstlane(ctype[cid]);
     if (wave >= C::CW) {
         const int fw = wave - C::CW;
         q_faces<N>(x, face, nbr, ctype, aff, cid, lane, fw * FPW, sX[C::OWN_LDS ? fw : 0], sF + fw * FPW * 3 * QN);
@@ -548,7 +548,7 @@ template <int N>
 hipError_t apply_q_n(hx_ctx *c, const double *x, double *y)
 {
     hipLaunchKernelGGL(k_apply_q<N>, dim3((unsigned)c->n_cells), dim3(QCfg<N>::NT), 0, c->stream, x, y,
-                       c->qcell, c->qface, c->nbr, c->ctype, c->kk64, (int)c->n_cells);
+                       c->qcell, c->qface, c->nbr, c->q_lean ? c->ctype : nullptr, c->kk64, (int)c->n_cells);
     return hipGetLastError();
 }
 

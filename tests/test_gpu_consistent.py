@@ -55,6 +55,33 @@ def test_consistent_on_affine_and_general_cells(k):
     ctx.close()
 
 
+@pytest.mark.parametrize("k", [1, 4, 5, 7])
+def test_consistent_with_the_compression_off(k):
+    """With the compression off hx_set_consistent builds the general data of
+    every cell and face: the same operator, by other products on the affine
+    cells, and the data stay when the switch is turned afterwards."""
+    import torch
+    print(f"[consistent] compression off, k={k}", flush=True)
+    # skewed affine cells, whose constants are rounded otherwise than the
+    # products at the points
+    p = problem(si.box_mesh(7, 1, 1, periodic=(True, False, True), mapping=si.random_affine_mapping(9)), k,
+                coef="random")
+    ctx = gpu_context(p)
+    x = to_dev(si.random_vector(p.n_dofs, 51 + k))
+    ref = p.apply_q(x.cpu().numpy(), 2 * k + 1)
+    y = {}
+    for on in (True, False):
+        ctx.set_cell_compression(on)
+        ctx.set_consistent(p.alpha, p.beta)
+        y[on] = ctx.apply_consistent(x)
+        e2, einf = normwise(y[on].cpu().numpy(), ref)
+        assert e2 <= 1e-12 and einf <= 1e-12, (k, on, e2, einf)
+    assert not torch.equal(y[True], y[False])
+    ctx.set_cell_compression(True)
+    assert torch.equal(ctx.apply_consistent(x), y[False])
+    ctx.close()
+
+
 def test_consistent_sampled_full_size():
     import torch
     free = torch.cuda.mem_get_info()[0]
