@@ -8,7 +8,7 @@
 // separable approximation of the Helmholtz cell block.
 //
 // Mapping: N*N threads per cell, one per pencil, a cell's threads in one wave
-// where enough of its lanes work (BjMap in bj_cell.hpp); 6 sweeps of N x N 1-D
+// where that costs no round of workgroups (bj_by_wave); 6 sweeps of N x N 1-D
 // matrices that differ per cell (kept in LDS) plus one diagonal scaling.
 // A fused form also performs the conjugate-gradient updates of x and r
 // before the solve and sums r.z and r.r per block, so one CG step touches
@@ -31,11 +31,37 @@ struct Cfg {
     static constexpr int NT = ((CPB * NF + 63) / 64) * 64;
 };
 
-// block-Jacobi kernels: 256 threads
+constexpr int BJ_T = 256;   // threads of a block-Jacobi workgroup
+
+// The map of the cells for a mesh.  Packed into waves a cell waits for no
+// other wave, but at N = 5 and 7 a workgroup then holds fewer cells (8 instead
+// of 10, 4 instead of 5), and the kernel takes a time per round of workgroups
+// over the compute units: the waves only where they need no more rounds.  By
+// waves / by barriers, FP64, degree 4: 512 cells 4.3 / 4.8 us, 4,096 6.2 /
+// 6.7, 8,192 9.7 / 10.4 (as many rounds), 2,197 5.9 / 5.2, 6,400 9.5 / 8.5,
+// 32,768 29.2 / 27.1 (more rounds); degree 6: 512 5.8 / 6.3, 4,096 15.2 / 16.2,
+// 2,197 11.6 / 9.4, 6,400 23.8 / 19.9, 16,384 49.3 / 44.2, and its CG solve on
+// 13^3 cells 5.71 / 5.45 ms.  Where both hold as many cells (N = 2, 3, 4,
+// 8) always the waves: degree 7, 4,096 cells 16.5 / 17.3.
 template <int N>
-struct BCfg {
-    static constexpr int NF = N * N, ND = N * N * N, NT = 256, CPB = BjMap<N>::cells(NT);
-};
+bool bj_by_wave(int64_t n_cells)
+{
+    auto rounds = [&](int64_t cpb) { return (n_cells + cpb * NCU - 1) / (cpb * NCU); };
+    return rounds(BjMap<N, true>::cells(BJ_T)) <= rounds(BjMap<N, false>::cells(BJ_T));
+}
+
+// f with the map as a compile-time value
+template <int N, typename F>
+hipError_t with_bj_map(int64_t n_cells, F f)
+{
+    if constexpr (!BJ_WAVE<N>) {
+        return f(std::false_type{});
+    } else {
+        if constexpr (BjMap<N, true>::cells(BJ_T) < BjMap<N, false>::cells(BJ_T))
+            if (!bj_by_wave<N>(n_cells)) return f(std::false_type{});
+        return f(std::true_type{});
+    }
+}
 
 // deterministic block sum of two values (result valid in thread 0)
 template <int NT>
@@ -76,15 +102,15 @@ __device__ __forceinline__ void block_sum2(double &u, double &v, double *sh)
 // norm from the fixed-order sum256 of the partial sums.
 constexpr int CHEB_READ_D = 1, CHEB_ACCUM = 2;
 
-template <int N, typename T, bool FUSE, bool CHEB = false>
-__global__ void __launch_bounds__(BCfg<N>::NT)
+template <int N, typename T, bool WAVE, bool FUSE, bool CHEB = false>
+__global__ void __launch_bounds__(BJ_T)
 k_bj(const T *__restrict__ rin, T *__restrict__ z, const T *__restrict__ S, const T *__restrict__ L,
      const T *__restrict__ C, int n_cells, int nwg, T *x, T *rw, const T *__restrict__ p,
      const T *__restrict__ q, const double *__restrict__ sc, double *part, int ld, T ca = 0,
      T cb = 0, int flags = 0, const double *__restrict__ pqp = nullptr, int npq = 0)
 {
     const T *r = FUSE ? rw : rin;
-    constexpr int NF = BCfg<N>::NF, ND = BCfg<N>::ND, CPB = BCfg<N>::CPB;
+    constexpr int NF = N * N, ND = NF * N, CPB = BjMap<N, WAVE>::cells(BJ_T);
     __shared__ T sR[CPB][ND];
     __shared__ T sS[CPB][3][NF];
     __shared__ T sL[CPB][3][N];
@@ -95,7 +121,7 @@ k_bj(const T *__restrict__ rin, T *__restrict__ z, const T *__restrict__ S, cons
     const int wg = xcd * q8 + (xcd < r8 ? xcd : r8) + bid / NXCD;
     const int t = threadIdx.x;
     int lc0, tt;
-    BjMap<N>::place(t, BCfg<N>::NT, lc0, tt);
+    BjMap<N, WAVE>::place(t, BJ_T, lc0, tt);
     const bool slot = lc0 < CPB;
     const int lc = slot ? lc0 : 0;
     const int a = tt % N, b = tt / N;
@@ -135,7 +161,7 @@ k_bj(const T *__restrict__ rin, T *__restrict__ z, const T *__restrict__ S, cons
     T sfac = 1;
     // the scale and p.q while those loads are in flight
     if (scaled) {
-        static_assert(BCfg<N>::NT == 256, "the scaled form sums with a 256-thread workgroup");
+        static_assert(BJ_T == 256, "the scaled form sums with a 256-thread workgroup");
         __shared__ double shs[4];
         sfac = (T)(1.0 / sqrt(sum256(part, ld, shs)));
     }
@@ -184,7 +210,6 @@ k_bj(const T *__restrict__ rin, T *__restrict__ z, const T *__restrict__ S, cons
         }
         if (tt < 4) sC[lc][tt] = tC;
     }
-    constexpr bool WAVE = BjMap<N>::WAVE;
     if constexpr (WAVE) lds_wave_sync();
     else __syncthreads();
     bj_cell_solve<N, T, WAVE>(sR[lc], sS[lc], sL[lc], sC[lc], a, b, active, acc_rz);
@@ -212,8 +237,8 @@ k_bj(const T *__restrict__ rin, T *__restrict__ z, const T *__restrict__ S, cons
         }
     }
     if (FUSE) {
-        __shared__ double sh2[2 * (BCfg<N>::NT / 64)];
-        block_sum2<BCfg<N>::NT>(acc_rz, acc_rr, sh2);
+        __shared__ double sh2[2 * (BJ_T / 64)];
+        block_sum2<BJ_T>(acc_rz, acc_rr, sh2);
         if (threadIdx.x == 0) {
             part[bid] = acc_rz;
             part[ld + bid] = acc_rr;
@@ -234,17 +259,19 @@ struct CgArgs {
 template <int N, typename T>
 hipError_t bj_cheb_n(hx_ctx *c, const T *r, T *d, T *x, double ca, double cb, int flags)
 {
-    const int cpb = BCfg<N>::CPB;
-    const int nwg = (int)((c->n_cells + cpb - 1) / cpb);
     const bool dbl = std::is_same<T, double>::value;
     const T *S = dbl ? (const T *)c->bjS64 : (const T *)c->bjS32;
     const T *L = dbl ? (const T *)c->bjL64 : (const T *)c->bjL32;
     const T *C = dbl ? (const T *)c->bjC64 : (const T *)c->bjC32;
-    hipLaunchKernelGGL((k_bj<N, T, false, true>), dim3(nwg), dim3(BCfg<N>::NT), 0, c->stream, r, d,
-                       S, L, C, (int)c->n_cells, nwg, x, (T *)nullptr, (const T *)nullptr,
-                       (const T *)nullptr, (const double *)nullptr, (double *)nullptr, 0, (T)ca,
-                       (T)cb, flags);
-    return hipGetLastError();
+    return with_bj_map<N>(c->n_cells, [&](auto wave) {
+        const int cpb = BjMap<N, wave.value>::cells(BJ_T);
+        const int nwg = (int)((c->n_cells + cpb - 1) / cpb);
+        hipLaunchKernelGGL((k_bj<N, T, wave.value, false, true>), dim3(nwg), dim3(BJ_T), 0, c->stream,
+                           r, d, S, L, C, (int)c->n_cells, nwg, x, (T *)nullptr, (const T *)nullptr,
+                           (const T *)nullptr, (const double *)nullptr, (double *)nullptr, 0, (T)ca,
+                           (T)cb, flags);
+        return hipGetLastError();
+    });
 }
 
 template <typename T>
@@ -267,23 +294,25 @@ hipError_t bj_cheb_dispatch(hx_ctx *c, const T *r, T *d, T *x, double ca, double
 template <int N, typename T>
 hipError_t bj_n(hx_ctx *c, const T *r, T *z, const CgArgs<T> *cg, int *nblk)
 {
-    const int cpb = BCfg<N>::CPB;
-    const int nwg = (int)((c->n_cells + cpb - 1) / cpb);
     const bool dbl = std::is_same<T, double>::value;
     const T *S = dbl ? (const T *)c->bjS64 : (const T *)c->bjS32;
     const T *L = dbl ? (const T *)c->bjL64 : (const T *)c->bjL32;
     const T *C = dbl ? (const T *)c->bjC64 : (const T *)c->bjC32;
-    if (nblk) *nblk = nwg;
-    if (cg)
-        hipLaunchKernelGGL((k_bj<N, T, true>), dim3(nwg), dim3(BCfg<N>::NT), 0, c->stream, r, z, S,
-                           L, C, (int)c->n_cells, nwg, cg->x, cg->r, cg->p, cg->q, cg->sc,
-                           c->cgpart, (int)c->n_cells + 1, (T)0, (T)0, 0, cg->pqp, cg->npq);
-    else
-        hipLaunchKernelGGL((k_bj<N, T, false>), dim3(nwg), dim3(BCfg<N>::NT), 0, c->stream, r, z, S,
-                           L, C, (int)c->n_cells, nwg, (T *)nullptr, (T *)nullptr,
-                           (const T *)nullptr, (const T *)nullptr, (const double *)nullptr,
-                           (double *)nullptr, 0);
-    return hipGetLastError();
+    return with_bj_map<N>(c->n_cells, [&](auto wave) {
+        const int cpb = BjMap<N, wave.value>::cells(BJ_T);
+        const int nwg = (int)((c->n_cells + cpb - 1) / cpb);
+        if (nblk) *nblk = nwg;
+        if (cg)
+            hipLaunchKernelGGL((k_bj<N, T, wave.value, true>), dim3(nwg), dim3(BJ_T), 0, c->stream, r, z, S,
+                               L, C, (int)c->n_cells, nwg, cg->x, cg->r, cg->p, cg->q, cg->sc,
+                               c->cgpart, (int)c->n_cells + 1, (T)0, (T)0, 0, cg->pqp, cg->npq);
+        else
+            hipLaunchKernelGGL((k_bj<N, T, wave.value, false>), dim3(nwg), dim3(BJ_T), 0, c->stream, r, z,
+                               S, L, C, (int)c->n_cells, nwg, (T *)nullptr, (T *)nullptr,
+                               (const T *)nullptr, (const T *)nullptr, (const double *)nullptr,
+                               (double *)nullptr, 0);
+        return hipGetLastError();
+    });
 }
 
 template <typename T>
@@ -305,13 +334,15 @@ hipError_t bj_dispatch(hx_ctx *c, const T *r, T *z, const CgArgs<T> *cg = nullpt
 template <int N>
 hipError_t bj_scaled_n(hx_ctx *c, const double *w, const double *part, int nb, double *v, double *z)
 {
-    const int cpb = BCfg<N>::CPB;
-    const int nwg = (int)((c->n_cells + cpb - 1) / cpb);
-    hipLaunchKernelGGL((k_bj<N, double, false>), dim3(nwg), dim3(BCfg<N>::NT), 0, c->stream, w, z,
-                       c->bjS64, c->bjL64, c->bjC64, (int)c->n_cells, nwg, v, (double *)nullptr,
-                       (const double *)nullptr, (const double *)nullptr, (const double *)nullptr,
-                       const_cast<double *>(part), nb);
-    return hipGetLastError();
+    return with_bj_map<N>(c->n_cells, [&](auto wave) {
+        const int cpb = BjMap<N, wave.value>::cells(BJ_T);
+        const int nwg = (int)((c->n_cells + cpb - 1) / cpb);
+        hipLaunchKernelGGL((k_bj<N, double, wave.value, false>), dim3(nwg), dim3(BJ_T), 0, c->stream, w, z,
+                           c->bjS64, c->bjL64, c->bjC64, (int)c->n_cells, nwg, v, (double *)nullptr,
+                           (const double *)nullptr, (const double *)nullptr, (const double *)nullptr,
+                           const_cast<double *>(part), nb);
+        return hipGetLastError();
+    });
 }
 
 }  // namespace

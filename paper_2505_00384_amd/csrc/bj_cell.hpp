@@ -19,15 +19,17 @@ __device__ __forceinline__ void lds_wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Cells are packed into waves, 64 / N^2 each, so that a cell's threads never
-// wait for another wave, unless that leaves too many lanes empty (N = 6: 36 of
-// 64 against 252 of 256): then N^2 consecutive threads per cell and barriers.
-// At N = 5 50 of 64 lanes work instead of 250 of 256, and the sweeps of a
-// cell take its own latency, not the slowest of four waves'.
+// Two ways of giving a cell N^2 threads.  WAVE: cells are packed into waves,
+// 64 / N^2 each, so that a cell's threads never wait for another wave; else N^2
+// consecutive threads per cell, with barriers.  BJ_WAVE: the first as the rule;
+// N = 6, where it would use 36 of 64 lanes instead of 252 of 256, has the
+// second only.
 template <int N>
+constexpr bool BJ_WAVE = 64 / (N * N) * 16 >= 256 / (N * N) * 3;
+
+template <int N, bool WAVE = BJ_WAVE<N>>
 struct BjMap {
     static constexpr int NF = N * N, CPW = 64 / NF;
-    static constexpr bool WAVE = 4 * CPW * 4 >= 3 * (256 / NF);
     // cells of a workgroup of nt threads, and a thread's cell and index in it
     // (a cell index at or past cells(nt): no cell)
     static constexpr int cells(int nt) { return WAVE ? nt / 64 * CPW : nt / NF; }

@@ -28,6 +28,7 @@ constexpr int MAXG = 8;             // highest geometry degree
 // 346 us at 128x32x32, degree 4), so its data stay in component order.
 constexpr bool face32_by_point(int n) { return n < 8; }
 constexpr int NXCD = 8;             // accelerator complex dies of the MI355X
+constexpr int NCU = 256;            // compute units
 
 // Reference data of one degree (host side, FP64).
 struct RefTab64 {

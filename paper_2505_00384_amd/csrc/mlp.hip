@@ -468,9 +468,9 @@ k_mlp_fused(int64_t n_cells, const double *__restrict__ w, double *__restrict__ 
         double unused = 0.0;
         // (the features of other waves have read r before the solve writes)
         __syncthreads();
-        bj_cell_solve<N, double, BjMap<N>::WAVE>(sR[lc], sBS[lc], sBL[lc], sBC[lc], tt % N, tt / N, active,
+        bj_cell_solve<N, double, BJ_WAVE<N>>(sR[lc], sBS[lc], sBL[lc], sBC[lc], tt % N, tt / N, active,
                                                  unused);
-        if constexpr (BjMap<N>::WAVE) __syncthreads();
+        if constexpr (BJ_WAVE<N>) __syncthreads();
     } else {
         // BJ(r) from z (loaded above), once the features have read r
         __syncthreads();

@@ -193,6 +193,32 @@ def test_block_jacobi_terrain_and_fp32():
     ctx.close()
 
 
+@pytest.mark.parametrize("cells", [2048, 2049])
+@pytest.mark.parametrize("k", [4, 6])
+def test_block_jacobi_maps_of_the_cells(k, cells):
+    """The largest mesh whose cells are packed into waves without a further
+    round of workgroups (degree 4: 256 of 8 cells, degree 6: 512 of 4) and one
+    cell more, which takes the map across waves: the plain kernel in both
+    precisions, and the forms fused into a CG and an FGMRES step, whose
+    recurrences then agree with the residual recomputed at the end."""
+    import torch
+    import paper_2505_00384_amd as hx
+    print(f"[bj] k={k} cells={cells}", flush=True)
+    p = problem(si.box_mesh(cells, 1, 1, periodic=(True, False, False), hi=(float(cells), 1.0, 1.0)), k, seed=k)
+    ctx = gpu_context(p)
+    r = si.random_vector(p.n_dofs, 13)
+    zr = p.bj_apply(r)
+    _check(ctx.apply_preconditioner(to_dev(r)).cpu().numpy(), zr, tol=1e-11)
+    z32 = ctx.apply_preconditioner(to_dev(r, torch.float32)).double().cpu().numpy()
+    assert normwise(z32, zr)[0] <= 1e-5
+    for method in (0, 1):
+        prm = hx.default_params(method=method, rtol=1e-300, max_iter=8)
+        _, info = ctx.solve(to_dev(r), params=prm, history=8)
+        assert info["iters"] == 8 and 0.0 < info["true_rel_res"] < 1.0
+        np.testing.assert_allclose(info["history"][-1], info["true_rel_res"], rtol=1e-8)
+    ctx.close()
+
+
 @pytest.mark.parametrize("k", [1, 2, 4])
 def test_operator_parts_match_oracle(k):
     """The cell integrals alone and the face terms alone against the oracle's
