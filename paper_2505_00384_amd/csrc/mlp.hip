@@ -466,10 +466,11 @@ k_mlp_fused(int64_t n_cells, const double *__restrict__ w, double *__restrict__ 
         const int lc = lc0 < FT ? lc0 : 0;
         const bool active = lc0 < FT && c0 + lc0 < n_cells;
         double unused = 0.0;
-        // (the features of other waves have read r before the solve writes)
-        __syncthreads();
-        bj_cell_solve<N, double, BJ_WAVE<N>>(sR[lc], sBS[lc], sBL[lc], sBC[lc], tt % N, tt / N, active,
-                                                 unused);
+        // (the features of other waves have read r before the solve writes: with
+        // barriers in the solve its first one sees to that; one more took 0.25
+        // of 16.4 us at N = 6)
+        if constexpr (BJ_WAVE<N>) __syncthreads();
+        bj_cell_solve<N, double, BJ_WAVE<N>>(sR[lc], sBS[lc], sBL[lc], sBC[lc], tt % N, tt / N, active, unused);
         if constexpr (BJ_WAVE<N>) __syncthreads();
     } else {
         // BJ(r) from z (loaded above), once the features have read r

@@ -189,6 +189,12 @@ def test_learned_preconditioner_parity_other_degrees(k):
         ctx.close()
 
 
+def test_learned_preconditioner_parity_at_degree_5():
+    """The one degree whose one-launch form solves its block-Jacobi systems
+    across waves, with barriers."""
+    test_learned_preconditioner_parity_other_degrees(5)
+
+
 def test_learned_preconditioner_two_launch_form():
     """On 4,352 cells (272 workgroups of 16 cells, more than one per compute
     unit of a 256-CU device) block Jacobi and the network kernel run as two
