@@ -268,9 +268,12 @@ typedef struct {
     double ms_total;     /* wall time of the solve (host clock) */
     double ms_op, ms_pc, ms_orth;  /* device time per phase (HIP events): operator,
                                       preconditioner, orthogonalisation (FGMRES) or
-                                      vector updates and dot products (CG); with a
-                                      cheap preconditioner on small systems every
-                                      seventh step is timed and scaled */
+                                      vector updates and dot products (CG).  With a
+                                      cheap preconditioner on systems below 2^22
+                                      dofs the first five steps are timed, then
+                                      every eleventh (thirteenth, if the restart
+                                      length is a multiple of 11), whose mean is
+                                      taken for the others; else every step */
     double *history;     /* optional HOST buffer: residual estimate per iteration */
     int history_len;     /* in: capacity of history; out: entries written */
 } hx_solve_info;

@@ -32,19 +32,9 @@ namespace {
 
 constexpr int64_t SC_OFF = 1024 * 66;   // device scalar area inside c->red
 
-// Phase times from HIP events on the stream.  An event between two kernels
-// costs 2 to 4 us of idle device, so on small systems with a cheap step only
-// every TIMED-th step is timed and the sums are scaled to all steps (a solve
-// of 103 CG steps at 512,000 dofs, five events a step: 5.55 ms with every
-// step timed, 4.05 without timing); from 2^22 dofs on, where a step takes
-// 300 us, and with costly preconditioners every step is.  7 shares no factor
-// with the usual restart lengths, so all positions of a cycle are met.
-constexpr int TIMED = 7;
-constexpr int64_t TIME_ALL = (int64_t)1 << 22;
-
+// Phase times from HIP events on the stream: a timer per step in flight.
 struct Timer {
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
-    double op = 0, pc = 0, orth = 0;
     bool ok = false;
     explicit Timer(bool on)
     {
@@ -62,38 +52,61 @@ struct Timer {
     {
         if (ok) (void)hipEventRecord(ev[i], s);
     }
-    float span(int i, int j)
+    float span(int i, int j) const
     {
         float t = 0;
-        return hipEventElapsedTime(&t, ev[i], ev[j]) == hipSuccess ? t : 0.0f;
+        return ok && hipEventElapsedTime(&t, ev[i], ev[j]) == hipSuccess ? t : 0.0f;
     }
-    // after a stream sync (FGMRES order ev0 < ev1 < ev2 < ev3):
-    // pc = ev0..1, op = ev1..2, orth = ev2..3
-    void acc()
+};
+
+// Sums of the phase times of a solve.  An event between two kernels costs 2 to
+// 4 us of idle device, so on small systems with a cheap step not every step is
+// timed (a solve of 103 CG steps at 512,000 dofs, five events a step: 5.55 ms
+// with every step timed, 4.05 without timing); from 2^22 dofs on, where a step
+// takes 300 us, and with costly preconditioners every step is.  The first HEAD
+// steps always are, so that a short solve is not judged by its first, cold
+// step; of the others every stride-th, whose mean stands for all of them.  The
+// stride shares no factor with the restart length, so the timed steps visit
+// all positions of a cycle, whose orthogonalisation costs grow along it.  103
+// steps: 14 timed.  The sums go to info at the end of the solve.
+constexpr int64_t TIME_ALL = (int64_t)1 << 22;
+
+struct PhaseTimes {
+    static constexpr int HEAD = 5;
+    hx_solve_info *info;
+    int stride;
+    double head[3] = {0, 0, 0};   // operator, preconditioner, orthogonalisation: the first steps,
+    double tail[3] = {0, 0, 0};   // the timed ones of the others,
+    double extra = 0;             // and orthogonalisation between the steps
+    int steps = 0, timed = 0;     // steps after the head, and those timed
+    PhaseTimes(hx_solve_info *info_, bool all, int restart)
+        : info(info_), stride(all ? 1 : (restart % 11 ? 11 : 13)) {}
+    ~PhaseTimes()
     {
-        if (!ok) return;
-        pc += span(0, 1);
-        op += span(1, 2);
-        orth += span(2, 3);
+        const double f = timed > 0 ? (double)steps / timed : 0.0;
+        info->ms_op = head[0] + tail[0] * f;
+        info->ms_pc = head[1] + tail[1] * f;
+        info->ms_orth = head[2] + tail[2] * f + extra;
     }
-    // CG order ev1 < ev2 < ev0 < ev3: op = ev1..2, p.q = ev2..0, fused
-    // updates and preconditioner = ev0..3
-    void acc_cg()
+    bool wanted(int step) const { return step < HEAD || (step - HEAD) % stride == 0; }
+    // a step that has ended (its events, if wanted, are recorded): the phases'
+    // first and last events
+    void add(int step, const Timer &t, int op0, int op1, int pc0, int pc1, int or0, int or1)
     {
-        if (!ok) return;
-        op += span(1, 2);
-        orth += span(2, 0);
-        pc += span(0, 3);
+        if (step >= HEAD) ++steps;
+        if (!wanted(step)) return;
+        if (step >= HEAD) ++timed;
+        double *sum = step < HEAD ? head : tail;
+        sum[0] += t.span(op0, op1);
+        sum[1] += t.span(pc0, pc1);
+        sum[2] += t.span(or0, or1);
     }
-    // add the second timer of two steps in flight, and scale the sums of the
-    // timed steps to all
-    void finish(const Timer &other, int timed, int all)
-    {
-        const double f = timed > 0 ? (double)all / timed : 0.0;
-        op = (op + other.op) * f;
-        pc = (pc + other.pc) * f;
-        orth = (orth + other.orth) * f;
-    }
+    // FGMRES order ev0 < ev1 < ev2 < ev3: preconditioner, operator,
+    // orthogonalisation
+    void add_fgmres(int step, const Timer &t) { add(step, t, 1, 2, 0, 1, 2, 3); }
+    // CG order ev1 < ev2 < ev0 < ev3: operator, p.q, fused updates and
+    // preconditioner
+    void add_cg(int step, const Timer &t) { add(step, t, 1, 2, 0, 3, 2, 0); }
 };
 
 // Events that the host waits on.  fast: for values the kernels have stored
@@ -305,7 +318,7 @@ hipError_t sys_apply_dot(hx_ctx *c, const hx_solve_params *prm, const double *p,
 }
 
 hx_status solve_cg(hx_ctx *c, const hx_solve_params *prm, const double *b, double *x,
-                   hx_solve_info *info, Timer &tm)
+                   hx_solve_info *info)
 {
     const int64_t n = c->n_dofs;
     hx_status s = ensure_work(c, 4 * (size_t)n, 0);
@@ -342,12 +355,10 @@ hx_status solve_cg(hx_ctx *c, const hx_solve_params *prm, const double *b, doubl
     Signals sig;
     if (!sig.ok) return fail(c, HX_ERR_DEVICE, "hipEventCreate failed");
     hipEvent_t done[2] = {nullptr, nullptr};
-    Timer tb(true);
-    Timer *tms[2] = {&tm, &tb};
+    Timer tms[2] = {Timer(true), Timer(true)};
     const bool costly = prm->pc == HX_PC_CHEBYSHEV || prm->pc == HX_PC_MULTIGRID ||
                         prm->pc == HX_PC_MULTIGRID_MIXED;
-    const int every = (costly || prm->system != 0 || n >= TIME_ALL) ? 1 : TIMED;
-    int timed = 0;
+    PhaseTimes times(info, costly || prm->system != 0 || n >= TIME_ALL, 1);
     double *hr = c->pin_host;   // slots 0, 1 (device-mapped: the reduction may write them)
     int it = 0, checked = 0;
     bool stop = false;
@@ -359,18 +370,15 @@ hx_status solve_cg(hx_ctx *c, const hx_solve_params *prm, const double *b, doubl
             err = fail(c, HX_ERR_DEVICE, "CG: event wait failed");
             return true;
         }
-        if (k % every == 0) {
-            tms[k % 2]->acc_cg();
-            ++timed;
-        }
+        times.add_cg(k, tms[k % 2]);
         const double rk = std::sqrt(hr[k % 2]) / nb;
         if (info->history && k < info->history_len) info->history[k] = rk;
         checked = k + 1;
         return !(rk > prm->rtol) || !std::isfinite(rk);
     };
     while (it < prm->max_iter && !stop) {
-        Timer &t = *tms[it % 2];
-        const bool timing = it % every == 0;
+        Timer &t = tms[it % 2];
+        const bool timing = times.wanted(it);
         if (timing) t.rec(1, c->stream);
         int npq = 0;
         if (hipSuccess != sys_apply_dot(c, prm, p, q, sc + 1, &npq)) { err = fail(c, HX_ERR_DEVICE, "CG: apply"); break; }
@@ -397,7 +405,6 @@ hx_status solve_cg(hx_ctx *c, const hx_solve_params *prm, const double *b, doubl
     }
     // the steps still in flight
     while (err == HX_OK && checked < it) check(checked);
-    tm.finish(tb, timed, it);
     if (err != HX_OK) return err;
     info->iters = it;
     info->history_len = info->history ? (it < info->history_len ? it : info->history_len) : 0;
@@ -481,7 +488,7 @@ struct Hess {
 //    finalising it.
 
 hx_status solve_fgmres(hx_ctx *c, const hx_solve_params *prm, const double *b, double *x,
-                       hx_solve_info *info, Timer &tm)
+                       hx_solve_info *info)
 {
     const int64_t n = c->n_dofs;
     const int m = prm->restart;
@@ -504,14 +511,11 @@ hx_status solve_fgmres(hx_ctx *c, const hx_solve_params *prm, const double *b, d
     Signals sig;
     if (!sig.ok) return fail(c, HX_ERR_DEVICE, "hipEventCreate failed");
     hipEvent_t *ready = sig.fast;
-    Timer tb(tm.ok);
-    Timer *tms[2] = {&tm, &tb};
+    Timer tms[2] = {Timer(true), Timer(true)};
     const bool costly = prm->mixed == 1 || prm->pc == HX_PC_CHEBYSHEV || prm->pc == HX_PC_MULTIGRID ||
                         prm->pc == HX_PC_MULTIGRID_MIXED;
-    const int every = (costly || prm->system != 0 || n >= TIME_ALL) ? 1 : TIMED;
-    int timed = 0, steps = 0;        // steps whose times were taken, and all
-    double fin_ms = 0.0;             // the cycles' extra block dots
-    Timer tfin(tm.ok);
+    PhaseTimes times(info, costly || !delayed || prm->system != 0 || n >= TIME_ALL, m);
+    Timer tfin(true);                // the cycles' extra block dots
     int nb_step[2] = {0, 0};
     double *fin_host = c->red_host;
 
@@ -552,7 +556,7 @@ hx_status solve_fgmres(hx_ctx *c, const hx_solve_params *prm, const double *b, d
         HX_HIP(c, hipMemcpyAsync(fin_host, sc, sizeof(double) * (j + 2), hipMemcpyDeviceToHost,
                                  c->stream));
         HX_HIP(c, hipStreamSynchronize(c->stream));
-        fin_ms += tfin.span(2, 3);
+        times.extra += tfin.span(2, 3);
         double cc = 0.0;
         for (int i = 0; i <= j; ++i) cc += fin_host[i] * fin_host[i];
         const double r2 = fin_host[j + 1] - cc;
@@ -576,12 +580,12 @@ hx_status solve_fgmres(hx_ctx *c, const hx_solve_params *prm, const double *b, d
         bool sw = false;
         for (int j = 0; !delayed && j < m && it < prm->max_iter; ++j) {
             double *vj = V + (size_t)j * n, *zj = Z + (size_t)j * n;
-            tm.rec(0, c->stream);
+            tms[0].rec(0, c->stream);
             if ((s = precondition(c, pc, mixed, prm->inner_iters, vj, zj, w32, &info->inner_iters)) != HX_OK)
                 return s;
-            tm.rec(1, c->stream);
+            tms[0].rec(1, c->stream);
             HX_HIP(c, step_apply(c, prm, zj, w, w32));
-            tm.rec(2, c->stream);
+            tms[0].rec(2, c->stream);
             {
                 // CGS2
                 HX_HIP(c, blas_mdot(c, n, j + 1, V, n, w, sc));
@@ -590,13 +594,11 @@ hx_status solve_fgmres(hx_ctx *c, const hx_solve_params *prm, const double *b, d
                 HX_HIP(c, blas_mupdate(c, n, j + 1, V, n, sc + 64, -1.0, w));
                 HX_HIP(c, blas_dot(c, n, w, w, sc + 128));
                 HX_HIP(c, blas_scale_copy(c, n, sc + 128, 2, w, V + (size_t)(j + 1) * n));
-                tm.rec(3, c->stream);
+                tms[0].rec(3, c->stream);
                 HX_HIP(c, hipMemcpyAsync(c->red_host, sc, sizeof(double) * 129,
                                          hipMemcpyDeviceToHost, c->stream));
                 HX_HIP(c, hipStreamSynchronize(c->stream));
-                tm.acc();
-                ++timed;
-                ++steps;
+                times.add_fgmres(it, tms[0]);
                 for (int i = 0; i <= j; ++i) H.h(i, j) = c->red_host[i] + c->red_host[64 + i];
                 const double hn = std::sqrt(c->red_host[128]);
                 H.h(j + 1, j) = hn;
@@ -633,8 +635,8 @@ hx_status solve_fgmres(hx_ctx *c, const hx_solve_params *prm, const double *b, d
         int nb_prev = 0;   // partial sums of |w|^2 of the previous step
         auto launch_step = [&](int j) -> hx_status {
             double *vj = V + (size_t)j * n, *zj = Z + (size_t)j * n;
-            Timer &t = *tms[j % 2];
-            const bool timing = (base + j) % every == 0;
+            Timer &t = tms[j % 2];
+            const bool timing = times.wanted(base + j);
             if (timing) t.rec(0, c->stream);
             if (j > 0 && fuse) {
                 if (pc == HX_PC_LEARNED) {
@@ -665,11 +667,7 @@ hx_status solve_fgmres(hx_ctx *c, const hx_solve_params *prm, const double *b, d
             if (ahead && (s = launch_step(j + 1)) != HX_OK) return s;
             if (hipEventSynchronize(ready[j % 2]) != hipSuccess)
                 return fail(c, HX_ERR_DEVICE, "FGMRES: event wait failed");
-            ++steps;
-            if ((base + j) % every == 0) {
-                tms[j % 2]->acc();
-                ++timed;
-            }
+            times.add_fgmres(base + j, tms[j % 2]);
             const double *hs = c->pin_host + (size_t)(j % 2) * FG_SLOT;
             const double rho = hs[DCGS_S + 2], hj = hs[DCGS_S + 3], flag = hs[DCGS_S + 4];
             const double nu = std::sqrt(host_sum256(hs + FG_PART, nb_step[j % 2]));
@@ -759,8 +757,6 @@ hx_status solve_fgmres(hx_ctx *c, const hx_solve_params *prm, const double *b, d
             }
         }
     }
-    tm.finish(tb, timed, steps);
-    tm.orth += fin_ms;
     info->iters = it;
     info->history_len = info->history ? hist : 0;
     return HX_OK;
@@ -930,9 +926,7 @@ hx_status hx_solve(hx_ctx *c, const hx_solve_params *prm, const double *b, doubl
         return fail(c, HX_ERR_ARG, "the pressure system is not symmetric; use FGMRES");
     HX_HIP(c, hipSetDevice(c->device));
     const double t0 = now_ms();
-    Timer tm(true);
-    hx_status s = prm->method == 0 ? solve_cg(c, prm, b, x, info, tm)
-                                   : solve_fgmres(c, prm, b, x, info, tm);
+    hx_status s = prm->method == 0 ? solve_cg(c, prm, b, x, info) : solve_fgmres(c, prm, b, x, info);
     if (s != HX_OK && s != HX_ERR_NOCONV) {
         info->status = s;
         return s;
@@ -949,9 +943,6 @@ hx_status hx_solve(hx_ctx *c, const hx_solve_params *prm, const double *b, doubl
     if ((s2 = read_scalars(c, sc + 200, 2, hh)) != HX_OK) return s2;
     info->true_rel_res = hh[1] > 0 ? std::sqrt(hh[0] / hh[1]) : 0.0;
     info->ms_total = now_ms() - t0;
-    info->ms_op = tm.op;
-    info->ms_pc = tm.pc;
-    info->ms_orth = tm.orth;
     const bool conv = info->true_rel_res <= prm->rtol * 1.0001;
     hx_status st = conv ? (info->fallback_used ? HX_FALLBACK_USED : HX_OK) : HX_ERR_NOCONV;
     info->status = st;

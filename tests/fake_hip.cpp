@@ -3,6 +3,7 @@
 // binds to these instead of the runtime's.  Kernels do not run; of a few of
 // them the launch writes the values that the host code goes on with.  Built and
 // run by test_host_paths.py; the first argument names the scenario.
+#include <cmath>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -27,6 +28,7 @@ struct State {
     std::map<const void *, std::string> kernels;     // host stub -> name
     std::map<char *, size_t> live;                   // allocations
     int n_dev = 1, dev = 0;
+    double clock = 0.0;                              // ms, advanced by on_launch
     std::function<void(const Launch &)> on_launch;
 };
 // (the library registers its kernels before this program's own objects exist)
@@ -120,6 +122,74 @@ void device_of_expansion()
     hx_destroy(c);
 }
 
+// The phase times that a solve reports, on a clock that the launches advance:
+// the block dots of step j of a cycle cost 1 + j / 4, a launch of the solve's
+// first step 20, every other one 1.  The first five steps are exact; the estimate for
+// the others is near the sum over all steps, whatever the restart length.
+void phase_times()
+{
+    hx_ctx *c = context(0, 2);
+    coefficients(c);
+    const int64_t n = hx_num_dofs(c);
+    std::vector<double> b(n, 1.0), x(n);
+    for (int method = 0; method < 2; ++method)
+        for (int restart : {5, 7, 11, 13, 14, 22, 30, 48})
+            for (int iters : {1, 2, 5, 7, 9, 16, 140, 300}) {
+                bool first = true;
+                double op = 0.0, pc = 0.0, orth = 0.0;
+                bool started = false;
+                st().on_launch = [&](const Launch &l) {
+                    auto is = [&](const char *k) { return l.name.find(k) != std::string::npos; };
+                    double cost = first ? 20.0 : 1.0;
+                    if (is("k_dcgs_dot")) cost += 0.25 * arg<int>(l, 1);
+                    st().clock += cost;
+                    // what the host reads: |.|^2 of a dot product, the step's scalars
+                    if (is("k_red2")) std::fill_n(arg<double *>(l, 3), l.grid, 1.0);
+                    if (is("k_dcgs_coef")) {
+                        double *h = arg<double *>(l, 4);
+                        std::fill_n(h, 128, 0.0);
+                        h[366] = h[367] = 1.0;   // rho, the column's diagonal entry
+                        h[368] = 0.0;
+                    }
+                    if (is("k_dcgs_update")) {
+                        std::fill_n(arg<double *>(l, 8), l.grid, 0.0);
+                        arg<double *>(l, 8)[0] = 1.0;
+                    }
+                    if (is("k_cg_pt_red")) *arg<double *>(l, 8) = 1.0;
+                    if (is("k_dcgs_update") || is("k_cg_pt_red")) first = false;
+                    // the phases (the residual form, with a right-hand side, and
+                    // the first preconditioner of CG are outside the steps)
+                    if (is("k_apply") && !arg<void *>(l, 2)) {
+                        op += cost;
+                        started = true;
+                    } else if (is("k_bj") && (method == 1 || started)) {
+                        pc += cost;
+                    } else if (is("k_dcgs") || is("k_mdot1")) {
+                        orth += cost;
+                    }
+                };
+                hx_solve_params prm;
+                hx_default_params(&prm);
+                prm.method = method;
+                prm.restart = restart;
+                prm.max_iter = iters;
+                prm.rtol = 1e-300;
+                hx_solve_info info{};
+                hx_solve(c, &prm, b.data(), x.data(), &info);
+                st().on_launch = nullptr;
+                char what[200];
+                snprintf(what, sizeof what, "method %d restart %d: %d of %d steps, op %.1f (%.1f) pc %.1f (%.1f) orth %.1f (%.1f)",
+                         method, restart, info.iters, iters, info.ms_op, op, info.ms_pc, pc, info.ms_orth, orth);
+                check(info.iters == iters, what);
+                const double tol = iters <= 5 ? 1e-5 : 0.1;
+                auto near = [&](double a, double ref) { return std::fabs(a - ref) <= tol * ref; };
+                check(near(info.ms_op, op) && near(info.ms_pc, pc), what);
+                // (a cycle's last block dot is summed by a launch of its own)
+                if (method == 1) check(std::fabs(info.ms_orth - orth) <= tol * orth + 25.0 * (1 + iters / restart), what);
+            }
+    hx_destroy(c);
+}
+
 }  // namespace
 
 extern "C" {
@@ -188,15 +258,16 @@ int hipMemcpyAsync(void *d, const void *s, size_t n, int, void *) { return memmo
 int hipMemsetAsync(void *d, int v, size_t n, void *) { return memset(d, v, n), 0; }
 int hipEventCreateWithFlags(double **e, unsigned) { return *e = new double(0.0), 0; }
 int hipEventDestroy(double *e) { return delete e, 0; }
-int hipEventRecord(double *, void *) { return 0; }
+int hipEventRecord(double *e, void *) { return *e = st().clock, 0; }
 int hipEventSynchronize(double *) { return 0; }
-int hipEventElapsedTime(float *t, double *, double *) { return *t = 0.0f, 0; }
+int hipEventElapsedTime(float *t, double *a, double *b) { return *t = (float)(*b - *a), 0; }
 }
 
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "device") device_of_expansion();
+    else if (what == "times") phase_times();
     else check(false, "unknown scenario");
     check(st().live.empty(), "device memory left allocated");
     printf("%s: %d failures\n", what.c_str(), failures);
