@@ -93,7 +93,7 @@ static hx_status update_visit_masks(hx_ctx *c)
     const std::vector<int32_t> &order = *c->order_h, &nb = *c->nbr_h;
     const std::vector<uint8_t> &ct = *c->ctype_h;
     const size_t nc = (size_t)c->n_cells;
-    const int cpw = op_cells_per_wave(c->n);
+    const int cpw = 64 / op_lanes(c->n);
     auto record = [&](int32_t *r, int32_t cell, int aff) {
         int32_t mask = aff;
         for (int f = 0; f < 6; ++f) {

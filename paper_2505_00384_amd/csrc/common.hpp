@@ -30,6 +30,22 @@ constexpr bool face32_by_point(int n) { return n < 8; }
 constexpr int NXCD = 8;             // accelerator complex dies of the MI355X
 constexpr int NCU = 256;            // compute units
 
+constexpr int pow2_at_least(int v)
+{
+    int p = 1;
+    while (p < v) p *= 2;
+    return p;
+}
+// Lanes of a wave per cell in the operator kernel at n points per direction:
+// n^2 pencils, 6 n face columns.  The traversal records are grouped in waves of
+// 64 / op_lanes(n) cells of one kind, and whoever reads a wave's kind from its
+// first record groups them so too.
+constexpr int op_lanes(int n)
+{
+    const int p = pow2_at_least(n > 6 ? n * n : 6 * n);
+    return p < 64 ? p : 64;
+}
+
 // Reference data of one degree (host side, FP64).
 struct RefTab64 {
     double xq[MAXN], wq[MAXN], xl[MAXN];   // GL points/weights, GLL nodes on [0,1]
@@ -299,8 +315,6 @@ hipError_t launch_hang_geometry(hx_ctx *c);
 hipError_t launch_hang_coefficients(hx_ctx *c, const double *beta);
 hipError_t launch_hang_apply64(hx_ctx *c, const double *x, double *y, bool residual);
 hipError_t launch_hang_apply32(hx_ctx *c, const float *x, float *y, bool residual);
-// cells per wave of the operator kernel at n points per direction
-int op_cells_per_wave(int n);
 // one part of A x: part 1 the cell integrals only, part 2 the face terms only
 hipError_t launch_apply_part64(hx_ctx *c, int part, const double *x, double *y);
 hipError_t launch_apply_part32(hx_ctx *c, int part, const float *x, float *y);

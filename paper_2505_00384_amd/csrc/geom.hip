@@ -439,18 +439,11 @@ __global__ void k_affine_detect(const double *__restrict__ nodes, int ng, int nd
 // geometric factors loaded plane by plane, 0.32 to 0.44: more concurrent
 // streams only scatter the writes).
 // -------------------------------------------------------------------------
-constexpr int lanes_for(int v)
-{
-    int p = 1;
-    while (p < v) p *= 2;
-    return p;
-}
-
 template <int N>
 struct SCfg {
-    static constexpr int NF = N * N, ND = NF * N, LPC = lanes_for(NF), CPW = 64 / LPC;
+    static constexpr int NF = N * N, ND = NF * N, LPC = pow2_at_least(NF), CPW = 64 / LPC;
     // face kernel: 6 N columns per cell
-    static constexpr int FLPC = lanes_for(6 * N), FCPW = 64 / FLPC;
+    static constexpr int FLPC = pow2_at_least(6 * N), FCPW = 64 / FLPC;
     static_assert(NF <= 64 && 6 * N <= 64, "one wave per cell at most");
 };
 

@@ -166,18 +166,10 @@ __device__ __forceinline__ void contract_t2(const T (&u)[N], const T (&v)[N], T 
     acc.out(y);
 }
 
-constexpr int pow2_at_least(int v)
-{
-    int p = 1;
-    while (p < v) p *= 2;
-    return p;
-}
-
 template <int N>
 struct Cfg {
     static constexpr int NF = N * N, ND = N * N * N;
-    static constexpr int LPC = pow2_at_least(NF > 6 * N ? NF : 6 * N) > 64
-                                   ? 64 : pow2_at_least(NF > 6 * N ? NF : 6 * N);
+    static constexpr int LPC = op_lanes(N);
     static constexpr int CPW = 64 / LPC;                       // cells per wave
     static constexpr int GS = (18 * NF > 3 * ND) ? 18 * NF : 3 * ND;  // work area per cell
     static_assert(NF <= 64 && 6 * N <= 64, "one wave per cell at most");
@@ -1211,20 +1203,6 @@ hipError_t launch_apply_part64(hx_ctx *c, int part, const double *x, double *y)
 hipError_t launch_apply_part32(hx_ctx *c, int part, const float *x, float *y)
 {
     return apply_dispatch<float>(c, x, y, nullptr, nullptr, nullptr, part);
-}
-
-// cells per wave of the operator kernel at n = k + 1 points per direction
-int op_cells_per_wave(int n)
-{
-    switch (n) {
-    case 2: return Cfg<2>::CPW;
-    case 3: return Cfg<3>::CPW;
-    case 4: return Cfg<4>::CPW;
-    case 5: return Cfg<5>::CPW;
-    case 6: return Cfg<6>::CPW;
-    case 7: return Cfg<7>::CPW;
-    default: return Cfg<8>::CPW;
-    }
 }
 
 // y = A x and x.y (summed in a fixed order): the per-workgroup partial sums

@@ -57,15 +57,6 @@ constexpr int GRAD_T = 64, DIV_T = 128;
 template <int N> constexpr int grad_nt() { return PCfg<N, GRAD_T>::NT; }
 template <int N> constexpr int div_nt() { return PCfg<N, DIV_T>::NT; }
 
-// lanes per cell of the operator's traversal records (op_cells_per_wave)
-constexpr int op_lanes(int n)
-{
-    const int need = n * n > 6 * n ? n * n : 6 * n;
-    int p = 1;
-    while (p < need) p *= 2;
-    return p < 64 ? p : 64;
-}
-
 // order of LDS accesses between the lanes of one wave, whose LDS operations
 // execute in order: only the compiler has to keep them so
 __device__ __forceinline__ void press_sync()
