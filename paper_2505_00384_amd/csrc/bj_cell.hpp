@@ -8,16 +8,9 @@
 
 #include <hip/hip_runtime.h>
 
-namespace hx {
+#include "wave_sync.hpp"
 
-// Order of LDS accesses between the lanes of one wave, whose LDS operations
-// execute in order: only the compiler has to keep them so.
-__device__ __forceinline__ void lds_wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
+namespace hx {
 
 // Two ways of giving a cell N^2 threads.  WAVE: cells are packed into waves,
 // 64 / N^2 each, so that a cell's threads never wait for another wave; else N^2

@@ -44,6 +44,7 @@
 // 36.4 / 26.4 (the former form 29.5).  N = 6 is slower without the LDS copy
 // (923 us), and two cell waves lose at N = 5 (521), 6 (1032) and 7 (1783).
 #include "common.hpp"
+#include "wave_sync.hpp"
 
 namespace hx {
 namespace {
@@ -78,21 +79,13 @@ struct QCfg {
     static_assert(NF <= 64 && FPW * Q <= 64, "one row lane per face row");
 };
 
-// order of LDS accesses between the lanes of one wave
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // between the sweeps: the waves of a role wait for each other, if there are two
 // by the workgroup's barrier, which the other role then meets as often
 template <int N>
 __device__ __forceinline__ void q_sync()
 {
     if constexpr (QCfg<N>::CW > 1) __syncthreads();
-    else wave_sync();
+    else lds_wave_sync();
 }
 
 // y = B u (W = 0) or BD u (W = 1), n -> nq

@@ -23,6 +23,7 @@
 // the face-layer nodes, and the pencil owners add them.  Each output is
 // written by one thread: no atomics, bitwise reproducible.
 #include "common.hpp"
+#include "wave_sync.hpp"
 
 namespace hx {
 namespace {
@@ -56,15 +57,6 @@ struct PCfg {
 constexpr int GRAD_T = 64, DIV_T = 128;
 template <int N> constexpr int grad_nt() { return PCfg<N, GRAD_T>::NT; }
 template <int N> constexpr int div_nt() { return PCfg<N, DIV_T>::NT; }
-
-// order of LDS accesses between the lanes of one wave, whose LDS operations
-// execute in order: only the compiler has to keep them so
-__device__ __forceinline__ void press_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // cell-local index of face-layer node (e1, e2) at normal coordinate m of
 // direction d; e1, e2 run along the tangential directions t1 < t2
@@ -779,7 +771,7 @@ __device__ __forceinline__ void sys_cell(const double *__restrict__ x, double *_
         to_points<N>(u, t);
         L.template put<0>(F, t);
     }
-    press_sync();
+    lds_wave_sync();
 #pragma unroll
     for (int c = 0; c < COLS; ++c) {
         if (!fl[c]) continue;
@@ -795,13 +787,13 @@ __device__ __forceinline__ void sys_cell(const double *__restrict__ x, double *_
         to_points<N>(u, t);
         L.template put<1>(F, t);
     }
-    press_sync();
+    lds_wave_sync();
     if (cl) {
         L.template get<2>(F, u);
         to_points<N>(u, pz);
         L.template put<2>(F, pz);
     }
-    press_sync();
+    lds_wave_sync();
     // ---- face means x^ at the lane's point of each face (a: first, b: second
     // tangential direction), times tau
     double ph[6];
@@ -817,7 +809,7 @@ __device__ __forceinline__ void sys_cell(const double *__restrict__ x, double *_
 #pragma unroll
         for (int g = 0; g < 6; ++g) ph[g] = tau * (inner[g] ? 0.5 * (ph[g] + P[g * NF + ln]) : ph[g]);
     }
-    press_sync();
+    lds_wave_sync();
     double rz[N], fx[6];
     if constexpr (AFF) {
         // H_d along the lines of d; H_x and H_y pass to the z lines in F0, F1
@@ -838,7 +830,7 @@ __device__ __forceinline__ void sys_cell(const double *__restrict__ x, double *_
             line(pz, ph[4], ph[5], hz);
             load_line<N>(mr + o + L.z, NF, mi);
         }
-        press_sync();
+        lds_wave_sync();
         // v_e = sum_d K_de H_d / mr and a_d = sum_e K_de v_e
         if (cl) {
             double hx[N], hy[N];
@@ -857,7 +849,7 @@ __device__ __forceinline__ void sys_cell(const double *__restrict__ x, double *_
             L.template put<2>(F, hx);
             L.template put<2>(F + ND, hy);
         }
-        press_sync();
+        lds_wave_sync();
         auto cline = [&](const double (&ad)[N], const double (&hl)[N], double &f0, double &f1, double (&out)[N]) {
             f0 = -wab * at_end<N>(0, ad);
             f1 = wab * at_end<N>(1, ad);
@@ -880,12 +872,12 @@ __device__ __forceinline__ void sys_cell(const double *__restrict__ x, double *_
 #pragma unroll
             for (int q = 0; q < N; ++q) rz[q] += K[9] * wab * wq[q] * pz[q];
         }
-        press_sync();
+        lds_wave_sync();
         if (cl) {
             L.template put<0>(F, c0);
             L.template put<1>(F + ND, c1);
         }
-        press_sync();
+        lds_wave_sync();
         if (cl) {
             L.template get<2>(F, c0);
             L.template get<2>(F + ND, c1);
@@ -912,7 +904,7 @@ __device__ __forceinline__ void sys_cell(const double *__restrict__ x, double *_
                 gline(px, Wx[e], ph[0] * n6[0][e], ph[1] * n6[1][e], g);
                 L.template put<0>(F + e * ND, g);
             }
-        press_sync();
+        lds_wave_sync();
         if (cl)
 #pragma unroll
             for (int e = 0; e < 3; ++e) {
@@ -921,7 +913,7 @@ __device__ __forceinline__ void sys_cell(const double *__restrict__ x, double *_
                 gline(py, Wy[e], ph[2] * n6[2][e], ph[3] * n6[3][e], g);
                 L.template put<1>(F + e * ND, g);
             }
-        press_sync();
+        lds_wave_sync();
         if (cl) {
             double mi[N];
             load_line<N>(mr + o + L.z, NF, mi);
@@ -936,7 +928,7 @@ __device__ __forceinline__ void sys_cell(const double *__restrict__ x, double *_
                 L.template put<2>(F + e * ND, v[e]);
             }
         }
-        press_sync();
+        lds_wave_sync();
         // own fluxes and hr sum_e W_de v_e on the lines of d, its DG^T
         auto cline = [&](const double (&ve)[3][N], const double (&w)[3][N], const double (&hl)[N], int f0,
                          double (&out)[N]) {
@@ -972,12 +964,12 @@ __device__ __forceinline__ void sys_cell(const double *__restrict__ x, double *_
             load_line<N>(hr + o + L.y, N, hl);
             cline(v, Wy, hl, 2, c1);
         }
-        press_sync();
+        lds_wave_sync();
         if (cl) {
             L.template put<0>(F, c0);
             L.template put<1>(F + ND, c1);
         }
-        press_sync();
+        lds_wave_sync();
         if (cl) {
             L.template get<2>(F, c0);
             L.template get<2>(F + ND, c1);
@@ -1055,7 +1047,7 @@ k_sys_face(const double *__restrict__ r, const double *__restrict__ flux, const 
 #pragma unroll
         for (int f = 0; f < 4; ++f) P[f * NF + ln] = g[f];
     }
-    press_sync();
+    lds_wave_sync();
     if (cl) {
         double ex[2] = {0.0, 0.0}, ey[2] = {0.0, 0.0};   // E at the lane's x and y index
 #pragma unroll
@@ -1084,13 +1076,13 @@ k_sys_face(const double *__restrict__ r, const double *__restrict__ flux, const 
         back(u, t);
         L.template put<2>(F, t);
     }
-    press_sync();
+    lds_wave_sync();
     if (cl) {
         L.template get<1>(F, u);
         back(u, t);
         L.template put<1>(F, t);
     }
-    press_sync();
+    lds_wave_sync();
     if (cl) {
         L.template get<0>(F, u);
         back(u, t);
