@@ -897,9 +897,9 @@ k_train_wgrad(int64_t B, int ksteps, int per, WGrad g, TrainBuf t, float *__rest
 }
 
 // Parameters, one per thread: with chunks > 0 the gradient (the chunks' sums
-// in order) to grad and grad_out, with update the Adam step; the BF16 copies
-// of the weight in each layout that a product reads: row-major for the
-// batched forward pass, and fragment order (columns of W and of W^T) for the
+// in order) to grad_out, with update the Adam step; the BF16 copies of the
+// weight in each layout that a product reads: row-major for the batched forward
+// pass, and fragment order (columns of W and of W^T) for the
 // fused kernels.  The padding of the copies is zeroed once, at creation.
 //
 // Fragment order of W for v_mfma_f32_16x16x32_bf16: for column tile ct (16
@@ -911,7 +911,7 @@ k_train_wgrad(int64_t B, int ksteps, int per, WGrad g, TrainBuf t, float *__rest
 struct Params {
     int n_in, n_out, ldx;
     int64_t off_b1, off_w2, off_b2, off_w3, off_b3, P;
-    float *w, *m, *v, *grad;
+    float *w, *m, *v;
     uint16_t *w1b, *w2b, *w3b, *wfr, *wbk;
 };
 
@@ -957,7 +957,6 @@ k_params(Params p, int chunks, const float *__restrict__ part, const double *__r
             for (int k = 0; k < chunks; ++k) s += (double)part[(int64_t)k * p.P + i];
             g = (float)s;
         }
-        p.grad[i] = g;
         if (grad_out) grad_out[i] = g;
         if (!update) return;
         const float mi = b1 * p.m[i] + (1.f - b1) * g;
@@ -1029,7 +1028,7 @@ struct MlpState {
     int n_in = 0, ldx = 0, n_out = 0;
     int64_t P = 0;
     int64_t off_w1 = 0, off_b1 = 0, off_w2 = 0, off_b2 = 0, off_w3 = 0, off_b3 = 0;
-    float *w = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr;
+    float *w = nullptr, *m = nullptr, *v = nullptr;
     uint16_t *w1b = nullptr, *w2b = nullptr, *w3b = nullptr;
     uint16_t *wfr = nullptr;   // the three layers in the fused kernels' fragment order
     uint16_t *wbk = nullptr;   // W3^T, W2^T in the backward products' fragment order
@@ -1149,7 +1148,6 @@ hx_status mlp_create(hx_ctx *c)
     A(s->w, 4 * (size_t)s->P);
     A(s->m, 4 * (size_t)s->P);
     A(s->v, 4 * (size_t)s->P);
-    A(s->grad, 4 * (size_t)s->P);
     A(s->w1b, 2 * (size_t)HID * s->ldx);
     A(s->w2b, 2 * (size_t)HID * HID);
     A(s->w3b, 2 * (size_t)s->n_out * HID);
@@ -1183,10 +1181,9 @@ void mlp_destroy(hx_ctx *c)
     if (!s) return;
     free_batch(s);
     free_train(s);
-    void **b[] = {(void **)&s->w, (void **)&s->m, (void **)&s->v, (void **)&s->grad,
-                  (void **)&s->w1b, (void **)&s->w2b, (void **)&s->w3b, (void **)&s->wfr,
-                  (void **)&s->wbk, (void **)&s->gpart, (void **)&s->bpart, (void **)&s->loss,
-                  (void **)&s->zt};
+    void **b[] = {(void **)&s->w, (void **)&s->m, (void **)&s->v, (void **)&s->w1b, (void **)&s->w2b,
+                  (void **)&s->w3b, (void **)&s->wfr, (void **)&s->wbk, (void **)&s->gpart,
+                  (void **)&s->bpart, (void **)&s->loss, (void **)&s->zt};
     for (void **p : b) dfree(p);
     if (s->loss_host) (void)hipHostFree(s->loss_host);
     delete s;
@@ -1199,7 +1196,7 @@ static hipError_t params_step(hx_ctx *c, int chunks, float *grad_out, float lr)
 {
     MlpState *s = c->mlp;
     const Params p{s->n_in, s->n_out, s->ldx, s->off_b1, s->off_w2, s->off_b2, s->off_w3, s->off_b3, s->P,
-                   s->w, s->m, s->v, s->grad, s->w1b, s->w2b, s->w3b, s->wfr, s->wbk};
+                   s->w, s->m, s->v, s->w1b, s->w2b, s->w3b, s->wfr, s->wbk};
     const float b1 = 0.9f, b2 = 0.999f;
     float c1 = 1.f, c2 = 1.f;
     if (lr != 0.0f) {
