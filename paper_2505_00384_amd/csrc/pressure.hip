@@ -608,17 +608,11 @@ __device__ __forceinline__ void load_line(const double *__restrict__ p, int stri
     for (int i = 0; i < N; ++i) v[i] = p[i * stride];
 }
 
-// DG(q, r) = sum_i BD(q, i) B^-1(i, r): derivative at point q of the basis
-// function of point r; E(s, r): that function at end s
-template <int N>
-__device__ __forceinline__ constexpr double tDG(int q, int r)
-{
-    double s = 0.0;
-    for (int i = 0; i < N; ++i) s += tD<N>(q, i) * tBi<N>(i, r);
-    return s;
-}
+// E(s, r): value at end s of the basis function of point r
 template <int N>
 __device__ __forceinline__ constexpr double tE(int s, int r) { return tBi<N>(s ? N - 1 : 0, r); }
+// DG(q, r) = sum_i BD(q, i) B^-1(i, r): derivative at point q of the basis
+// function of point r
 template <int N>
 struct DGTab {
     double d[N * N];
