@@ -39,6 +39,16 @@ void dfree(void **p)
     *p = nullptr;
 }
 
+hx_status dalloc_all(hx_ctx *c, std::initializer_list<Buffer> bufs)
+{
+    hx_status s = HX_OK;
+    for (const Buffer &b : bufs)
+        if ((s = dalloc(c, b.p, b.bytes)) != HX_OK) break;
+    if (s != HX_OK)
+        for (const Buffer &b : bufs) dfree(b.p);
+    return s;
+}
+
 static void free_mesh(hx_ctx *c)
 {
     void **bufs[] = {(void **)&c->nodes, (void **)&c->nbr, (void **)&c->visit, (void **)&c->visitp, (void **)&c->ref, (void **)&c->vol,
@@ -546,18 +556,11 @@ hx_status hx_set_pressure_system(hx_ctx *c, const double *rho, const double *h, 
     const int64_t n = c->n_dofs, nc = c->n_cells;
     hx_status s = HX_OK;
     if (!c->psW) {
-        auto al = [&](double **p, size_t count) {
-            if (s == HX_OK) s = dalloc(c, (void **)p, sizeof(double) * count);
-        };
-        al(&c->psW, (size_t)nc * 9 * c->nd);
-        al(&c->psWC, (size_t)nc * 9 * c->nd);
-        al(&c->psMr, (size_t)n);
-        al(&c->psMd, (size_t)n);
-        al(&c->psHr, (size_t)n);
-        al(&c->psK, (size_t)nc * 16);
-        al(&c->psFn, (size_t)nc * 18 * c->nf);
-        al(&c->psFh, (size_t)nc * 6 * c->nf);
-        al(&c->psWork, (size_t)7 * n);
+        auto d = [](double *&p, size_t count) { return Buffer{(void **)&p, sizeof(double) * count}; };
+        s = dalloc_all(c, {d(c->psW, (size_t)nc * 9 * c->nd), d(c->psWC, (size_t)nc * 9 * c->nd),
+                           d(c->psMr, n), d(c->psMd, n), d(c->psHr, n), d(c->psK, (size_t)nc * 16),
+                           d(c->psFn, (size_t)nc * 18 * c->nf), d(c->psFh, (size_t)nc * 6 * c->nf),
+                           d(c->psWork, (size_t)7 * n)});
         if (s != HX_OK) return s;
     }
     // fields on the device: [rho, h, alpha, beta]
@@ -594,9 +597,10 @@ hx_status hx_set_consistent(hx_ctx *c, const double *alpha, const double *beta, 
     const int nq = 2 * c->n - 1;
     hx_status s = HX_OK;
     if (!c->qcell) {
-        if ((s = dalloc(c, (void **)&c->refq, sizeof(RefTabQ))) != HX_OK) return s;
-        if ((s = dalloc(c, (void **)&c->qcell, sizeof(double) * nc * 7 * nq * nq * nq)) != HX_OK) return s;
-        if ((s = dalloc(c, (void **)&c->qface, sizeof(double) * nc * 3 * 7 * nq * nq)) != HX_OK) return s;
+        s = dalloc_all(c, {{(void **)&c->refq, sizeof(RefTabQ)},
+                           {(void **)&c->qcell, sizeof(double) * nc * 7 * nq * nq * nq},
+                           {(void **)&c->qface, sizeof(double) * nc * 3 * 7 * nq * nq}});
+        if (s != HX_OK) return s;
     }
     c->nq = nq;
     RefTabQ tq;

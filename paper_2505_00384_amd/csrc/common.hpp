@@ -5,6 +5,7 @@
 
 #include <cstdint>
 #include <cstdio>
+#include <initializer_list>
 #include <string>
 #include <vector>
 
@@ -231,6 +232,12 @@ hx_status fail(hx_ctx *c, hx_status s, const char *fmt, ...);
     } while (0)
 
 hx_status dalloc(hx_ctx *c, void **p, size_t bytes);
+// all of the buffers or, when one cannot be had, none
+struct Buffer {
+    void **p;
+    size_t bytes;
+};
+hx_status dalloc_all(hx_ctx *c, std::initializer_list<Buffer> bufs);
 void build_traversal(const int32_t *nbr, int64_t n_cells, int32_t *order);
 void dfree(void **p);
 

@@ -1018,8 +1018,8 @@ hx_status hx_set_chebyshev(hx_ctx *c, int degree, double lo, double hi)
     if (!(lo > 0.0) || !(hi > lo) || !std::isfinite(hi)) return fail(c, HX_ERR_ARG, "need 0 < lo < hi");
     HX_HIP(c, hipSetDevice(c->device));
     if (!c->chebw) {
-        hx_status s = dalloc(c, (void **)&c->chebw, sizeof(double) * 2 * c->n_dofs);
-        if (s == HX_OK) s = dalloc(c, (void **)&c->chebw32, sizeof(float) * 2 * c->n_dofs);
+        const hx_status s = dalloc_all(c, {{(void **)&c->chebw, sizeof(double) * 2 * c->n_dofs},
+                                           {(void **)&c->chebw32, sizeof(float) * 2 * c->n_dofs}});
         if (s != HX_OK) return s;
     }
     c->cheb_deg = degree;
@@ -1068,10 +1068,9 @@ hx_status hx_set_multigrid(hx_ctx *c, hx_ctx *coarse, const int32_t *parent, con
     hx_status s = dalloc(c, (void **)&c->mg_cptr, sizeof(int32_t) * (nc + 1));
     if (s == HX_OK) s = dalloc(c, (void **)&c->mg_clist, sizeof(int32_t) * nf);
     for (hx_ctx *L : {c, coarse})
-        if (s == HX_OK && !L->mgw) {
-            s = dalloc(L, (void **)&L->mgw, sizeof(double) * 3 * L->n_dofs);
-            if (s == HX_OK) s = dalloc(L, (void **)&L->mgw32, sizeof(float) * 3 * L->n_dofs);
-        }
+        if (s == HX_OK && !L->mgw)
+            s = dalloc_all(L, {{(void **)&L->mgw, sizeof(double) * 3 * L->n_dofs},
+                               {(void **)&L->mgw32, sizeof(float) * 3 * L->n_dofs}});
     if (s != HX_OK) return s;
     HX_HIP(c, hipMemcpy(c->mg_cptr, ptr.data(), sizeof(int32_t) * (nc + 1), hipMemcpyHostToDevice));
     HX_HIP(c, hipMemcpy(c->mg_clist, list.data(), sizeof(int32_t) * nf, hipMemcpyHostToDevice));

@@ -28,6 +28,7 @@ struct State {
     std::map<const void *, std::string> kernels;     // host stub -> name
     std::map<char *, size_t> live;                   // allocations
     int n_dev = 1, dev = 0;
+    int allocations_left = -1;                       // then hipMalloc fails once (-1: never)
     double clock = 0.0;                              // ms, advanced by on_launch
     std::function<void(const Launch &)> on_launch;
 };
@@ -190,6 +191,48 @@ void phase_times()
     hx_destroy(c);
 }
 
+// A call that runs out of memory at any of its allocations reports that, and
+// made again it has every buffer that it has at the first attempt elsewhere,
+// and none twice.
+void failed_allocations()
+{
+    const std::vector<int32_t> parent{0, 1}, octant{0, 0};
+    const char *names[] = {"pressure system", "consistent", "Chebyshev", "multigrid"};
+    for (int call = 0; call < 4; ++call) {
+        size_t buffers = 0;
+        int n = -1;   // allocations before the one that fails; -1: none fails
+        for (bool more = true; more; ++n) {
+            hx_ctx *c = context(0, 2), *coarse = context(0, 2);
+            coefficients(c);
+            const std::vector<double> one(hx_num_dofs(c), 1.0);
+            auto run = [&] {
+                switch (call) {
+                case 0: return hx_set_pressure_system(c, one.data(), one.data(), 1.4, 1.0, 2.0, 0);
+                case 1: return hx_set_consistent(c, one.data(), one.data(), 0);
+                case 2: return hx_set_chebyshev(c, 3, 0.1, 2.0);
+                default: return hx_set_multigrid(c, coarse, parent.data(), octant.data());
+                }
+            };
+            st().allocations_left = n;
+            const hx_status s = run();
+            more = n < 0 || s != HX_OK;
+            st().allocations_left = -1;
+            if (n >= 0 && more) {
+                check(s == HX_ERR_OOM, names[call]);
+                check(run() == HX_OK, names[call]);
+            }
+            if (n < 0) buffers = st().live.size();
+            char what[100];
+            snprintf(what, sizeof what, "%s, allocation %d refused: %zu buffers, not %zu", names[call], n,
+                     st().live.size(), buffers);
+            check(st().live.size() == buffers, what);
+            hx_destroy(c);
+            hx_destroy(coarse);
+        }
+        check(n > 2, "allocations were refused");
+    }
+}
+
 }  // namespace
 
 extern "C" {
@@ -235,6 +278,7 @@ int hipGetLastError() { return 0; }
 const char *hipGetErrorString(int) { return "refused"; }
 int hipMalloc(void **p, size_t n)
 {
+    if (st().allocations_left >= 0 && st().allocations_left-- == 0) return 2;
     *p = calloc(n, 1);
     st().live[(char *)*p] = n;
     return 0;
@@ -268,6 +312,7 @@ int main(int argc, char **argv)
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "device") device_of_expansion();
     else if (what == "times") phase_times();
+    else if (what == "memory") failed_allocations();
     else check(false, "unknown scenario");
     check(st().live.empty(), "device memory left allocated");
     printf("%s: %d failures\n", what.c_str(), failures);
