@@ -97,7 +97,7 @@ struct hx_ctx {
 
     double *nodes = nullptr;      // [n_cells][(g+1)^3][3]
     int32_t *nbr = nullptr;       // [n_cells][6]
-    int32_t *visit = nullptr;     // [n_cells][8] operator traversal: {cell, 6 neighbours, 0}
+    int32_t *visit = nullptr;     // [n_vis_op][8] operator traversal: {cell, 6 neighbours, mask}
     hx::RefTab64 *ref = nullptr;  // device copy of the tables of degree k
     hx::RefTab64 ref_host{};
     double *vol = nullptr;        // [n_cells]
@@ -166,7 +166,8 @@ struct hx_ctx {
     double *psK = nullptr;        // [n_cells][16]     detJ J^-1 (9), detJ / (gamma - 1) of affine cells
     double *psFn = nullptr;       // [n_cells][6][3][nf] outward ds n on the own faces
     double *psFh = nullptr;       // [n_cells][6][nf]  h rho on the own faces
-    double *psWork = nullptr;     // [7][n_dofs]       velocity temporaries and C A^-1 B x
+    double *psWork = nullptr;     // [7][n_dofs]       velocity temporaries; S: point values and own
+                                  //                   fluxes [n_cells][6][nf] from the fourth on
     // Chebyshev preconditioner: degree and interval of M^-1 A (M = block Jacobi)
     int cheb_deg = 0;
     double cheb_lo = 0.0, cheb_hi = 0.0;

@@ -9,9 +9,10 @@ namespace hx {
 
 // The whole operator computes the quarters in its own launch.  From n = 7 its
 // registers leave two waves per SIMD, too few for the quarters' latencies:
-// there a launch of their own is faster.  32x8x16 cells refined over the
-// ridge, FP64, own launch / operator's: degree 1 15.3 / 11.7 us, 4 45.4 /
-// 43.0, 5 93.0 / 89.8, 6 118.5 / 128.8, 7 167.7 / 179.4.
+// there a launch of their own is faster on meshes that fill the chip.  32x8x16
+// cells refined over the ridge, FP64, own launch / operator's: degree 1 14.4 /
+// 11.6 us, 4 43.5 / 40.8, 5 92.3 / 88.1, 6 116.2 / 125.9, 7 168.7 / 179.7 (FP32
+// 65.5 / 60.4, 79.5 / 86.9; 16x4x8 cells, FP64, 31.8 / 28.5, 43.1 / 40.0).
 constexpr bool hang_in_operator(int n) { return n < 7; }
 
 // contributions of one quarter to the test functions of both cells (one

@@ -8,11 +8,13 @@
 // outward normal) come from the fine side; the minus cell is the one whose
 // +d face it is; sigma = P (k+1)^2 max(|S|/|K_fine|, |S|/|K_coarse|).
 //
-// The operator kernel treats these faces as absent (neighbour -2); after it,
-// k_hang_apply computes each quarter's contributions to the test functions
-// of both cells (one workgroup per quarter, no atomics) into a staging
-// buffer, and k_hang_gather adds them to y cell by cell in a fixed order, so
-// results stay bitwise reproducible.  The set-up kernels evaluate the basis
+// The operator kernel treats these faces as absent (neighbour -2).  Each
+// quarter's contributions to the test functions of both cells go to a staging
+// buffer (hang_quarter.hpp, one workgroup per quarter, no atomics): up to n = 6
+// in the operator's own launch (k_apply_hang), from n = 7 on and for the face
+// part alone by k_hang_apply after it (hang_in_operator).  k_hang_gather then
+// adds them to y cell by cell in a fixed order, so results stay bitwise
+// reproducible.  The set-up kernels evaluate the basis
 // and the map at the points directly (Lagrange evaluation); the apply kernel
 // sum-factorises on the face.
 //

@@ -637,7 +637,9 @@ __device__ __forceinline__ f32x4 back_mfma(const uint16_t (*sA)[LDA], const uint
 // masks its signal and keeps the value in a register.  The bound is each
 // workgroup's chain of five layers (weights from L2, products, barrier), so a
 // layer's weights are requested before the previous layer's products, at
-// degrees up to 4 (above, their registers would spill).
+// degrees up to 4 (above, their registers would spill; degrees 6 and 7 spill 8
+// and 11 of the 128 registers of a wave as it is: 57 and 65 us for the step at
+// 2,048 rows, where the chain of products took 787 and 736).
 template <int N>
 __global__ void __launch_bounds__(64 * FW)
 k_train_fb(int64_t B, const float *__restrict__ feats, const float *__restrict__ targets,

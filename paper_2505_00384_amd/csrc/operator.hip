@@ -945,11 +945,13 @@ k_apply_split(const T *__restrict__ x, T *__restrict__ y, const T *__restrict__ 
 
 // The two-wave form where a launch of nwg one-wave workgroups leaves at most
 // one to a SIMD (256 CUs of 4): its time is then a single wave's chain.  One
-// wave / two, FP64, 8x8x8 cells: degree 3 6.7 / 5.8 us, 4 7.6 / 6.1, 5 10.0 /
-// 7.7, 6 12.2 / 9.3, 7 15.9 / 11.2; 16x8x8 cells, degree 6 14.3 / 11.9; FP32
-// 8x8x8 degree 4 6.4 / 6.0, 7 11.0 / 8.2.  With two waves per SIMD the one-wave
-// form catches up (degree 6, 16x16x8 cells: 21.0 / 22.0).  At degree 1, and in
-// FP32 at degree 2, the launch itself takes the time (5.1 / 6.0).
+// wave / two, FP64, 8x8x8 cells: degree 3 6.5 / 4.7 us, 4 7.5 / 5.6, 5 9.6 /
+// 7.1, 6 11.6 / 8.8, 7 15.2 / 10.7; 16x8x8 cells, degree 6 13.5 / 11.3; FP32
+// 8x8x8 degree 4 6.2 / 4.8, 7 10.4 / 7.5.  With two waves per SIMD the one-wave
+// form catches up in FP64 (16x16x8 cells, degree 6 19.8 / 20.5, 7 26.1 / 29.3;
+// FP32 13.5 / 11.4, 15.4 / 15.9), though not where a round of waves more is
+// nearly empty (2,197 cells, degree 6: 31.3 / 26.0).  At degree 1, and in FP32 at
+// degree 2, the launch itself takes the time.
 constexpr int SPLIT_MAX = 1024;
 constexpr bool split_degree(int n, bool f64) { return n >= (f64 ? 3 : 4); }
 
@@ -958,7 +960,9 @@ constexpr bool split_degree(int n, bool f64) { return n >= (f64 ? 3 : 4); }
 // contributions into the staging buffer, one each, the others the conforming
 // part.  The quarters need x only; for 32x8x16 cells refined over the ridge,
 // degree 4, they took 7.8 of 46.9 us in a launch of their own after it, and
-// all takes 40.9 us now.
+// all takes 40.8 us now.  Three waves per SIMD as in the operator, though the
+// FP64 kernel of both kinds spills 6 registers at N = 5: with two, and no
+// spills, 42.1 us (8x4x4 cells 11.6 instead of 11.9).
 template <typename T>
 struct HangArgs {
     const int32_t *hang;
@@ -1151,8 +1155,9 @@ hipError_t apply_conforming(hx_ctx *c, const T *x, T *y, const T *b, double *dpa
 }
 
 // the operator, with the terms of the non-conforming quarter faces in its
-// launch or in one of their own, and their addition after it; with quarter faces the fused x.(A x) of the CG variant is not used
-// (the callers take the dot product after the whole operator)
+// launch or in one of their own, and their addition after it; with quarter
+// faces the fused x.(A x) of the CG variant is not used (the callers take the
+// dot product after the whole operator)
 template <typename T>
 hipError_t apply_dispatch(hx_ctx *c, const T *x, T *y, const T *b, double *dpart = nullptr,
                           int *nwg = nullptr, int part = 0)

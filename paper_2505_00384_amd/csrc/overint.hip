@@ -42,7 +42,10 @@
 // that at N = 8 two workgroups share a CU's 160 KB, and its cell integrals
 // take two waves: degree 6 1830 / 1696 us, 7 4794 / 2587; 96 cells, degree 7,
 // 36.4 / 26.4 (the former form 29.5).  N = 6 is slower without the LDS copy
-// (923 us), and two cell waves lose at N = 5 (521), 6 (1032) and 7 (1783).
+// (923 us), and two cell waves lose at N = 5 (521), 6 (1032) and 7 (1783).  The
+// bound on the waves per SIMD matters at N = 6 only, which has room for three
+// with its 159 registers (737 us when three are asked for); N = 4 and 5 take the
+// same times with one less.
 #include "common.hpp"
 #include "wave_sync.hpp"
 

@@ -980,7 +980,11 @@ __device__ __forceinline__ void sys_cell(const double *__restrict__ x, double *_
 }
 
 // MODE: the waves' cells are general (0), affine (1) or of either kind, the
-// first record of a wave telling which (2), as in the operator kernel
+// first record of a wave telling which (2), as in the operator kernel.  One
+// launch of both kinds gives the affine waves the registers of the general ones
+// (236 instead of 110 at N = 5), but a launch for each kind is slower: terrain
+// 64x32x32, both passes, degree 2 131 / 146 us, 4 281 / 302, 7 1130 / 1186 (5 780
+// / 760), and 8x4x3 cells, degree 4, 11.6 / 17.1.
 template <int N, int MODE>
 __global__ void __launch_bounds__(64, SysCfg<N>::WAVES)
 k_sys_cell(const double *__restrict__ x, double *__restrict__ r, double *__restrict__ flux,
