@@ -297,6 +297,20 @@ def consistent_bytes_per_dof(ctx, k):
     return 16 + 8 * values / (n["cells"] * (k + 1) ** 3)
 
 
+def pressure_bytes_per_dof(ctx, k):
+    """Algorithmic bytes per dof of the pressure system S in its two passes: x,
+    the point values between the passes and y, the own face fluxes written and
+    read, h rho at the face points; on general cells the nine metric values,
+    both masses and h rho per point and ds n on the own faces, on affine ones
+    two values per point and ten constants."""
+    n = k + 1
+    c, _ = ctx.operator_info()
+    aff = c["affine_cells"] / c["cells"]
+    faces = 8.0 * 6 / n
+    general, affine = 8.0 * 12 + 3 * faces, 16 + 80.0 / n ** 3
+    return 32 + 3 * faces + (1 - aff) * general + aff * affine
+
+
 def consistent_suite(ctx, torch, k, reps=10):
     """The operator with consistent integration (2k+1 Gauss points): time per
     application, algorithmic bytes (consistent_bytes_per_dof: cell and face data, x
@@ -437,7 +451,7 @@ def kernels_suite(hx, ctx, torch, dev, dims, k, reps):
     FP64 and FP32 operator, block Jacobi in both precisions, the learned
     correction (seeded random network), the consistent-integration operator,
     the multigrid restriction and prolongation to the 2x coarser channel, and
-    the pressure parts B (gradient) and C (divergence)."""
+    the pressure parts B (gradient) and C (divergence) and the system S."""
     import synth_inputs as si
     n = ctx.n_dofs
     nd = (k + 1) ** 3
@@ -502,6 +516,7 @@ def kernels_suite(hx, ctx, torch, dev, dims, k, reps):
     u3 = torch.stack([field_on_device(si.rhs_terrain(s_), xyz, torch) for s_ in (6, 7, 8)])
     rec("pressure_B", lambda: ctx.apply_pressure_part(hx.HX_PS_GRAD, x), 132.8)
     rec("pressure_C", lambda: ctx.apply_pressure_part(hx.HX_PS_DIV, u3), 142.4)
+    rec("pressure_S", lambda: ctx.apply_pressure_part(hx.HX_PS_SYSTEM, x), pressure_bytes_per_dof(ctx, k))
     del u3, xyz, x, y
     return out
 
